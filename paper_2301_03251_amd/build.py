@@ -21,7 +21,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libqlayer.so")
-SOURCES = ["tile.hip", "kernels.hip", "api.cpp", "plan.cpp"]
+SOURCES = ["tile.hip", "kernels.hip", "runs.hip", "api.cpp", "plan.cpp", "runs.cpp"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"

@@ -20,6 +20,7 @@
 
 #include "launch.hpp"
 #include "plan.hpp"
+#include "runs_launch.hpp"
 
 using namespace qlayer;
 
@@ -42,6 +43,7 @@ struct Tables {
     size_t off_xptr = 0, off_xslot = 0, off_wptr = 0, off_wslot = 0, off_gates = 0, off_diag = 0;
     size_t off_fuse = 0, off_czg = 0, off_pthr = 0;
     size_t off_pptr = 0, off_pops = 0;  // product-prefix CSR (per qubit)
+    size_t off_rstep = 0, off_rent = 0, off_rmem = 0, off_rword = 0;  // run plan
     std::vector<DevPass> passes;
     int n_diags = 0, n_fuses = 0;
     int n_ops = 0;
@@ -56,12 +58,14 @@ size_t put(std::vector<uint8_t>& blob, const std::vector<T>& v) {
     return off;
 }
 
-void build_tables(const Circuit& c, int dt, Tables& T) {
+// Tables of a circuit that the run kernel takes (rp), or of its tile or
+// whole-state plan.
+void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
     const Plan& pl = c.plan[dt];
     std::vector<DevPass> passes;
     std::vector<DevOp> ops;
     std::vector<int32_t> gsl;
-    if (!pl.whole_state) {
+    if (!pl.whole_state && !rp) {
         for (const PassPlan& pp : pl.passes) {
             DevPass d{};
             d.k = pl.k;
@@ -111,15 +115,25 @@ void build_tables(const Circuit& c, int dt, Tables& T) {
     for (const Gate& g : c.gates) gates.push_back({g.kind, g.q0, g.q1, g.slot});
 
     T.blob.clear();
-    T.off_pass = put(T.blob, passes);
-    T.off_phase = put(T.blob, pl.phases);
-    T.off_ops = put(T.blob, ops);
-    T.off_gslot = put(T.blob, gsl);
     T.off_slots = put(T.blob, slots);
     T.off_xptr = put(T.blob, xptr);
     T.off_xslot = put(T.blob, xs);
     T.off_wptr = put(T.blob, wptr);
     T.off_wslot = put(T.blob, ws);
+    if (rp) {
+        std::vector<RunRecord> rec;
+        for (const DevRunStep& st : rp->steps) rec.push_back(run_record(st));
+        T.off_rstep = put(T.blob, rec);
+        T.off_rent = put(T.blob, rp->entries);
+        T.off_rmem = put(T.blob, rp->members);
+        T.off_rword = put(T.blob, rp->words);
+        T.blob.resize(align256(T.blob.size()), 0);
+        return;
+    }
+    T.off_pass = put(T.blob, passes);
+    T.off_phase = put(T.blob, pl.phases);
+    T.off_ops = put(T.blob, ops);
+    T.off_gslot = put(T.blob, gsl);
     T.off_gates = put(T.blob, gates);
     T.off_diag = put(T.blob, pl.diags);
     T.n_diags = (int)pl.diags.size();
@@ -154,6 +168,11 @@ void build_tables(const Circuit& c, int dt, Tables& T) {
     T.n_ops = (int)ops.size();
 }
 
+// The run kernel's largest circuits by default, and its LDS budget (gfx950
+// has 160 KiB per CU).
+constexpr int RUNS_DEFAULT_QUBITS = 11;
+constexpr size_t RUNS_LDS_MAX = 160 * 1024;
+
 struct Layout {
     size_t tables = 0, coef = 0, opc = 0, dzc = 0, fzc = 0, zpart = 0, gpart = 0, psi = 0, lam = 0, total = 0;
     size_t enorm = 0, edot = 0;  // embedding: per-circuit |x| or basis index; L_b
@@ -174,6 +193,8 @@ bool mul_ok(size_t a, size_t b, size_t& out) {
 
 struct ql_circuit {
     Circuit c;
+    RunPlan rp;
+    bool runs[2] = {false, false};  // per dtype: the run kernel takes every call
     Tables t[2];
     // pinned host copies of the table blobs (made on the first call of each
     // dtype), so the per-call upload is an asynchronous DMA
@@ -206,7 +227,8 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     const int maxq = dt == 0 ? QL_MAX_QUBITS_C64 : QL_MAX_QUBITS_C128;
     if (c.n > maxq) return fail(QL_EUNSUPPORTED, "too many qubits for this dtype");
     L = Layout{};
-    if (pl.whole_state) {
+    const bool runs = h->runs[dt], one = runs || pl.whole_state;  // one workgroup per sample, state on chip
+    if (one) {
         L.n_wg = 1;
     } else {
         const int64_t tiles = (int64_t)1 << (c.n - pl.k);
@@ -228,8 +250,8 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     off = align256(off + h->t[dt].blob.size());
     L.coef = off;
     if (!mul_ok((size_t)B * (size_t)std::max(1, (int)c.slots.size()), amp, sz)) return fail(QL_ENOMEM, "size overflow");
-    off = align256(off + sz);
-    if (!pl.whole_state) {
+    if (!runs) off = align256(off + sz);
+    if (!one) {
         // per-sample op records (16 bytes fp32 / 32 bytes fp64) plus an end record
         L.opc = off;
         if (!mul_ok((size_t)B * (size_t)(h->t[dt].n_ops + 1), dt == 0 ? 16 : 32, sz))
@@ -248,7 +270,7 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     L.zpart = off;
     if (!mul_ok((size_t)B * (size_t)L.n_wg, (size_t)c.n * 8, sz)) return fail(QL_ENOMEM, "size overflow");
     off = align256(off + sz);
-    if (pl.product) {
+    if (pl.product && !runs) {
         // per circuit and qubit the prefix factor (phi(0), phi(1)), complex fp64
         L.phi = off;
         if (!mul_ok((size_t)B, (size_t)c.n * 32, sz)) return fail(QL_ENOMEM, "size overflow");
@@ -260,7 +282,7 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
             return fail(QL_ENOMEM, "size overflow");
         off = align256(off + sz);
     }
-    if (bwd && pl.product) {
+    if (bwd && pl.product && !runs) {
         // per sample, environment workgroup and qubit: (re, im) of r_q(0) and r_q(1), fp64
         L.env = off;
         if (!mul_ok((size_t)B * (size_t)env_workgroups(dt, c.n, B), (size_t)c.n * 32, sz))
@@ -273,12 +295,12 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     // gives each forward pass but the last its own output buffer, which the
     // backward pass over the next pass reads instead of a stored
     // un-computed state.
-    const bool multi = !pl.whole_state && pl.passes.size() > 1;
-    const bool emb = c.embed != E_NONE, amp_bwd = bwd && c.embed == E_AMPLITUDE;
+    const bool multi = !one && pl.passes.size() > 1;
+    const bool emb = c.embed != E_NONE && !runs, amp_bwd = bwd && c.embed == E_AMPLITUDE && !runs;
     const bool keep = multi && mode == QL_MODE_FWD_BWD_KEEP;
     // the product prefix's environment reads lambda at the end of the backward sweep
     const bool need_psi = own_psi && (emb || (multi && !keep));
-    const bool need_lam = (bwd && multi) || amp_bwd || (bwd && !pl.whole_state && pl.product);
+    const bool need_lam = (bwd && multi) || amp_bwd || (bwd && !one && pl.product);
     size_t st = 0;
     if (need_psi || need_lam || keep)
         if (!mul_ok((size_t)B, ((size_t)1 << c.n) * amp, st)) return fail(QL_ENOMEM, "size overflow");
@@ -392,9 +414,10 @@ struct Ctx {
     Layout L;
     hipStream_t stream;
     Timer tm;
+    bool runs = false;      // the run kernel takes the call
     bool no_alloc = false;  // make no host or device allocation (no pinned copy, no event)
-    // the angle sources of the current circuits (set by bind(); the
-    // one-wavefront kernel binds the angles itself)
+    // the angle sources of the current circuits (set by bind(); the run
+    // kernel binds the angles itself)
     const void* inputs = nullptr;
     const void* weights = nullptr;
     int64_t v0 = 0;
@@ -458,13 +481,13 @@ PrefixArgs prefix_args(const Ctx& x, int64_t B) {
 // copies of a parameter-shift chunk: circuit i is virtual circuit v = v0 + i,
 // sample v / vper, and v % vper = 2s+1 (2s+2) shifts rotation slot s by
 // +pi/2 (-pi/2).
-int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0, int32_t vper, bool bwd) {
+int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0, int32_t vper) {
     hipError_t e;
     x.inputs = inputs;
     x.weights = weights;
     x.v0 = v0;
     x.vper = vper;
-    if (x.pl.whole_state && whole_uses_wave(x.c.n, bwd, B)) return QL_OK;  // bound in the kernel
+    if (x.runs) return QL_OK;  // bound in the kernel
     if (x.pl.whole_state) {
         BindArgs ba{};
         ba.inputs = inputs;
@@ -515,7 +538,7 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
 // buffer or the workspace's). Circuit i is sample i, or sample (v0 + i) / vper
 // of a parameter-shift chunk.
 int embed(Ctx& x, int64_t B, const void* inputs, void* psi, int64_t v0, int32_t vper) {
-    if (x.c.embed == E_NONE) return QL_OK;
+    if (x.c.embed == E_NONE || x.runs) return QL_OK;
     EmbedArgs ea{};
     ea.inputs = inputs;
     ea.psi = psi;
@@ -531,6 +554,59 @@ int embed(Ctx& x, int64_t B, const void* inputs, void* psi, int64_t v0, int32_t 
     hipError_t e = launch_embed(x.dt, ea, x.stream);
     x.tm.stop();
     return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("k_embed: ") + hipGetErrorString(e));
+}
+
+// The run kernel over B circuits: states, <Z> (into expz) and, bwd, every
+// gradient but the weights' sum over the batch (terms in gpart).
+int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, void* grad_inputs, void* grad_weights,
+              void* psi_out) {
+    const Circuit& c = x.c;
+    const RunPlan& rp = x.h->rp;
+    const uint8_t* tab = x.W + x.L.tables;
+    RunArgs a{};
+    a.steps = (const uint2*)(tab + x.T.off_rstep);
+    a.entries = (const DevRunEntry*)(tab + x.T.off_rent);
+    a.members = (const DevRunMember*)(tab + x.T.off_rmem);
+    a.words = (const uint32_t*)(tab + x.T.off_rword);
+    for (int p = 0; p < c.n; p++) {
+        a.first_qubit |= (uint64_t)rp.first_qubit[p] << (4 * p);
+        a.last_qubit |= (uint64_t)rp.last_qubit[p] << (4 * p);
+    }
+    a.slots = (const SlotSrc*)(tab + x.T.off_slots);
+    a.x_ptr = (const int32_t*)(tab + x.T.off_xptr);
+    a.x_slot = (const int32_t*)(tab + x.T.off_xslot);
+    a.w_ptr = (const int32_t*)(tab + x.T.off_wptr);
+    a.w_slot = (const int32_t*)(tab + x.T.off_wslot);
+    a.inputs = x.inputs;
+    a.weights = x.weights;
+    a.grad_out = grad_out;
+    a.expz = expz;
+    a.psi_out = psi_out;
+    a.grad_inputs = bwd && c.n_inputs > 0 ? grad_inputs : nullptr;
+    a.grad_weights = bwd && B == 1 ? grad_weights : nullptr;
+    a.gpart = bwd && B > 1 && grad_weights ? (double*)(x.W + x.L.gpart) : nullptr;
+    a.B = B;
+    a.v0 = x.v0;
+    a.vper = x.vper;
+    a.bwd = bwd ? 1 : 0;
+    a.n = c.n;
+    a.log_t = rp.log_t;
+    a.F = c.n_inputs;
+    a.P = c.n_weights;
+    a.n_slots = (int)c.slots.size();
+    a.n_steps = (int)rp.steps.size() - 1;
+    a.prefix = rp.prefix;
+    a.n_entries = (int)rp.entries.size();
+    a.n_members = (int)rp.members.size();
+    a.n_words = (int)rp.words.size();
+    a.embed = c.embed;
+    a.first = c.embed_first;
+    a.lds = runs_lds(x.dt, rp, a.n_slots, bwd);
+    if (a.lds.total > g_lds_limit) return fail(QL_EUNSUPPORTED, "state does not fit in LDS");
+    x.tm.start(1);
+    hipError_t e = launch_runs(x.dt, rp.log_r, a, std::max(64, 1 << rp.log_t), x.stream);
+    x.tm.stop();
+    return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("k_runs: ") + hipGetErrorString(e));
 }
 
 // The state passes of B circuits: the whole-state kernel, or the forward tile
@@ -557,12 +633,6 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         wa.bwd = bwd ? 1 : 0;
         wa.B = B;
         wa.coef = x.W + x.L.coef;
-        wa.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
-        wa.inputs = x.inputs;
-        wa.weights = x.weights;
-        wa.F = c.n_inputs;
-        wa.v0 = x.v0;
-        wa.vper = x.vper;
         wa.grad_out = grad_out;
         wa.zpart = zpart;
         wa.gpart = gpart;
@@ -711,11 +781,16 @@ int run(const ql_circuit* hc, ql_dtype dtype, int64_t B, int mode, const void* i
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}, h->runs[dt]};
     x.no_alloc = no_alloc;
     if (no_alloc) x.tm.h = nullptr;  // no timing events either
     if ((rc = upload_tables(x))) return rc;
-    if ((rc = bind(x, B, inputs, weights, 0, 0, bwd))) return rc;
+    if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
+    if (x.runs) {
+        if ((rc = run_steps(x, B, bwd, grad_out, expz, grad_inputs, grad_weights, nullptr))) return rc;
+        if (bwd && B > 1 && grad_weights && h->c.n_weights > 0) return reduce(x, B, true, nullptr, nullptr, grad_weights);
+        return QL_OK;
+    }
     if ((rc = embed(x, B, inputs, x.L.psi ? (void*)(x.W + x.L.psi) : nullptr, 0, 0))) return rc;
     if ((rc = state_passes(x, B, bwd, grad_out))) return rc;
     if (bwd && x.pl.product) {  // the prefix rotations' gradient terms, into gpart
@@ -795,17 +870,21 @@ int param_shift(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inp
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, S.L, stream, Timer{h, stream}};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, S.L, stream, Timer{h, stream}, h->runs[dt]};
     if ((rc = upload_tables(x))) return rc;
     const int32_t V = (int32_t)(2 * h->c.n_param_slots + 1);
     void* ev = x.W + S.ev;
     double* dv = (double*)(x.W + S.dv);
     for (int64_t v0 = 0; v0 < S.total; v0 += S.chunk) {
         const int64_t cb = std::min(S.chunk, S.total - v0);
-        if ((rc = bind(x, cb, inputs, weights, v0, V, false))) return rc;
+        if ((rc = bind(x, cb, inputs, weights, v0, V))) return rc;
         if ((rc = embed(x, cb, inputs, x.L.psi ? (void*)(x.W + x.L.psi) : nullptr, v0, V))) return rc;
-        if ((rc = state_passes(x, cb, false, nullptr))) return rc;
-        if ((rc = reduce(x, cb, false, ev, nullptr, nullptr))) return rc;
+        if (x.runs) {
+            if ((rc = run_steps(x, cb, false, nullptr, ev, nullptr, nullptr, nullptr))) return rc;
+        } else {
+            if ((rc = state_passes(x, cb, false, nullptr))) return rc;
+            if ((rc = reduce(x, cb, false, ev, nullptr, nullptr))) return rc;
+        }
         ShiftDotArgs sa{};
         sa.ev = ev;
         sa.grad_out = grad_out;
@@ -856,9 +935,10 @@ int state(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inputs, c
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}, h->runs[dt]};
     if ((rc = upload_tables(x))) return rc;
-    if ((rc = bind(x, B, inputs, weights, 0, 0, false))) return rc;
+    if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
+    if (x.runs) return run_steps(x, B, false, nullptr, nullptr, nullptr, nullptr, psi);
     if ((rc = embed(x, B, inputs, psi, 0, 0))) return rc;
     if ((rc = state_passes(x, B, false, nullptr, psi))) return rc;
     if (x.pl.whole_state) return QL_OK;  // exact gates: no phase to undo
@@ -918,6 +998,21 @@ Options to_options(const ql_options* o) {
     return r;
 }
 
+// Whether the run kernel takes a circuit's calls: small states planned with
+// the default options (the options describe tile plans), whose matrices and
+// sums fit in LDS beside the state.
+void choose_runs(ql_circuit* h) {
+    const Circuit& c = h->c;
+    const Options& o = c.opts;
+    const bool plain = !o.log_regs && !o.log_threads && !o.low_qubits && !o.max_gates_per_pass && !o.force_tiled &&
+                       !o.wg_per_sample && !o.rz_groups && !o.pass_search && !o.product_prefix && !o.cz_groups;
+    if (c.n > RUNS_DEFAULT_QUBITS || (c.n >= 8 && !plain)) return;
+    build_run_plan(c, h->rp);
+    if (!h->rp.ok) return;
+    for (int dt = 0; dt < 2; dt++)
+        h->runs[dt] = runs_lds(dt, h->rp, (int)c.slots.size(), true).total <= RUNS_LDS_MAX;
+}
+
 }  // namespace
 
 extern "C" {
@@ -942,8 +1037,10 @@ int ql_circuit_create_desc(int32_t n_qubits, const ql_gate* gates, int32_t n_gat
     try {
         err = build_circuit(n_qubits, (const int32_t*)gates, n_gates, n_inputs, n_weights, ext,
                             to_options(opts), h->c);
-        if (err.empty())
-            for (int dt = 0; dt < 2; dt++) build_tables(h->c, dt, h->t[dt]);
+        if (err.empty()) {
+            choose_runs(h);
+            for (int dt = 0; dt < 2; dt++) build_tables(h->c, dt, h->runs[dt] ? &h->rp : nullptr, h->t[dt]);
+        }
     } catch (const std::bad_alloc&) {
         delete h;
         return fail(QL_ENOMEM, "host allocation failed");

@@ -1,0 +1,58 @@
+"""The run kernel's plans, on the CPU: every step list carried out on the host
+(forward and back) equals the circuit's gates applied one by one. Covers every
+gate kind, controlled rotations, Pauli channels, embeddings and every qubit
+count the kernel takes, and reads no table outside its bounds (g++ sanitizers)."""
+
+from __future__ import annotations
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "sanitize")
+CSRC = os.path.join(ROOT, "paper_2301_03251_amd", "csrc")
+ALL = (W.H, W.RX, W.RY, W.RZ, W.CNOT, W.CZ, W.CRX, W.CRY, W.CRZ)
+
+
+def _record(f, n, gates, F, P, embed=(0, 0), pauli_p=None):
+    gates = np.ascontiguousarray(gates, np.int32).reshape(-1, 5)
+    pp = np.zeros((0, 3)) if pauli_p is None else np.asarray(pauli_p, np.float64).reshape(-1, 3)
+    np.array([n, gates.shape[0], F, P, embed[0], embed[1], pp.shape[0], 1], np.int32).tofile(f)
+    gates.tofile(f)
+    np.ascontiguousarray(pp, np.float64).tofile(f)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_run_plans_on_the_host(tmp_path):
+    path = str(tmp_path / "circuits.bin")
+    with open(path, "wb") as f:
+        for name in ("4q", "10q", "qae"):
+            wl = W.get(name)
+            _record(f, wl.n, wl.gates(), wl.n_inputs, wl.n_weights, embed=getattr(wl, "embed", None) or (0, 0))
+        for n in range(1, 13):
+            for seed in range(6):
+                kinds = [ALL, (W.RX, W.RY, W.RZ, W.CNOT), (W.H, W.RZ, W.CZ, W.RY), (W.CRX, W.CRY, W.CRZ, W.RZ, W.RX),
+                         (W.CNOT, W.CZ, W.RZ, W.RX), (W.CNOT, W.CRY, W.H)][seed]
+                _record(f, n, W.random_circuit(n, 12 * n + 10, 4, 6, seed=100 * n + seed, kinds=kinds), 4, 6,
+                        embed=(W.EMBED_AMPLITUDE, 0) if seed == 9 else (0, 0))
+            layered = W.layered_circuit(n, "h_rz" if n % 2 else "ry", 3, (W.RY, W.RZ), W.CZ if n % 2 else W.CNOT,
+                                        ("ring", "linear", "brick")[n % 3])
+            noisy, pp, k = W.with_depolarizing(layered, n, n, 0.3, every=max(len(layered) // 4, 1))
+            _record(f, n, noisy, n + k, 6 * n, pauli_p=pp)
+            _record(f, n, layered, max(n, 1), 6 * n, embed=(W.EMBED_BASIS, 0))
+            _record(f, n, W.random_circuit(n, 60, 1 << n, 6, seed=n, kinds=ALL), 1 << n, 6,
+                    embed=(W.EMBED_AMPLITUDE, 0))
+            _record(f, n, np.zeros((0, 5), np.int32), 1, 1)
+    exe = str(tmp_path / "runs_driver")
+    subprocess.run(["g++", "-std=c++17", "-g", "-O1", "-Wall", "-fsanitize=address,undefined", "-fno-sanitize-recover=all",
+                    f"-I{CSRC}", os.path.join(HERE, "runs_driver.cpp"), os.path.join(CSRC, "runs.cpp"),
+                    os.path.join(CSRC, "plan.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe, path, "v"], capture_output=True, text=True, timeout=600)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+    assert "cases 123 " in r.stdout
