@@ -161,7 +161,7 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
             }
     }
     T.off_pthr = put(T.blob, pthr);
-    T.off_pptr = put(T.blob, pl.pre_ptr);
+    T.off_pptr = put(T.blob, pl.product ? pl.pre_ptr : std::vector<int32_t>(c.n + 1, 0));
     T.off_pops = put(T.blob, pl.pre_ops);
     T.blob.resize(align256(T.blob.size()), 0);
     T.passes = passes;
@@ -270,7 +270,7 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     L.zpart = off;
     if (!mul_ok((size_t)B * (size_t)L.n_wg, (size_t)c.n * 8, sz)) return fail(QL_ENOMEM, "size overflow");
     off = align256(off + sz);
-    if (pl.product && !runs) {
+    if ((pl.product || !own_psi) && !one) {
         // per circuit and qubit the prefix factor (phi(0), phi(1)), complex fp64
         L.phi = off;
         if (!mul_ok((size_t)B, (size_t)c.n * 32, sz)) return fail(QL_ENOMEM, "size overflow");
@@ -454,6 +454,7 @@ int upload_tables(Ctx& x) {
         x.h->uploads.push_back({x.stream, ev});
     }
     e = hipEventRecord(ev, x.stream);
+    double* phase = nullptr;  // ql_state: factor on every circuit's initial state
     return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
 }
 
@@ -507,6 +508,7 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ba.inputs = inputs;
         ba.weights = weights;
         ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+    pa.phase = x.phase;
         ba.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
         ba.opc = x.W + x.L.opc;
         ba.diags = (const DevDiag*)(x.W + x.L.tables + x.T.off_diag);
@@ -523,7 +525,8 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ba.vper = vper;
         x.tm.start(2);
         e = launch_bind_tile(x.dt, ba, x.stream);
-        if (e == hipSuccess && x.pl.product) {
+        if (e == hipSuccess && x.phase) e = launch_state_phase(x.dt, ba, x.phase, x.stream);
+        if (e == hipSuccess && (x.pl.product || (x.phase && x.c.embed == E_NONE))) {
             PrefixArgs pa = prefix_args(x, B);
             pa.v0 = v0;
             pa.vper = vper;
@@ -583,6 +586,7 @@ int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, voi
     a.expz = expz;
     a.psi_out = psi_out;
     a.grad_inputs = bwd && c.n_inputs > 0 ? grad_inputs : nullptr;
+    ea.phase = x.phase;
     a.grad_weights = bwd && B == 1 ? grad_weights : nullptr;
     a.gpart = bwd && B > 1 && grad_weights ? (double*)(x.W + x.L.gpart) : nullptr;
     a.B = B;
@@ -679,7 +683,7 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         ta.n_wg = x.L.n_wg;
         ta.flags = flags;
         ta.n_gslots = (flags & PF_BWD) ? d.n_gslots : 0;
-        ta.phi = pl.product ? (const double*)(x.W + x.L.phi) : nullptr;
+        ta.phi = pl.product || x.phase ? (const double*)(x.W + x.L.phi) : nullptr;
         // dynamic LDS: <Z> scratch and gradient accumulators (the exchange
         // buffer is static)
         const size_t st = tile_static_lds(x.dt, pl.log_r, threads), real = x.dt == 0 ? 4 : 8;
@@ -697,7 +701,7 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
     // factors) in registers unless an embedding wrote the initial state; the
     // last backward pass stores lambda_0 when the amplitude-embedding gradient
     // or the product prefix's environment needs it
-    const int init = emb ? 0 : (pl.product ? PF_PRODUCT : PF_INIT);
+    const int init = emb ? 0 : (pl.product || x.phase ? PF_PRODUCT : PF_INIT);
     const int lam0 = (amp_bwd || pl.product) ? PF_STORE_LAM : 0;
     for (int p = 0; p + 1 < m; p++) {
         void* out = keep ? kept(p) : psi_buf;
@@ -940,23 +944,7 @@ int state(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inputs, c
     if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
     if (x.runs) return run_steps(x, B, false, nullptr, nullptr, nullptr, nullptr, psi);
     if ((rc = embed(x, B, inputs, psi, 0, 0))) return rc;
-    if ((rc = state_passes(x, B, false, nullptr, psi))) return rc;
-    if (x.pl.whole_state) return QL_OK;  // exact gates: no phase to undo
-    BindTileArgs ba{};
-    ba.inputs = inputs;
-    ba.weights = weights;
-    ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
-    ba.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
-    ba.diags = (const DevDiag*)(x.W + x.L.tables + x.T.off_diag);
-    ba.n_diags = x.T.n_diags;
-    ba.fuses = (const DevFuse*)(x.W + x.L.tables + x.T.off_fuse);
-    ba.n_fuses = x.T.n_fuses;
-    ba.B = B;
-    ba.n_ops = x.T.n_ops;
-    ba.bwd_first = x.T.bwd_first;
-    ba.F = h->c.n_inputs;
-    hipError_t e = launch_state_phase(dt, ba, (double*)(x.W + x.L.zpart), psi, h->c.n, stream);
-    return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("state phase: ") + hipGetErrorString(e));
+    return state_passes(x, B, false, nullptr, psi);
 }
 
 // Blocks of 2^bb amplitudes for shot sampling.
@@ -970,6 +958,8 @@ int sample_blocks(int n, int& bb, int64_t& nblk) {
 int sample_bytes(int n, int64_t B, size_t& out) {
     int bb;
     int64_t nblk;
+    // the tile path drops global phases: the initial states start with their inverse
+    if (!x.runs && !x.pl.whole_state) x.phase = (double*)(x.W + x.L.zpart);
     int rc = sample_blocks(n, bb, nblk);
     if (rc) return rc;
     if (B < 1) return fail(QL_EINVAL, "batch must be >= 1");

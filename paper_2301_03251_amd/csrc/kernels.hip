@@ -28,7 +28,7 @@
 //               factors of the first pass's initial state, the environment sums
 //               of lambda at the end of the backward sweep, and the prefix
 //               gates' gradient terms
-//   k_state_phase, k_phase_fix -- the global phase of the tile path's final states
+//   k_state_phase -- the global phase of the tile path's final states
 //   k_block_sums, k_block_scan, k_shots, k_shot_z -- shot sampling by inverse CDF
 #include "kcommon.hpp"
 #include "runs_launch.hpp"
@@ -510,6 +510,11 @@ __global__ void __launch_bounds__(256) k_bind_prefix(const PrefixArgs a) {
         }
         apply_gate1(g.kind, th, false, v0, v1);
     }
+    if (a.phase && q == 0) {  // the state's global phase, on one qubit's factor
+        const double2 f = make_double2(a.phase[2 * b], a.phase[2 * b + 1]);
+        v0 = zmul(v0, f);
+        v1 = zmul(v1, f);
+    }
     double2* out = (double2*)a.phi + 2 * t;
     out[0] = v0;
     out[1] = v1;
@@ -760,17 +765,22 @@ __global__ void __launch_bounds__(256) k_env_grad(const PrefixArgs a) {
 // (a factor (-1)^k per rotation whose angle moved by 2 pi k) and an RZ on a
 // register bit as diag(1, exp(i t)) (dropping exp(-i t / 2)); both are global
 // phases per sample. k_state_phase sums them over the forward ops, from the
-// same angle sources and reduction as k_bind_tile and stores the inverse
-// phase factor (cos, sin) per sample; k_phase_fix multiplies the state by it.
+// same angle sources and reduction as k_bind_tile, and stores the inverse
+// phase factor (cos, sin) per sample; the initial state starts with that
+// factor (k_bind_prefix, k_embed_write), so the final state needs no pass of
+// its own. One wavefront per sample, the lanes over the ops: one thread per
+// sample walked the ops' loads one after another (16 qubits, 8 layers, 256
+// samples: 86 us, and 43 us more to multiply the final states).
 
 template <typename Real>
-__global__ void k_state_phase(const BindTileArgs a, double* phase) {
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_state_phase(const BindTileArgs a, double* phase) {
+    const int64_t b = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int lane = threadIdx.x & 63;
     if (b >= a.B) return;
     const double pi = 3.141592653589793238463, two_pi = 2.0 * pi;
     double ph = 0.0;
     int64_t bs;
-    for (int o = 0; o < a.bwd_first; ++o) {
+    for (int o = lane; o < a.bwd_first; o += 64) {
         const DevOp op = a.ops[o];
         if (op.h == H_DZ) {  // an RZ group drops exp(-i theta / 2) per member, unreduced
             const DevDiag d = a.diags[op.arg];
@@ -787,24 +797,12 @@ __global__ void k_state_phase(const BindTileArgs a, double* phase) {
         if (op.h >= H_RYZ && op.h < H_RYZ + 5)  // the pair's RZ, as a single RZ on a register bit
             ph += 0.5 * angle_of<Real>(a.inputs, a.weights, a.F, a.slots[a.fuses[op.arg >> 16].slot], b, 0, 0, bs);
     }
+    ph = wave_sum(ph);
+    if (lane != 0) return;
     double sn, cs;  // the inverse phase factor, once per sample
     sincos(-ph, &sn, &cs);
     phase[2 * b] = cs;
     phase[2 * b + 1] = sn;
-}
-
-template <typename T2>
-__global__ void k_phase_fix(void* psi, const double* phase, int64_t B, int n) {
-    const int64_t total = B << n;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const double cs = phase[2 * (i >> n)], sn = phase[2 * (i >> n) + 1];
-        T2 v = ((T2*)psi)[i];
-        const double x = (double)v.x, y = (double)v.y;
-        v.x = (decltype(v.x))(x * cs - y * sn);
-        v.y = (decltype(v.y))(x * sn + y * cs);
-        ((T2*)psi)[i] = v;
-    }
 }
 
 // ---------------------------------------------------------------------------
@@ -864,8 +862,13 @@ __global__ void __launch_bounds__(256) k_embed_write(const EmbedArgs a) {
             const int64_t bs = a.vper > 0 ? (a.v0 + i) / a.vper : i;
             const Real v = ((const Real*)a.inputs)[bs * a.F + a.first + j];
             re = r > 0 ? (Real)((double)v / r) : (Real)0;
+            if (a.phase && r > 0) {
+                ((T2*)a.psi)[t] = mk<T2>((Real)((double)v / r * a.phase[2 * i]), (Real)((double)v / r * a.phase[2 * i + 1]));
+                continue;
+            }
         }
-        ((T2*)a.psi)[t] = mk<T2>(re, (Real)0);
+        ((T2*)a.psi)[t] = a.phase ? mk<T2>((Real)((double)re * a.phase[2 * i]), (Real)((double)re * a.phase[2 * i + 1]))
+                                  : mk<T2>(re, (Real)0);
     }
 }
 
@@ -907,14 +910,69 @@ __global__ void __launch_bounds__(256) k_embed_grad(const EmbedGradArgs a) {
 // block totals and the in-block search both lane-scan those stored sums, so
 // they see bitwise the same numbers.
 
-// Inclusive scan over the 64 lanes, Hillis-Steele, fixed order.
-__device__ __forceinline__ double lane_scan(double v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const double t = __shfl_up(v, off, 64);
-        if (lane >= off) v += t;
-    }
+// A DPP move (lanes outside the move's source or the row mask read 0).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or0(double v) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    uint2 r;
+    r.x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, ROWS, 0xF, false);
+    r.y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, ROWS, 0xF, false);
+    return __builtin_bit_cast(double, r);
+}
+
+// Inclusive scan over the 64 lanes in a fixed order: inside each 16-lane row
+// by row shifts, then row totals broadcast to the rows above (all moves on the
+// VALU; the shuffles of a scan through LDS bounded the sampling kernels).
+__device__ __forceinline__ double lane_scan(double v) {
+    v += dpp_or0<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+    v += dpp_or0<0x112, 0xF>(v);
+    v += dpp_or0<0x114, 0xF>(v);
+    v += dpp_or0<0x118, 0xF>(v);
+    v += dpp_or0<0x142, 0xA>(v);  // row 0's total to row 1, row 2's to row 3
+    v += dpp_or0<0x143, 0xC>(v);  // lane 31's to rows 2 and 3
     return v;
+}
+__device__ __forceinline__ double lane_value(double v, int l) {  // of lane l (uniform)
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    uint2 r;
+    r.x = (uint32_t)__builtin_amdgcn_readlane((int)u.x, l);
+    r.y = (uint32_t)__builtin_amdgcn_readlane((int)u.y, l);
+    return __builtin_bit_cast(double, r);
+}
+
+// Sum over all lanes of 64 values per lane, lane l keeping value l's: log2(64)
+// levels, each halving the values. On lane bit B, lanes with the bit clear keep
+// the lower half of the values and the others the upper half, and each adds
+// its partner's. Bits 5 and 4 by permlane swaps, the lower ones with the
+// partners l ^ 15, l ^ 7, l ^ 3, l ^ 1 (one DPP move each; together they reach
+// every lane of the row).
+template <int B>
+__device__ __forceinline__ double keep_half(double a, double b, int lane) {
+    if constexpr (B >= 4) {
+        uint2 x = __builtin_bit_cast(uint2, a), y = __builtin_bit_cast(uint2, b);
+        const auto lo = B == 5 ? __builtin_amdgcn_permlane32_swap(x.x, y.x, false, false)
+                               : __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false);
+        const auto hi = B == 5 ? __builtin_amdgcn_permlane32_swap(x.y, y.y, false, false)
+                               : __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+        x.x = lo[0];
+        y.x = lo[1];
+        x.y = hi[0];
+        y.y = hi[1];
+        return __builtin_bit_cast(double, x) + __builtin_bit_cast(double, y);
+    } else {
+        constexpr int CTRL = B == 3 ? 0x140 : B == 2 ? 0x141 : B == 1 ? 0x1B : 0xB1;
+        const bool up = (lane >> B) & 1;
+        const double mine = up ? b : a, theirs = up ? a : b;
+        return mine + dpp_or0<CTRL, 0xF>(theirs);
+    }
+}
+template <int B>
+__device__ __forceinline__ void keep_halves(double* v, int lane) {
+    if constexpr (B >= 0) {
+#pragma unroll
+        for (int k = 0; k < (1 << B); ++k) v[k] = keep_half<B>(v[k], v[k + (1 << B)], lane);
+        keep_halves<B - 1>(v, lane);
+    }
 }
 
 // Chunk geometry of a block: lane l covers [l * csz, l * csz + cnt_l).
@@ -927,8 +985,11 @@ __device__ __forceinline__ void chunk_of(int bb, int lane, int64_t& lo, int64_t&
 
 // One wavefront per (sample, block): the 64 chunk sums into csum and the
 // block total into bsum. The block is read in coalesced rows of 64
-// amplitudes; a row holds 64 / csz whole chunks, summed by a butterfly over
-// each group of csz lanes (fixed order), and lane c keeps chunk c's sum.
+// amplitudes. A full block (4096 amplitudes) has 64 rows of one chunk each:
+// the 64 row sums come from one reduction of 64 values per lane (bound by the
+// reads: 128 MiB of states 53 -> 35 us against a butterfly per row). Smaller
+// states: a row holds 64 / csz whole chunks, summed by a butterfly over each
+// group of csz lanes, and lane c keeps chunk c's sum. Fixed orders.
 template <typename T2>
 __global__ void __launch_bounds__(256) k_block_sums(const SampleArgs a) {
     const int lane = threadIdx.x & 63;
@@ -940,7 +1001,17 @@ __global__ void __launch_bounds__(256) k_block_sums(const SampleArgs a) {
         const int rows = bs >= 64 ? 64 / per : 1;
         const T2* p = (const T2*)a.psi + (b << a.n) + (blk << a.bb);
         double mine = 0.0;
-        for (int k = 0; k < rows; ++k) {
+        if (csz == 64) {
+            double v[64];
+#pragma unroll
+            for (int k = 0; k < 64; ++k) {
+                const T2 z = p[lane + 64 * k];
+                v[k] = (double)z.x * (double)z.x + (double)z.y * (double)z.y;
+            }
+            keep_halves<5>(v, lane);
+            mine = v[0];
+        }
+        for (int k = 0; k < rows && csz < 64; ++k) {
             const int64_t i = lane + 64 * (int64_t)k;
             double q = 0.0;
             if (i < bs) {
@@ -952,7 +1023,7 @@ __global__ void __launch_bounds__(256) k_block_sums(const SampleArgs a) {
             if (lane / per == k) mine = g;
         }
         a.csum[wv * 64 + lane] = mine;
-        const double s = lane_scan(mine, lane);
+        const double s = lane_scan(mine);
         if (lane == 63) a.bsum[wv] = s;
     }
 }
@@ -1017,18 +1088,15 @@ __global__ void __launch_bounds__(256) k_shots(const SampleArgs a, const double*
         const int64_t base = (b << a.n) + (blk << a.bb);
         const T2* p = (const T2*)a.psi;
         const double mine = cs_all[(b * a.nblk + blk) * 64 + lane];  // this lane's chunk sum
-        const double incl = lane_scan(mine, lane);
-        // shuffle with every lane active, then select (a shuffle inside the
-        // conditional would read lane 0 while it is switched off)
-        const double up = __shfl_up(incl, 1, 64);
-        const double prev = lane > 0 ? up : 0.0;
+        const double incl = lane_scan(mine);
         const uint64_t hit = __ballot(before + incl > r && ccnt > 0 && mine > 0.0);
         int L = hit ? (int)__builtin_ctzll(hit) : -1;
         if (L < 0) {  // rounding left r above the block: the last chunk of nonzero probability
             const uint64_t has = __ballot(ccnt > 0 && mine > 0.0);
             L = has ? 63 - (int)__builtin_clzll(has) : 63 - (int)__builtin_clzll(__ballot(ccnt > 0));
         }
-        const double start = before + __shfl(prev, L, 64);
+        L = __builtin_amdgcn_readfirstlane(L);
+        const double start = before + (L > 0 ? lane_value(incl, L - 1) : 0.0);
         int64_t lL, cL;
         chunk_of(a.bb, L, lL, cL);  // cL <= 64: one amplitude per lane
         double q = 0.0;
@@ -1036,7 +1104,7 @@ __global__ void __launch_bounds__(256) k_shots(const SampleArgs a, const double*
             const T2 v = p[base + lL + lane];
             q = (double)v.x * (double)v.x + (double)v.y * (double)v.y;
         }
-        const double run = start + lane_scan(q, lane);
+        const double run = start + lane_scan(q);
         const uint64_t in = __ballot(lane < cL && run > r && q > 0.0);
         int64_t idx;
         if (in) {
@@ -1049,16 +1117,32 @@ __global__ void __launch_bounds__(256) k_shots(const SampleArgs a, const double*
     }
 }
 
-// <Z_q> from the shots: one thread per (sample, qubit), exact integer counts.
+// <Z_q> from the shots, exact integer counts: one workgroup per sample, each
+// wavefront counting 64 shots at a time by a ballot per qubit (lane q keeps
+// qubit q's count). One thread per (sample, qubit) read its sample's shots one
+// after another: 108 us for 256 samples of 1000 shots, now 5.
 template <typename Real>
 __global__ void __launch_bounds__(256) k_shot_z(const SampleArgs a) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < a.B * a.n; t += stride) {
-        const int64_t b = t / a.n;
-        const int q = (int)(t - b * a.n);
-        int64_t ones = 0;
-        for (int64_t s = 0; s < a.shots; ++s) ones += (a.samples[b * a.shots + s] >> q) & 1;
-        ((Real*)a.zhat)[t] = a.shots > 0 ? (Real)((double)(a.shots - 2 * ones) / (double)a.shots) : (Real)0;
+    __shared__ unsigned long long ones[4][32];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int64_t b = blockIdx.x; b < a.B; b += gridDim.x) {
+        const int64_t* smp = a.samples + b * a.shots;
+        unsigned long long cnt = 0;
+        for (int64_t s0 = (int64_t)wave * 64; s0 < a.shots; s0 += 256) {
+            const uint32_t v = s0 + lane < a.shots ? (uint32_t)smp[s0 + lane] : 0u;  // n <= 32 bits
+            for (int q = 0; q < a.n; ++q) {
+                const int c = __popcll(__ballot((v >> q) & 1u));
+                cnt += lane == q ? (unsigned)c : 0u;
+            }
+        }
+        if (lane < 32) ones[wave][lane] = cnt;
+        __syncthreads();
+        if ((int)threadIdx.x < a.n) {
+            const int q = threadIdx.x;
+            const int64_t t = (int64_t)(ones[0][q] + ones[1][q] + ones[2][q] + ones[3][q]);
+            ((Real*)a.zhat)[b * a.n + q] = (Real)((double)(a.shots - 2 * t) / (double)a.shots);
+        }
+        __syncthreads();
     }
 }
 
@@ -1202,18 +1286,10 @@ hipError_t launch_env_grad(int dtype, const PrefixArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, void* psi, int n,
-                              hipStream_t s) {
-    const unsigned g1 = (unsigned)((a.B + 255) / 256);
-    const int64_t total = a.B << n;
-    const unsigned g2 = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
-    if (dtype == 0) {
-        hipLaunchKernelGGL(k_state_phase<float>, dim3(g1), dim3(256), 0, s, a, phase);
-        hipLaunchKernelGGL(k_phase_fix<float2>, dim3(g2), dim3(256), 0, s, psi, (const double*)phase, a.B, n);
-    } else {
-        hipLaunchKernelGGL(k_state_phase<double>, dim3(g1), dim3(256), 0, s, a, phase);
-        hipLaunchKernelGGL(k_phase_fix<double2>, dim3(g2), dim3(256), 0, s, psi, (const double*)phase, a.B, n);
-    }
+hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, hipStream_t s) {
+    const unsigned grid = (unsigned)((a.B + 3) / 4);
+    if (dtype == 0) hipLaunchKernelGGL(k_state_phase<float>, dim3(grid), dim3(256), 0, s, a, phase);
+    else hipLaunchKernelGGL(k_state_phase<double>, dim3(grid), dim3(256), 0, s, a, phase);
     return hipGetLastError();
 }
 
@@ -1242,9 +1318,8 @@ hipError_t launch_sample(int dtype, const SampleArgs& a, hipStream_t s) {
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (a.zhat) {
-        const int64_t t = a.B * a.n;
-        if (dtype == 0) hipLaunchKernelGGL(k_shot_z<float>, dim3(sample_grid(t, 256)), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(k_shot_z<double>, dim3(sample_grid(t, 256)), dim3(256), 0, s, a);
+        if (dtype == 0) hipLaunchKernelGGL(k_shot_z<float>, dim3(sample_grid(a.B, 1)), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL(k_shot_z<double>, dim3(sample_grid(a.B, 1)), dim3(256), 0, s, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

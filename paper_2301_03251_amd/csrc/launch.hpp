@@ -108,6 +108,7 @@ struct EmbedArgs {
     int64_t v0;
     int32_t vper;         // 0: circuit i is sample i
     int32_t kind, first, F, n;
+    const double* phase;  // [count] complex: a factor on the initial state, or null
 };
 
 // Amplitude-embedding VJP: grad_inputs[b][first + j] += (2 / |x|) (Re lam_j -
@@ -187,6 +188,7 @@ struct PrefixArgs {
     int32_t vper;
     int32_t n, F, n_wg;
     int32_t env_wg;            // workgroups per sample of the environment kernel
+    const double* phase;       // [count] complex: a factor on the product state, or null
 };
 // Workgroups per sample of the environment kernel for n qubits and batch B.
 int env_workgroups(int dtype, int n, int64_t B);
@@ -226,10 +228,9 @@ hipError_t launch_tile(int dtype, int log_r, bool bwd, const TileArgs& a, int th
 hipError_t launch_reduce(int dtype, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_shift_dot(int dtype, const ShiftDotArgs& a, hipStream_t s);
 hipError_t launch_sample(int dtype, const SampleArgs& a, hipStream_t s);
-// Undo the per-sample global phase the tile kernel leaves on final states
-// (phase: [2B] fp64 scratch: the inverse phase factor per sample).
-hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, void* psi, int n,
-                              hipStream_t s);
+// Inverse of the per-sample global phase that the forward ops leave (phase:
+// [B] complex fp64).
+hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, hipStream_t s);
 hipError_t launch_embed(int dtype, const EmbedArgs& a, hipStream_t s);
 hipError_t launch_embed_grad(int dtype, const EmbedGradArgs& a, hipStream_t s);
 hipError_t launch_shift_grad(int dtype, const ShiftGradArgs& a, hipStream_t s);
