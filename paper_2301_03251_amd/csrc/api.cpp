@@ -168,9 +168,7 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
     T.n_ops = (int)ops.size();
 }
 
-// The run kernel's largest circuits by default, and its LDS budget (gfx950
-// has 160 KiB per CU).
-constexpr int RUNS_DEFAULT_QUBITS = 11;
+// The run kernel's LDS budget (gfx950 has 160 KiB per CU).
 constexpr size_t RUNS_LDS_MAX = 160 * 1024;
 
 struct Layout {
@@ -179,10 +177,10 @@ struct Layout {
     size_t keep = 0;             // kept forward states: n_keep buffers of state_bytes each
     size_t phi = 0, env = 0;     // product prefix: per-circuit factors; per-tile environment sums
     size_t state_bytes = 0;
-    int n_wg_fwd = 1;            // workgroups per sample of the forward passes before the last
-    bool runs = false;           // the run kernel takes the call
     int n_keep = 0;
     int n_wg = 1;
+    int n_wg_fwd = 1;            // workgroups per sample of the forward passes before the last
+    bool runs = false;           // the run kernel takes the call
 };
 
 bool mul_ok(size_t a, size_t b, size_t& out) {
@@ -196,12 +194,12 @@ bool mul_ok(size_t a, size_t b, size_t& out) {
 struct ql_circuit {
     Circuit c;
     RunPlan rp;
-    bool runs[2] = {false, false};  // per dtype: the run kernel takes every call
-    Tables t[2];
-    // pinned host copies of the table blobs (made on the first call of each
-    // dtype), so the per-call upload is an asynchronous DMA
-    void* pinned[2] = {nullptr, nullptr};
-    std::once_flag pin_once[2];
+    bool runs[2][2] = {};  // [dtype][with a backward]: the run kernel can take the call
+    Tables t[2][2];        // [dtype][0: tile or whole-state plan, 1: run plan]
+    // pinned host copies of the table blobs (made on the first call that uses
+    // each), so the per-call upload is an asynchronous DMA
+    void* pinned[2][2] = {};
+    std::once_flag pin_once[2][2];
     // an event per stream that copied from a pinned blob, recorded after each
     // such copy: destruction waits for these copies only
     std::mutex up_mu;
@@ -218,6 +216,28 @@ struct ql_circuit {
 
 namespace {
 
+// Whether the run kernel takes a call. Below 32 KiB of state per sample (n <=
+// 10, and 11 in complex64) it is faster at every batch (1.0 to 3.4 times the
+// tile kernel; circuits of 4 layers, batches of 256 to 30000). Larger states
+// have fewer passes over the matrices' 8 FMAs per amplitude hidden behind
+// anything: with every wavefront slot taken once (256 CUs of 1024 threads) the
+// run kernel still wins, beyond that the tile kernel's 3 FMAs per rotation do.
+// Training step, tile / run kernel: 12 qubits complex64, 256 samples 150 / 104
+// us, 300 samples of a random circuit 219 / 266 us; 11 qubits complex128, 512
+// samples 183 / 173 us, 1000 samples 251 / 312 us. Forward only, four rounds
+// (32 KiB): 12 qubits complex64, 1000 samples 128 / 115 us, 2000 samples 183 /
+// 201 us; 11 qubits complex128, 2000 samples 146 / 145 us. 12 qubits complex128
+// forward: 512 samples 72 / 78 us.
+bool runs_take(const ql_circuit* h, int dt, int64_t B, int mode) {
+    const bool bwd = mode != QL_MODE_FWD;
+    const int n = h->c.n;
+    if (!h->runs[dt][bwd]) return false;
+    const int64_t state = (int64_t)(dt == 0 ? 8 : 16) << n;
+    if (state < 32768) return true;
+    const int64_t round = ((int64_t)256 * 1024) >> (n - 2);  // workgroups of 2^(n-2) threads
+    return B <= (!bwd && state == 32768 ? 4 * round : round);
+}
+
 // own_psi = false: the caller's state buffer holds psi (ql_state), so the
 // workspace has none.
 int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, bool own_psi = true) {
@@ -229,7 +249,9 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     const int maxq = dt == 0 ? QL_MAX_QUBITS_C64 : QL_MAX_QUBITS_C128;
     if (c.n > maxq) return fail(QL_EUNSUPPORTED, "too many qubits for this dtype");
     L = Layout{};
-    const bool runs = h->runs[dt], one = runs || pl.whole_state;  // one workgroup per sample, state on chip
+    const bool runs = runs_take(h, dt, B, mode), one = runs || pl.whole_state;  // one workgroup per sample, state on chip
+    const Tables& T = h->t[dt][runs];
+    L.runs = runs;
     if (one) {
         L.n_wg = 1;
     } else {
@@ -243,28 +265,6 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
         int64_t nwg = c.opts.wg_per_sample ? c.opts.wg_per_sample : (8192 + B - 1) / B;
         const int64_t cap = c.opts.wg_per_sample ? tiles : std::max<int64_t>(1, tiles / 2);
         nwg = std::max<int64_t>(1, std::min<int64_t>(nwg, cap));
-        if (nwg * B > (int64_t)INT32_MAX) return fail(QL_ENOMEM, "grid too large");
-        L.n_wg = (int)nwg;
-    }
-    const bool bwd = mode == QL_MODE_FWD_BWD || mode == QL_MODE_FWD_BWD_KEEP;
-    size_t off = 0, sz = 0;
-    L.tables = off;
-    off = align256(off + h->t[dt].blob.size());
-    L.coef = off;
-    if (!mul_ok((size_t)B * (size_t)std::max(1, (int)c.slots.size()), amp, sz)) return fail(QL_ENOMEM, "size overflow");
-    if (!runs) off = align256(off + sz);
-    if (!one) {
-        // per-sample op records (16 bytes fp32 / 32 bytes fp64) plus an end record
-        L.opc = off;
-        if (!mul_ok((size_t)B * (size_t)(h->t[dt].n_ops + 1), dt == 0 ? 16 : 32, sz))
-            return fail(QL_ENOMEM, "size overflow");
-        off = align256(off + sz);
-        // per-sample phase tables of the RZ groups
-        L.dzc = off;
-        if (!mul_ok((size_t)B * (size_t)h->t[dt].n_diags, (size_t)DZ_REGS * amp, sz))
-            return fail(QL_ENOMEM, "size overflow");
-        off = align256(off + sz);
-        // per-sample RZ coefficients of the RY-RZ pair ops
         L.n_wg_fwd = (int)nwg;
         // A backward pass carries one tile per workgroup and iteration: with
         // at most two workgroups per CU in all, each takes one tile instead of
@@ -273,8 +273,30 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
         // 64 samples of 8 tiles: 434 -> 405). With 1024 tiles it would cost
         // 5 to 12 %. The forward passes keep two tiles per workgroup.
         if (mode != QL_MODE_FWD && !c.opts.wg_per_sample && tiles <= 512 / B) nwg = tiles;
+        if (nwg * B > (int64_t)INT32_MAX) return fail(QL_ENOMEM, "grid too large");
+        L.n_wg = (int)nwg;
+    }
+    const bool bwd = mode == QL_MODE_FWD_BWD || mode == QL_MODE_FWD_BWD_KEEP;
+    size_t off = 0, sz = 0;
+    L.tables = off;
+    off = align256(off + T.blob.size());
+    L.coef = off;
+    if (!mul_ok((size_t)B * (size_t)std::max(1, (int)c.slots.size()), amp, sz)) return fail(QL_ENOMEM, "size overflow");
+    if (!runs) off = align256(off + sz);
+    if (!one) {
+        // per-sample op records (16 bytes fp32 / 32 bytes fp64) plus an end record
+        L.opc = off;
+        if (!mul_ok((size_t)B * (size_t)(T.n_ops + 1), dt == 0 ? 16 : 32, sz))
+            return fail(QL_ENOMEM, "size overflow");
+        off = align256(off + sz);
+        // per-sample phase tables of the RZ groups
+        L.dzc = off;
+        if (!mul_ok((size_t)B * (size_t)T.n_diags, (size_t)DZ_REGS * amp, sz))
+            return fail(QL_ENOMEM, "size overflow");
+        off = align256(off + sz);
+        // per-sample RZ coefficients of the RY-RZ pair ops
         L.fzc = off;
-        if (!mul_ok((size_t)B * (size_t)h->t[dt].n_fuses, amp, sz)) return fail(QL_ENOMEM, "size overflow");
+        if (!mul_ok((size_t)B * (size_t)T.n_fuses, amp, sz)) return fail(QL_ENOMEM, "size overflow");
         off = align256(off + sz);
     }
     L.zpart = off;
@@ -432,6 +454,7 @@ struct Ctx {
     const void* weights = nullptr;
     int64_t v0 = 0;
     int32_t vper = 0;
+    double* phase = nullptr;  // ql_state: factor on every circuit's initial state
 };
 
 int upload_tables(Ctx& x) {
@@ -440,19 +463,20 @@ int upload_tables(Ctx& x) {
                                       x.stream);
         return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("table upload: ") + hipGetErrorString(e));
     }
-    std::call_once(x.h->pin_once[x.dt], [&] {
+    void*& pinned = x.h->pinned[x.dt][x.runs];
+    std::call_once(x.h->pin_once[x.dt][x.runs], [&] {
         void* p = nullptr;
         if (hipHostMalloc(&p, x.T.blob.size(), hipHostMallocDefault) == hipSuccess) {
             std::memcpy(p, x.T.blob.data(), x.T.blob.size());
-            x.h->pinned[x.dt] = p;
+            pinned = p;
         } else {
             (void)hipGetLastError();  // keep the pageable copy
         }
     });
-    const void* src = x.h->pinned[x.dt] ? x.h->pinned[x.dt] : (const void*)x.T.blob.data();
+    const void* src = pinned ? pinned : (const void*)x.T.blob.data();
     hipError_t e = hipMemcpyAsync(x.W + x.L.tables, src, x.T.blob.size(), hipMemcpyHostToDevice, x.stream);
     if (e != hipSuccess) return fail(QL_EHIP, std::string("table upload: ") + hipGetErrorString(e));
-    if (!x.h->pinned[x.dt]) return QL_OK;
+    if (!pinned) return QL_OK;
     // mark the copy's completion on this stream for ql_circuit_destroy
     std::lock_guard<std::mutex> lk(x.h->up_mu);
     hipEvent_t ev = nullptr;
@@ -464,7 +488,6 @@ int upload_tables(Ctx& x) {
         x.h->uploads.push_back({x.stream, ev});
     }
     e = hipEventRecord(ev, x.stream);
-    double* phase = nullptr;  // ql_state: factor on every circuit's initial state
     return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
 }
 
@@ -485,6 +508,7 @@ PrefixArgs prefix_args(const Ctx& x, int64_t B) {
     pa.F = x.c.n_inputs;
     pa.n_wg = x.L.n_wg;
     pa.env_wg = env_workgroups(x.dt, x.c.n, B);
+    pa.phase = x.phase;
     return pa;
 }
 
@@ -518,7 +542,6 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ba.inputs = inputs;
         ba.weights = weights;
         ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
-    pa.phase = x.phase;
         ba.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
         ba.opc = x.W + x.L.opc;
         ba.diags = (const DevDiag*)(x.W + x.L.tables + x.T.off_diag);
@@ -563,6 +586,7 @@ int embed(Ctx& x, int64_t B, const void* inputs, void* psi, int64_t v0, int32_t 
     ea.first = x.c.embed_first;
     ea.F = x.c.n_inputs;
     ea.n = x.c.n;
+    ea.phase = x.phase;
     x.tm.start(2);
     hipError_t e = launch_embed(x.dt, ea, x.stream);
     x.tm.stop();
@@ -596,7 +620,6 @@ int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, voi
     a.expz = expz;
     a.psi_out = psi_out;
     a.grad_inputs = bwd && c.n_inputs > 0 ? grad_inputs : nullptr;
-    ea.phase = x.phase;
     a.grad_weights = bwd && B == 1 ? grad_weights : nullptr;
     a.gpart = bwd && B > 1 && grad_weights ? (double*)(x.W + x.L.gpart) : nullptr;
     a.B = B;
@@ -795,7 +818,7 @@ int run(const ql_circuit* hc, ql_dtype dtype, int64_t B, int mode, const void* i
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}, h->runs[dt]};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
     x.no_alloc = no_alloc;
     if (no_alloc) x.tm.h = nullptr;  // no timing events either
     if ((rc = upload_tables(x))) return rc;
@@ -884,7 +907,7 @@ int param_shift(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inp
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, S.L, stream, Timer{h, stream}, h->runs[dt]};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][S.L.runs], (uint8_t*)ws, S.L, stream, Timer{h, stream}, S.L.runs};
     if ((rc = upload_tables(x))) return rc;
     const int32_t V = (int32_t)(2 * h->c.n_param_slots + 1);
     void* ev = x.W + S.ev;
@@ -949,8 +972,10 @@ int state(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inputs, c
                                    std::to_string(ws_bytes));
     rc = ensure_device();
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt], (uint8_t*)ws, L, stream, Timer{h, stream}, h->runs[dt]};
+    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
     if ((rc = upload_tables(x))) return rc;
+    // the tile path drops global phases: the initial states start with their inverse
+    if (!x.runs && !x.pl.whole_state) x.phase = (double*)(x.W + x.L.zpart);
     if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
     if (x.runs) return run_steps(x, B, false, nullptr, nullptr, nullptr, nullptr, psi);
     if ((rc = embed(x, B, inputs, psi, 0, 0))) return rc;
@@ -968,8 +993,6 @@ int sample_blocks(int n, int& bb, int64_t& nblk) {
 int sample_bytes(int n, int64_t B, size_t& out) {
     int bb;
     int64_t nblk;
-    // the tile path drops global phases: the initial states start with their inverse
-    if (!x.runs && !x.pl.whole_state) x.phase = (double*)(x.W + x.L.zpart);
     int rc = sample_blocks(n, bb, nblk);
     if (rc) return rc;
     if (B < 1) return fail(QL_EINVAL, "batch must be >= 1");
@@ -1006,11 +1029,12 @@ void choose_runs(ql_circuit* h) {
     const Options& o = c.opts;
     const bool plain = !o.log_regs && !o.log_threads && !o.low_qubits && !o.max_gates_per_pass && !o.force_tiled &&
                        !o.wg_per_sample && !o.rz_groups && !o.pass_search && !o.product_prefix && !o.cz_groups;
-    if (c.n > RUNS_DEFAULT_QUBITS || (c.n >= 8 && !plain)) return;
+    if (c.n > RUNS_MAX_QUBITS || (c.n >= 8 && !plain)) return;
     build_run_plan(c, h->rp);
     if (!h->rp.ok) return;
     for (int dt = 0; dt < 2; dt++)
-        h->runs[dt] = runs_lds(dt, h->rp, (int)c.slots.size(), true).total <= RUNS_LDS_MAX;
+        for (int bwd = 0; bwd < 2; bwd++)
+            h->runs[dt][bwd] = runs_lds(dt, h->rp, (int)c.slots.size(), bwd != 0).total <= RUNS_LDS_MAX;
 }
 
 }  // namespace
@@ -1039,7 +1063,10 @@ int ql_circuit_create_desc(int32_t n_qubits, const ql_gate* gates, int32_t n_gat
                             to_options(opts), h->c);
         if (err.empty()) {
             choose_runs(h);
-            for (int dt = 0; dt < 2; dt++) build_tables(h->c, dt, h->runs[dt] ? &h->rp : nullptr, h->t[dt]);
+            for (int dt = 0; dt < 2; dt++) {
+                build_tables(h->c, dt, nullptr, h->t[dt][0]);
+                if (h->runs[dt][0]) build_tables(h->c, dt, &h->rp, h->t[dt][1]);
+            }
         }
     } catch (const std::bad_alloc&) {
         delete h;
@@ -1072,8 +1099,9 @@ void ql_circuit_destroy(ql_circuit* h) {
         (void)hipEventSynchronize(u.second);
         (void)hipEventDestroy(u.second);
     }
-    for (void* p : h->pinned)
-        if (p) (void)hipHostFree(p);
+    for (auto& d : h->pinned)
+        for (void* p : d)
+            if (p) (void)hipHostFree(p);
     for (auto& e : h->ev) {
         (void)hipEventDestroy(e.a);
         (void)hipEventDestroy(e.b);

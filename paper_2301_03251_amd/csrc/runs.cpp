@@ -235,10 +235,11 @@ struct Planner {
         e.count = (int)m.size();
         e.controlled = ctl >= 0;
         e.cs = p.n_cs;
-        bool rot = false;
+        bool rot = false, real = true;
         for (DevRunMember x : m) {
             x.cs = p.n_cs;
             p.n_cs += ctl >= 0 ? 2 : 1;
+            real &= x.kind == K_RY || x.kind == K_H;
             rot |= x.kind == K_RX || x.kind == K_RY || x.kind == K_RZ;
             p.members.push_back(x);
         }
@@ -256,7 +257,7 @@ struct Planner {
         } else {
             if (layer < 0 || (p.steps[layer].ctl & bit)) {
                 layer = (int)p.steps.size();
-                p.steps.push_back({RS_LAYER, (uint32_t)p.n_mat, 0, (uint32_t)p.n_grads});
+                p.steps.push_back({RS_LAYER_REAL, (uint32_t)p.n_mat, 0, (uint32_t)p.n_grads});
                 p.n_mat += 4 * p.n_pos;
                 p.n_grads += p.n_pos;
             }
@@ -266,6 +267,9 @@ struct Planner {
             e.grad = s.grad + (uint32_t)at[q];
         }
         if (!rot) e.grad = RUNS_NONE;
+        if (ctl < 0 && !real)  // a complex matrix makes its layer a complex one
+            for (DevRunStep& s : p.steps)
+                if (s.op == RS_LAYER_REAL && s.mat <= e.mat && e.mat < s.mat + 4u * (uint32_t)p.n_pos) s.op = RS_LAYER;
         touched |= qs;
         p.entries.push_back(e);
         m.clear();

@@ -78,10 +78,15 @@ __device__ __forceinline__ void swap_reg0(T2* a) {
     }
 }
 
-// a u + b v
-template <typename T2>
+// a u + b v (REAL: a and b are real)
+template <bool REAL, typename T2>
 __device__ __forceinline__ T2 mix(T2 a, T2 u, T2 b, T2 v) {
     T2 r;
+    if constexpr (REAL) {
+        r.x = fma(b.x, v.x, a.x * u.x);
+        r.y = fma(b.x, v.y, a.x * u.y);
+        return r;
+    }
     r.x = fma(-b.y, v.y, fma(b.x, v.x, fma(-a.y, u.y, a.x * u.x)));
     r.y = fma(b.y, v.x, fma(b.x, v.y, fma(a.y, u.x, a.x * u.y)));
     return r;
@@ -106,30 +111,30 @@ __device__ __forceinline__ Rows<T2> load_rows(const T2* m, int bit) {
 }
 
 // Gradient sums of one run on register bit M (pairs (i, i | 1 << M)).
-template <int R, int M, typename T2, typename Real>
+template <int R, int M, bool REAL, typename T2, typename Real>
 __device__ __forceinline__ void grads_reg(const T2* p, const T2* l, Real& sx, Real& sy, Real& sz) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         if (i >> M & 1) continue;
         const T2 p0 = p[i], p1 = p[i | 1 << M], l0 = l[i], l1 = l[i | 1 << M];
-        sx = fma(l0.x, p1.y, fma(-l0.y, p1.x, fma(l1.x, p0.y, fma(-l1.y, p0.x, sx))));
+        if constexpr (!REAL) sx = fma(l0.x, p1.y, fma(-l0.y, p1.x, fma(l1.x, p0.y, fma(-l1.y, p0.x, sx))));
         sy = fma(l1.x, p0.x, fma(l1.y, p0.y, fma(-l0.x, p1.x, fma(-l0.y, p1.y, sy))));
-        sz = fma(l0.x, p0.y, fma(-l0.y, p0.x, fma(-l1.x, p1.y, fma(l1.y, p1.x, sz))));
+        if constexpr (!REAL) sz = fma(l0.x, p0.y, fma(-l0.y, p0.x, fma(-l1.x, p1.y, fma(l1.y, p1.x, sz))));
     }
 }
 
-template <int R, int M, bool INV, typename T2>
+template <int R, int M, bool INV, bool REAL, typename T2>
 __device__ __forceinline__ void apply_reg(T2* s, const Rows<T2>& m) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         if (i >> M & 1) continue;
         const T2 u = s[i], v = s[i | 1 << M];
         if (INV) {
-            s[i] = mix(conj(m.own0), u, conj(m.oth1), v);
-            s[i | 1 << M] = mix(conj(m.oth0), v, conj(m.own1), u);
+            s[i] = mix<REAL>(conj(m.own0), u, conj(m.oth1), v);
+            s[i | 1 << M] = mix<REAL>(conj(m.oth0), v, conj(m.own1), u);
         } else {
-            s[i] = mix(m.own0, u, m.own1, v);
-            s[i | 1 << M] = mix(m.oth0, v, m.oth1, u);
+            s[i] = mix<REAL>(m.own0, u, m.own1, v);
+            s[i | 1 << M] = mix<REAL>(m.oth0, v, m.oth1, u);
         }
     }
 }
@@ -138,18 +143,20 @@ __device__ __forceinline__ void apply_reg(T2* s, const Rows<T2>& m) {
 // sums, then the inverse on psi and lambda; or the sums alone.
 enum { RUN_FWD = 0, RUN_BWD = 1, RUN_SUMS = 2 };
 
-// One run. POS: the position of its qubit.
-template <int LOG_R, int POS, int MODE, typename T2, typename Real>
+// One run. POS: the position of its qubit. REAL: its matrix is real (RY and H
+// only); un-applying RY and H never mixes the Y sum with the others, so it is
+// the only one needed.
+template <int LOG_R, int POS, int MODE, bool REAL, typename T2, typename Real>
 __device__ __forceinline__ void run_step(T2* ps, T2* lm, const Rows<T2>& m, int lane, Real& sx, Real& sy, Real& sz) {
     constexpr bool INV = MODE != RUN_FWD;
     constexpr int R = 1 << LOG_R;
     if constexpr (POS < LOG_R) {
         if constexpr (INV) {
-            grads_reg<R, POS, T2, Real>(ps, lm, sx, sy, sz);
+            grads_reg<R, POS, REAL, T2, Real>(ps, lm, sx, sy, sz);
             if constexpr (MODE == RUN_SUMS) return;
-            apply_reg<R, POS, true>(lm, m);
+            apply_reg<R, POS, true, REAL>(lm, m);
         }
-        apply_reg<R, POS, INV>(ps, m);
+        apply_reg<R, POS, INV, REAL>(ps, m);
     } else {
         constexpr int B = POS - LOG_R;
         if constexpr (INV) {
@@ -159,9 +166,9 @@ __device__ __forceinline__ void run_step(T2* ps, T2* lm, const Rows<T2>& m, int 
             Real ty = 0, tz = 0;
 #pragma unroll
             for (int i = 0; i < R; ++i) {
-                sx = fma(lm[i].x, pp[i].y, fma(-lm[i].y, pp[i].x, sx));
+                if constexpr (!REAL) sx = fma(lm[i].x, pp[i].y, fma(-lm[i].y, pp[i].x, sx));
                 ty = fma(lm[i].x, pp[i].x, fma(lm[i].y, pp[i].y, ty));
-                tz = fma(lm[i].x, ps[i].y, fma(-lm[i].y, ps[i].x, tz));
+                if constexpr (!REAL) tz = fma(lm[i].x, ps[i].y, fma(-lm[i].y, ps[i].x, tz));
             }
             const bool one = (runs_lane(lane) >> B) & 1;
             sy = one ? ty : -ty;
@@ -170,14 +177,14 @@ __device__ __forceinline__ void run_step(T2* ps, T2* lm, const Rows<T2>& m, int 
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const T2 lp = mk<T2>(partner<B>(lm[i].x, lane), partner<B>(lm[i].y, lane));
-                lm[i] = mix(conj(m.own0), lm[i], conj(m.oth1), lp);
-                ps[i] = mix(conj(m.own0), ps[i], conj(m.oth1), pp[i]);
+                lm[i] = mix<REAL>(conj(m.own0), lm[i], conj(m.oth1), lp);
+                ps[i] = mix<REAL>(conj(m.own0), ps[i], conj(m.oth1), pp[i]);
             }
         } else {
 #pragma unroll
             for (int i = 0; i < R; ++i) {
                 const T2 pp = mk<T2>(partner<B>(ps[i].x, lane), partner<B>(ps[i].y, lane));
-                ps[i] = mix(m.own0, ps[i], m.own1, pp);
+                ps[i] = mix<REAL>(m.own0, ps[i], m.own1, pp);
             }
         }
     }
@@ -186,17 +193,17 @@ __device__ __forceinline__ void run_step(T2* ps, T2* lm, const Rows<T2>& m, int 
 // Lane bits 4 and 5 with more than one register: the run is made on register
 // bit 0 between two permlane swaps (4 instructions per amplitude pair against
 // 12 for fetching both partners).
-template <int LOG_R, int POS, int MODE, typename T2, typename Real>
+template <int LOG_R, int POS, int MODE, bool REAL, typename T2, typename Real>
 __device__ __forceinline__ void run_any(T2* ps, T2* lm, const Rows<T2>& m, int lane, Real& sx, Real& sy, Real& sz) {
     constexpr int R = 1 << LOG_R, B = POS - LOG_R;
     if constexpr (LOG_R > 0 && (B == 4 || B == 5)) {
         swap_reg0<R, B>(ps);
         if constexpr (MODE != RUN_FWD) swap_reg0<R, B>(lm);
-        run_step<LOG_R, 0, MODE, T2, Real>(ps, lm, m, lane, sx, sy, sz);
+        run_step<LOG_R, 0, MODE, REAL, T2, Real>(ps, lm, m, lane, sx, sy, sz);
         swap_reg0<R, B>(ps);
         if constexpr (MODE != RUN_FWD) swap_reg0<R, B>(lm);
     } else {
-        run_step<LOG_R, POS, MODE, T2, Real>(ps, lm, m, lane, sx, sy, sz);
+        run_step<LOG_R, POS, MODE, REAL, T2, Real>(ps, lm, m, lane, sx, sy, sz);
     }
 }
 
@@ -210,11 +217,13 @@ __device__ __forceinline__ int row_bit(int pos, int sid) {
 }
 
 // The wavefront's gradient sums of one run into its words of the table.
-template <typename Real>
+template <bool REAL, typename Real>
 __device__ __forceinline__ void store_sums(Real* o, Real sx, Real sy, Real sz, int lane) {
-    sx = wave_to_last(sx);
     sy = wave_to_last(sy);
-    sz = wave_to_last(sz);
+    if constexpr (!REAL) {
+        sx = wave_to_last(sx);
+        sz = wave_to_last(sz);
+    }
     if (lane == 63) {
         o[0] = sx;
         o[1] = sy;
@@ -226,7 +235,7 @@ __device__ __forceinline__ void store_sums(Real* o, Real sx, Real sy, Real sz, i
 // distinct qubits, so any order is right). `base`: position 0's matrix, `o`:
 // this wavefront's sums of position 0, `stride` to the next position's. The
 // rows of the next position are fetched during a run.
-template <int LOG_R, int MODE, int POS, typename T2, typename Real>
+template <int LOG_R, int MODE, int POS, bool REAL, typename T2, typename Real>
 __device__ __forceinline__ void layer(T2* ps, T2* lm, const T2* base, uint32_t mask, const Rows<T2>& cur, Real* o,
                                       int stride, int sid, int lane) {
     if constexpr (POS < LOG_R + 6) {
@@ -235,10 +244,10 @@ __device__ __forceinline__ void layer(T2* ps, T2* lm, const T2* base, uint32_t m
             nxt = load_rows(base + 4 * (POS + 1), row_bit<LOG_R>(POS + 1, sid));
         if (mask >> POS & 1u) {
             Real sx = 0, sy = 0, sz = 0;
-            run_any<LOG_R, POS, MODE, T2, Real>(ps, lm, cur, lane, sx, sy, sz);
-            if constexpr (MODE != RUN_FWD) store_sums(o + POS * stride, sx, sy, sz, lane);
+            run_any<LOG_R, POS, MODE, REAL, T2, Real>(ps, lm, cur, lane, sx, sy, sz);
+            if constexpr (MODE != RUN_FWD) store_sums<REAL>(o + POS * stride, sx, sy, sz, lane);
         }
-        layer<LOG_R, MODE, POS + 1, T2, Real>(ps, lm, base, mask, nxt, o, stride, sid, lane);
+        layer<LOG_R, MODE, POS + 1, REAL, T2, Real>(ps, lm, base, mask, nxt, o, stride, sid, lane);
     }
 }
 
@@ -460,11 +469,11 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         if constexpr (P < LOG_R + 6) {                                                            \
             const T2* m = mat + cur.mat + (((sid >> (cur.y & 31u)) & 1) << 2);                    \
             Real sx = 0, sy = 0, sz = 0;                                                          \
-            run_any<LOG_R, P, MODE, T2, Real>(ps, lm, load_rows(m, row_bit<LOG_R>(P, sid)), lane, \
+            run_any<LOG_R, P, MODE, false, T2, Real>(ps, lm, load_rows(m, row_bit<LOG_R>(P, sid)), lane, \
                                               sx, sy, sz);                                        \
             if constexpr (MODE != RUN_FWD) {                                                      \
                 if (!((sid >> (cur.y & 31u)) & 1)) sx = sy = sz = 0; /* the control's 1 half */   \
-                store_sums(my_sums + (cur.y >> 8) * sum_stride, sx, sy, sz, lane);                \
+                store_sums<false>(my_sums + (cur.y >> 8) * sum_stride, sx, sy, sz, lane);                \
             }                                                                                     \
         }                                                                                         \
         break;
@@ -478,11 +487,17 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
             const Step cur = step_of(s);
             switch (cur.op) {
                 QL_CRUN_CASES(RUN_FWD)
+                case RS_LAYER_REAL: {
+                    const T2* base = mat + cur.mat;
+                    layer<LOG_R, RUN_FWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                                                             load_rows(base, row_bit<LOG_R>(0, sid)), (Real*)nullptr, 0,
+                                                             sid, lane);
+                } break;
                 case RS_LAYER: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_FWD, 0, T2, Real>(ps, lm, base, cur.y & 0xffu,
-                                                       load_rows(base, row_bit<LOG_R>(0, sid)), (Real*)nullptr, 0, sid,
-                                                       lane);
+                    layer<LOG_R, RUN_FWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                                                              load_rows(base, row_bit<LOG_R>(0, sid)), (Real*)nullptr, 0,
+                                                              sid, lane);
                 } break;
                 case RS_SIGN:
                     flip_signs<R>(ps, signs_of(cur.mat));
@@ -576,11 +591,17 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
             const Step cur = step_of(s);
             switch (cur.op) {
                 QL_CRUN_CASES(RUN_BWD)
+                case RS_LAYER_REAL: {
+                    const T2* base = mat + cur.mat;
+                    layer<LOG_R, RUN_BWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                                                             load_rows(base, row_bit<LOG_R>(0, sid)),
+                                                             my_sums + (cur.y >> 8) * sum_stride, sum_stride, sid, lane);
+                } break;
                 case RS_LAYER: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_BWD, 0, T2, Real>(ps, lm, base, cur.y & 0xffu,
-                                                       load_rows(base, row_bit<LOG_R>(0, sid)),
-                                                       my_sums + (cur.y >> 8) * sum_stride, sum_stride, sid, lane);
+                    layer<LOG_R, RUN_BWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                                                              load_rows(base, row_bit<LOG_R>(0, sid)),
+                                                              my_sums + (cur.y >> 8) * sum_stride, sum_stride, sid, lane);
                 } break;
                 case RS_SIGN: {
                     const uint32_t m = signs_of(cur.mat);
@@ -620,7 +641,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         }
         c1 = c0;
     }
-    layer<LOG_R, RUN_SUMS, 0, T2, Real>(ps, lm, mat, a.prefix, Rows<T2>{}, my_sums, sum_stride, sid, lane);
+    layer<LOG_R, RUN_SUMS, 0, false, T2, Real>(ps, lm, mat, a.prefix, Rows<T2>{}, my_sums, sum_stride, sid, lane);
 #undef QL_CRUN_CASE
 #undef QL_CRUN_CASES
     __syncthreads();

@@ -30,6 +30,7 @@ namespace qlayer {
 
 enum RunOp : uint32_t {
     RS_CRUN = 0,      // + position of the target's bit: a controlled run
+    RS_LAYER_REAL = 14,  // the same with real matrices only (RY and H): half the arithmetic
     RS_LAYER = 15,    // runs on several positions
     RS_EXCHANGE = 16, // through LDS (signs first)
     RS_SIGN = 17,     // signs only

@@ -143,6 +143,8 @@ int check(int n_case, const Circuit& c, const RunPlan& p, long& exchanges, long&
                 if (!(t >> pos & 1)) {
                     const uint32_t e = at + (ctl >= 0 ? ((uint32_t)(t >> p.log_r) >> ctl & 1u) * 4 : 0u);
                     C m00 = mat.at(e), m01 = mat.at(e + 1), m11 = mat.at(e + 2), m10 = mat.at(e + 3);
+                    if (s.op == RS_LAYER_REAL)  // the kernel reads the real parts only
+                        for (C* m : {&m00, &m01, &m11, &m10}) *m = m->real();
                     if (back) {
                         m00 = std::conj(m00);
                         m11 = std::conj(m11);
@@ -156,7 +158,7 @@ int check(int n_case, const Circuit& c, const RunPlan& p, long& exchanges, long&
                 }
             runs++;
         };
-        if (s.op == RS_LAYER) {
+        if (s.op == RS_LAYER || s.op == RS_LAYER_REAL) {
             for (int pos = 0; pos < p.n_pos; pos++)
                 if (s.ctl >> pos & 1) apply(pos, s.mat + 4 * pos, -1);
         } else {
@@ -167,8 +169,8 @@ int check(int n_case, const Circuit& c, const RunPlan& p, long& exchanges, long&
     const int S = (int)p.steps.size() - 1;
     for (int i = 0; i < S; i++) {
         const DevRunStep& s = p.steps[i];
-        if (s.op < RS_LAYER && ((int)s.op >= p.n_pos || (int)s.ctl >= p.log_t)) return fail(n_case, "controlled run's positions");
-        if (s.op == RS_LAYER && s.ctl >> p.n_pos) return fail(n_case, "run on a wavefront bit");
+        if (s.op < RS_LAYER_REAL && ((int)s.op >= p.n_pos || (int)s.ctl >= p.log_t)) return fail(n_case, "controlled run's positions");
+        if ((s.op == RS_LAYER || s.op == RS_LAYER_REAL) && s.ctl >> p.n_pos) return fail(n_case, "run on a wavefront bit");
         step(s, false);
     }
     for (int t = 0; t < N; t++)

@@ -38,7 +38,7 @@ def test_run_plans_on_the_host(tmp_path):
         for n in range(1, 13):
             for seed in range(6):
                 kinds = [ALL, (W.RX, W.RY, W.RZ, W.CNOT), (W.H, W.RZ, W.CZ, W.RY), (W.CRX, W.CRY, W.CRZ, W.RZ, W.RX),
-                         (W.CNOT, W.CZ, W.RZ, W.RX), (W.CNOT, W.CRY, W.H)][seed]
+                         (W.CNOT, W.CZ, W.RZ, W.RX), (W.CNOT, W.CRY, W.H, W.RY)][seed]
                 _record(f, n, W.random_circuit(n, 12 * n + 10, 4, 6, seed=100 * n + seed, kinds=kinds), 4, 6,
                         embed=(W.EMBED_AMPLITUDE, 0) if seed == 9 else (0, 0))
             layered = W.layered_circuit(n, "h_rz" if n % 2 else "ry", 3, (W.RY, W.RZ), W.CZ if n % 2 else W.CNOT,
