@@ -42,6 +42,8 @@ struct Tables {
     size_t off_pass = 0, off_phase = 0, off_ops = 0, off_gslot = 0, off_slots = 0;
     size_t off_xptr = 0, off_xslot = 0, off_wptr = 0, off_wslot = 0, off_gates = 0, off_diag = 0;
     size_t off_fuse = 0, off_czg = 0, off_pthr = 0;
+    size_t off_rrun = 0, off_rmemb = 0;  // rotation runs of the tile plan and their members
+    int n_runs = 0, n_rmemb = 0;
     size_t off_pptr = 0, off_pops = 0;  // product-prefix CSR (per qubit)
     size_t off_rstep = 0, off_rent = 0, off_rmem = 0, off_rword = 0;  // run plan
     std::vector<DevPass> passes;
@@ -64,7 +66,7 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
     const Plan& pl = c.plan[dt];
     std::vector<DevPass> passes;
     std::vector<DevOp> ops;
-    std::vector<int32_t> gsl;
+    std::vector<DevGradOut> gouts;
     if (!pl.whole_state && !rp) {
         for (const PassPlan& pp : pl.passes) {
             DevPass d{};
@@ -82,9 +84,10 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
             d.fwd_end = (int)ops.size();
             d.load_phase = pp.first_phase;
             d.bwd_phase = pp.last_phase;
-            d.gslot_base = (int)gsl.size();
-            gsl.insert(gsl.end(), pp.gslots.begin(), pp.gslots.end());
-            d.n_gslots = (int)pp.gslots.size();
+            d.gout_base = (int)gouts.size();
+            gouts.insert(gouts.end(), pp.gouts.begin(), pp.gouts.end());
+            d.n_gouts = (int)pp.gouts.size();
+            d.n_gslots = pp.n_acc;
             d.n_exchanges = pp.n_transposes;
             d.index = (int)passes.size();
             passes.push_back(d);
@@ -133,7 +136,11 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
     T.off_pass = put(T.blob, passes);
     T.off_phase = put(T.blob, pl.phases);
     T.off_ops = put(T.blob, ops);
-    T.off_gslot = put(T.blob, gsl);
+    T.off_gslot = put(T.blob, gouts);
+    T.off_rrun = put(T.blob, pl.runs);
+    T.off_rmemb = put(T.blob, pl.run_members);
+    T.n_runs = (int)pl.runs.size();
+    T.n_rmemb = (int)pl.run_members.size();
     T.off_gates = put(T.blob, gates);
     T.off_diag = put(T.blob, pl.diags);
     T.n_diags = (int)pl.diags.size();
@@ -172,7 +179,7 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
 constexpr size_t RUNS_LDS_MAX = 160 * 1024;
 
 struct Layout {
-    size_t tables = 0, coef = 0, opc = 0, dzc = 0, fzc = 0, zpart = 0, gpart = 0, psi = 0, lam = 0, total = 0;
+    size_t tables = 0, coef = 0, opc = 0, dzc = 0, fzc = 0, euler = 0, axes = 0, zpart = 0, gpart = 0, psi = 0, lam = 0, total = 0;
     size_t enorm = 0, edot = 0;  // embedding: per-circuit |x| or basis index; L_b
     size_t keep = 0;             // kept forward states: n_keep buffers of state_bytes each
     size_t phi = 0, env = 0;     // product prefix: per-circuit factors; per-tile environment sums
@@ -298,6 +305,15 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
         L.fzc = off;
         if (!mul_ok((size_t)B * (size_t)T.n_fuses, amp, sz)) return fail(QL_ENOMEM, "size overflow");
         off = align256(off + sz);
+        // per-sample angles of the rotation runs, and (backward) their members' axes
+        L.euler = off;
+        if (!mul_ok((size_t)B * (size_t)T.n_runs, 32, sz)) return fail(QL_ENOMEM, "size overflow");
+        off = align256(off + sz);
+        if (mode != QL_MODE_FWD) {
+            L.axes = off;
+            if (!mul_ok((size_t)B * (size_t)T.n_rmemb, 24, sz)) return fail(QL_ENOMEM, "size overflow");
+            off = align256(off + sz);
+        }
     }
     L.zpart = off;
     if (!mul_ok((size_t)B * (size_t)L.n_wg, (size_t)c.n * 8, sz)) return fail(QL_ENOMEM, "size overflow");
@@ -538,10 +554,26 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         e = launch_bind(x.dt, ba, x.stream);
         x.tm.stop();
     } else {
+        BindRunsArgs ra{};
+        ra.inputs = inputs;
+        ra.weights = weights;
+        ra.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+        ra.runs = (const DevRotRun*)(x.W + x.L.tables + x.T.off_rrun);
+        ra.members = (const DevRotMember*)(x.W + x.L.tables + x.T.off_rmemb);
+        ra.euler = (double*)(x.W + x.L.euler);
+        ra.axes = x.L.axes ? (double*)(x.W + x.L.axes) : nullptr;
+        ra.B = B;
+        ra.v0 = v0;
+        ra.n_runs = x.T.n_runs;
+        ra.n_members = x.T.n_rmemb;
+        ra.F = x.c.n_inputs;
+        ra.vper = vper;
         BindTileArgs ba{};
         ba.inputs = inputs;
         ba.weights = weights;
         ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+        ba.euler = ra.euler;
+        ba.n_runs = ra.n_runs;
         ba.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
         ba.opc = x.W + x.L.opc;
         ba.diags = (const DevDiag*)(x.W + x.L.tables + x.T.off_diag);
@@ -557,7 +589,8 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ba.v0 = v0;
         ba.vper = vper;
         x.tm.start(2);
-        e = launch_bind_tile(x.dt, ba, x.stream);
+        e = launch_bind_runs(x.dt, ra, x.stream);
+        if (e == hipSuccess) e = launch_bind_tile(x.dt, ba, x.stream);
         if (e == hipSuccess && x.phase) e = launch_state_phase(x.dt, ba, x.phase, x.stream);
         if (e == hipSuccess && (x.pl.product || (x.phase && x.c.embed == E_NONE))) {
             PrefixArgs pa = prefix_args(x, B);
@@ -698,7 +731,10 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         ta.pass = (const DevPass*)(x.W + x.L.tables + x.T.off_pass) + p;
         ta.phases = (const DevPhase*)(x.W + x.L.tables + x.T.off_phase);
         ta.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
-        ta.gslots = (const int32_t*)(x.W + x.L.tables + x.T.off_gslot) + d.gslot_base;
+        ta.gouts = (const DevGradOut*)(x.W + x.L.tables + x.T.off_gslot) + d.gout_base;
+        ta.n_gouts = d.n_gouts;
+        ta.axes = x.L.axes ? (const double*)(x.W + x.L.axes) : nullptr;
+        ta.n_members = x.T.n_rmemb;
         ta.opc = x.W + x.L.opc;
         ta.dzc = x.W + x.L.dzc;
         ta.n_diags = x.T.n_diags;

@@ -260,6 +260,62 @@ __device__ __forceinline__ double row_sum(double v) {
     return v;
 }
 
+// ---------------------------------------------------------------------------
+// products of one-qubit gates in fp64
+
+struct Z2 {  // 2x2 complex fp64
+    double2 a, b, c, d;
+};
+// gate * m for the gate of a member (cs: cos, sin of half its angle; a Pauli's index)
+__device__ __forceinline__ void left_row(int kind, double2 cs, double2 u, double2 v, double2& o0, double2& o1) {
+    switch (kind) {
+        case K_H: {
+            const double r = 0.70710678118654752440;
+            o0 = make_double2(r * (u.x + v.x), r * (u.y + v.y));
+            o1 = make_double2(r * (u.x - v.x), r * (u.y - v.y));
+        } break;
+        case K_RX:  // [[c, -i s], [-i s, c]]
+            o0 = make_double2(cs.x * u.x + cs.y * v.y, cs.x * u.y - cs.y * v.x);
+            o1 = make_double2(cs.x * v.x + cs.y * u.y, cs.x * v.y - cs.y * u.x);
+            break;
+        case K_RY:
+            o0 = make_double2(cs.x * u.x - cs.y * v.x, cs.x * u.y - cs.y * v.y);
+            o1 = make_double2(cs.y * u.x + cs.x * v.x, cs.y * u.y + cs.x * v.y);
+            break;
+        case K_RZ:
+            o0 = cxmul(u, make_double2(cs.x, -cs.y));
+            o1 = cxmul(v, make_double2(cs.x, cs.y));
+            break;
+        default: {
+            const int w = (int)cs.x;
+            o0 = w == 1 ? v : w == 2 ? make_double2(v.y, -v.x) : u;
+            o1 = w == 1 ? u : w == 2 ? make_double2(-u.y, u.x) : w == 3 ? make_double2(-v.x, -v.y) : v;
+        }
+    }
+}
+__device__ __forceinline__ Z2 left_mul(int kind, double2 cs, const Z2& m) {
+    Z2 r;
+    left_row(kind, cs, m.a, m.c, r.a, r.c);
+    left_row(kind, cs, m.b, m.d, r.b, r.d);
+    return r;
+}
+__device__ __forceinline__ Z2 zident() {
+    const double2 o = make_double2(1.0, 0.0), z = make_double2(0.0, 0.0);
+    return {o, z, z, o};
+}
+
+// The sums S = Im <lambda| (X, Y, Z) |psi> before a rotation by (cos, sin) of
+// its whole angle, from those after it: the next two axes in cyclic order mix,
+// (u, v) -> (c u + s v, c v - s u).
+__device__ __forceinline__ void sums_before(int kind, double c, double sn, double* S) {
+    const double u = kind == K_RX ? S[1] : kind == K_RY ? S[2] : S[0];
+    const double v = kind == K_RX ? S[2] : kind == K_RY ? S[0] : S[1];
+    const double u2 = c * u + sn * v, v2 = c * v - sn * u;
+    S[0] = kind == K_RX ? S[0] : kind == K_RY ? v2 : u2;
+    S[1] = kind == K_RX ? u2 : kind == K_RY ? S[1] : v2;
+    S[2] = kind == K_RX ? v2 : kind == K_RY ? u2 : S[2];
+}
+
 
 }  // namespace
 }  // namespace qlayer

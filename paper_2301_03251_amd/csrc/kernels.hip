@@ -257,6 +257,71 @@ __global__ void __launch_bounds__(256) k_whole(const WholeArgs a) {
 // (sample, op)); shear coefficients in fp64, rounded once. The inverse of a
 // rotation (backward ops) negates both coefficients.
 
+// The angle (fp64) of a tile op's slot for circuit b, with the parameter-shift
+// offset: a rotation slot's, or one of a rotation run's three.
+template <typename Real>
+__device__ __forceinline__ double op_angle(const BindTileArgs& a, int32_t slot, int64_t b) {
+    if (slot >= RUN_SLOT) {
+        const int i = slot - RUN_SLOT;
+        return a.euler[((size_t)b * a.n_runs + (i >> 2)) * 4 + (i & 3)];
+    }
+    int64_t bs;
+    return angle_of<Real>(a.inputs, a.weights, a.F, a.slots[slot], b, a.v0, a.vper, bs) + shift_of(b, a.v0, a.vper, slot);
+}
+
+// One thread per (circuit, rotation run): the product U of the run's rotations
+// as RZ(gamma) RY(beta) RZ(alpha) (U is in SU(2): u11 = cos(beta/2)
+// exp(i (gamma + alpha)/2), u10 = sin(beta/2) exp(i (gamma - alpha)/2)), and
+// the members' axes for the sums between the RY and the last RZ.
+template <typename Real>
+__global__ void __launch_bounds__(256) k_bind_runs(const BindRunsArgs a) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= a.B * a.n_runs) return;
+    const int64_t b = t / a.n_runs;
+    const DevRotRun run = a.runs[t - b * a.n_runs];
+    Z2 m = zident();
+    auto half = [&](const DevRotMember& g) {  // (cos, sin) of half the member's angle
+        int64_t bs;
+        const double th = angle_of<Real>(a.inputs, a.weights, a.F, a.slots[g.slot], b, a.v0, a.vper, bs) +
+                          shift_of(b, a.v0, a.vper, g.slot);
+        double2 r;
+        sincos(0.5 * th, &r.y, &r.x);
+        return r;
+    };
+    for (int k = 0; k < run.count; ++k) {
+        const DevRotMember g = a.members[run.first + k];
+        m = left_mul(g.kind, half(g), m);
+    }
+    const double p = atan2(m.d.y, m.d.x), q = atan2(m.c.y, m.c.x);
+    const double gamma = p + q;
+    double* e = a.euler + t * 4;
+    e[0] = p - q;
+    e[1] = 2.0 * atan2(hypot(m.c.x, m.c.y), hypot(m.d.x, m.d.y));
+    e[2] = gamma;
+    if (!a.axes) return;
+    // rows of the map from the sums after the run to those before each gate
+    double sg, cg;
+    sincos(gamma, &sg, &cg);
+    double X[3] = {1.0, 0.0, 0.0}, Y[3] = {0.0, 1.0, 0.0}, Z[3] = {0.0, 0.0, 1.0};
+    for (int k = run.count - 1; k >= 0; --k) {
+        const DevRotMember g = a.members[run.first + k];
+        // X, Y, Z: the images of the three unit sums, so row i is (X[i], Y[i], Z[i])
+        const int i = g.kind - K_RX;
+        const double nx = i == 0 ? X[0] : i == 1 ? X[1] : X[2], ny = i == 0 ? Y[0] : i == 1 ? Y[1] : Y[2],
+                     nz = i == 0 ? Z[0] : i == 1 ? Z[1] : Z[2];
+        // the sums after the last RZ from those before it: S_X = c s_X - s s_Y, S_Y = c s_Y + s s_X
+        double* n3 = a.axes + ((size_t)b * a.n_members + run.first + k) * 3;
+        n3[0] = nx * cg + ny * sg;
+        n3[1] = ny * cg - nx * sg;
+        n3[2] = nz;
+        const double2 h = half(g);
+        const double c = h.x * h.x - h.y * h.y, sn = 2.0 * h.x * h.y;
+        sums_before(g.kind, c, sn, X);
+        sums_before(g.kind, c, sn, Y);
+        sums_before(g.kind, c, sn, Z);
+    }
+}
+
 template <typename Real>
 __global__ void k_bind_tile(const BindTileArgs a) {
     using T2 = typename Cx<Real>::T;
@@ -291,10 +356,7 @@ __global__ void k_bind_tile(const BindTileArgs a) {
             double th[MAX_DZ_BITS];
             for (int j = 0; j < MAX_DZ_BITS; ++j) {
                 th[j] = 0.0;
-                if (d.slot[j] < 0) continue;
-                int64_t bs;
-                th[j] = angle_of<Real>(a.inputs, a.weights, a.F, a.slots[d.slot[j]], b, a.v0, a.vper, bs) +
-                        shift_of(b, a.v0, a.vper, d.slot[j]);
+                if (d.slot[j] >= 0) th[j] = op_angle<Real>(a, d.slot[j], b);
             }
             T2* tab = (T2*)a.dzc + ((size_t)b * a.n_diags + op.arg) * DZ_REGS;
             for (int i = 0; i < DZ_REGS; ++i) {
@@ -311,10 +373,7 @@ __global__ void k_bind_tile(const BindTileArgs a) {
         const int which = pauli_of<Real>(a.inputs, a.F, a.slots[op.slot], b, a.v0, a.vper);
         e.h = which == 0 ? (uint32_t)H_NOP : op.h + 5u * (uint32_t)(which - 1);
     } else if (op.slot >= 0) {
-        const SlotSrc src = a.slots[op.slot];
-        int64_t bs;
-        double th = angle_of<Real>(a.inputs, a.weights, a.F, src, b, a.v0, a.vper, bs) +
-                    shift_of(b, a.v0, a.vper, op.slot);
+        double th = op_angle<Real>(a, op.slot, b);
         const double two_pi = 6.283185307179586476925;
         th -= two_pi * rint(th / two_pi);  // [-pi, pi]; the dropped sign is common to psi and lambda
         if (o >= a.bwd_first) th = -th;     // backward ops apply the inverse
@@ -338,9 +397,7 @@ __global__ void k_bind_tile(const BindTileArgs a) {
             // forward angle in both records (the backward form inverts it);
             // the forward record writes the sample's coefficients
             const uint32_t fi = op.arg >> 16;
-            int64_t bz;
-            double tz = angle_of<Real>(a.inputs, a.weights, a.F, a.slots[a.fuses[fi].slot], b, a.v0, a.vper, bz) +
-                        shift_of(b, a.v0, a.vper, a.fuses[fi].slot);
+            double tz = op_angle<Real>(a, a.fuses[fi].slot, b);
             tz -= two_pi * rint(tz / two_pi);
             const double half_pi = 1.570796326794896619231;
             double phi = tz;
@@ -779,23 +836,21 @@ __global__ void __launch_bounds__(256) k_state_phase(const BindTileArgs a, doubl
     if (b >= a.B) return;
     const double pi = 3.141592653589793238463, two_pi = 2.0 * pi;
     double ph = 0.0;
-    int64_t bs;
     for (int o = lane; o < a.bwd_first; o += 64) {
         const DevOp op = a.ops[o];
         if (op.h == H_DZ) {  // an RZ group drops exp(-i theta / 2) per member, unreduced
             const DevDiag d = a.diags[op.arg];
             for (int j = 0; j < MAX_DZ_BITS; ++j)
-                if (d.slot[j] >= 0)
-                    ph += 0.5 * angle_of<Real>(a.inputs, a.weights, a.F, a.slots[d.slot[j]], b, 0, 0, bs);
+                if (d.slot[j] >= 0) ph += 0.5 * op_angle<Real>(a, d.slot[j], b);
             continue;
         }
         if (op.slot < 0 || op.kind == K_PAULI) continue;  // Paulis are applied exactly
-        const double th = angle_of<Real>(a.inputs, a.weights, a.F, a.slots[op.slot], b, 0, 0, bs);
+        const double th = op_angle<Real>(a, op.slot, b);
         const double k = rint(th / two_pi);
         ph += pi * k;
         if (op.h >= H_G1 + 15 && op.h < H_G1 + 20) ph += 0.5 * (th - two_pi * k);
         if (op.h >= H_RYZ && op.h < H_RYZ + 5)  // the pair's RZ, as a single RZ on a register bit
-            ph += 0.5 * angle_of<Real>(a.inputs, a.weights, a.F, a.slots[a.fuses[op.arg >> 16].slot], b, 0, 0, bs);
+            ph += 0.5 * op_angle<Real>(a, a.fuses[op.arg >> 16].slot, b);
     }
     ph = wave_sum(ph);
     if (lane != 0) return;
@@ -1174,6 +1229,15 @@ hipError_t launch_bind_tile(int dtype, const BindTileArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+
+hipError_t launch_bind_runs(int dtype, const BindRunsArgs& a, hipStream_t s) {
+    const int64_t total = a.B * a.n_runs;
+    if (total == 0) return hipSuccess;
+    const unsigned grid = (unsigned)((total + 255) / 256);
+    if (dtype == 0) hipLaunchKernelGGL(k_bind_runs<float>, dim3(grid), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_bind_runs<double>, dim3(grid), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
 
 hipError_t launch_reduce(int dtype, const ReduceArgs& a, hipStream_t s) {
     const int64_t nz = a.expz ? a.B * a.n : 0;

@@ -46,6 +46,8 @@ struct BindTileArgs {
     const DevDiag* diags;  // [n_diags] RZ groups
     void* dzc;             // [B][n_diags][DZ_REGS] complex: (cos, sin) of each register's phase
     int32_t n_diags;
+    const double* euler;   // [B][n_runs][4] angles (alpha, beta, gamma) of the rotation runs
+    int32_t n_runs;
     const DevFuse* fuses;  // [n_fuses] RZs of RY-RZ pair ops
     void* fzc;             // [B][n_fuses] (a, b) shear coefficients of each pair's RZ (forward)
     int32_t n_fuses;
@@ -53,6 +55,22 @@ struct BindTileArgs {
     int32_t n_ops, bwd_first, F;
     int64_t v0;            // parameter-shift chunks: first virtual circuit
     int32_t vper;          // circuits per sample (2 * n_slots + 1), 0 = plain batch
+};
+
+// Rotation runs: per circuit the angles of RZ(gamma) RY(beta) RZ(alpha) equal
+// to the product of the run's rotations and, with axes, every member's axis n
+// (its gradient is n . (S_X, S_Y, S_Z), the sums taken between RY and the last
+// RZ).
+struct BindRunsArgs {
+    const void* inputs;
+    const void* weights;
+    const SlotSrc* slots;
+    const DevRotRun* runs;         // [n_runs]
+    const DevRotMember* members;   // [n_members]
+    double* euler;                 // [B][n_runs][4]
+    double* axes;                  // [B][n_members][3] or null
+    int64_t B, v0;
+    int32_t n_runs, n_members, F, vper;
 };
 
 // Parameter shift: per shifted circuit v of a chunk, d[v] = sum_i grad_out[b][i]
@@ -146,7 +164,9 @@ struct TileArgs {
     const DevPass* pass;
     const DevPhase* phases;
     const DevOp* ops;
-    const int32_t* gslots;     // pass-local gradient index -> rotation slot
+    const DevGradOut* gouts;   // [n_gouts] the pass's rotations
+    const double* axes;        // [B][n_members][3]: axes of the rotation runs' members
+    int32_t n_gouts, n_members;
     const void* opc;           // [B][n_ops + 1] per-sample op records
     const void* dzc;           // [B][n_diags][DZ_REGS] RZ-group phase tables
     int32_t n_diags;
@@ -234,6 +254,7 @@ hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, h
 hipError_t launch_embed(int dtype, const EmbedArgs& a, hipStream_t s);
 hipError_t launch_embed_grad(int dtype, const EmbedGradArgs& a, hipStream_t s);
 hipError_t launch_shift_grad(int dtype, const ShiftGradArgs& a, hipStream_t s);
+hipError_t launch_bind_runs(int dtype, const BindRunsArgs& a, hipStream_t s);
 hipError_t launch_bind_prefix(int dtype, const PrefixArgs& a, hipStream_t s);
 hipError_t launch_env(int dtype, const PrefixArgs& a, hipStream_t s);
 hipError_t launch_env_grad(int dtype, const PrefixArgs& a, hipStream_t s);

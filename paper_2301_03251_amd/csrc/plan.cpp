@@ -34,13 +34,15 @@ int n_qubits_of(const Gate& g) { return (g.kind == K_CNOT || g.kind == K_CZ) ? 2
 // Returns the executed gate indices in order. A skipped gate blocks its
 // qubits, so every executed gate only commutes past skipped gates acting on
 // other qubits.
-std::vector<int> scan(const std::vector<Gate>& gates, const std::vector<char>& done,
+// The scan starts at gate `from` (all before are done) and ends once every
+// qubit of `all` is blocked.
+std::vector<int> scan(const std::vector<Gate>& gates, const std::vector<char>& done, int from, uint64_t all,
                       uint64_t& tile, int cap, bool grow, int max_gates) {
     std::vector<int> exec;
     uint64_t blocked = 0;
     int count = __builtin_popcountll(tile);
     int rotations = 0;
-    for (int i = 0; i < (int)gates.size(); i++) {
+    for (int i = from; i < (int)gates.size() && blocked != all; i++) {
         if (done[i]) continue;
         const Gate& g = gates[i];
         uint64_t qs = (1ull << g.q0) | (n_qubits_of(g) == 2 ? (1ull << g.q1) : 0);
@@ -127,7 +129,8 @@ uint32_t moved_bits(uint32_t h) {
 
 void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_r, int low,
                    uint32_t amp, std::vector<DevPhase>& phases, std::vector<DevDiag>* diags,
-                   std::vector<DevFuse>* fuses, std::vector<DevCzg>* czgs) {
+                   std::vector<DevFuse>* fuses, std::vector<DevCzg>* czgs, std::vector<DevRotRun>* runs,
+                   std::vector<DevRotMember>* run_members) {
     const int r = log_r;
     std::vector<int> bit_of(64, -1);  // qubit -> tile bit
     for (int j = 0; j < k; j++) bit_of[pp.qubits[j]] = j;
@@ -139,16 +142,33 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
     };
     const uint32_t low_bits = (low >= 32) ? 0xffffffffu : ((1u << low) - 1);
     // gates of `pending` that one phase with register bits `regmask` runs (the
-    // same ordered scan the phase itself makes)
+    // same ordered scan the phase itself makes, up to the first gate after
+    // which every qubit is blocked). Asked for hundreds of register sets per
+    // phase, so the pending gates' qubits and needed bits are listed once.
+    struct Need { uint64_t qs; uint32_t bit; };
+    std::vector<Need> needs;
+    uint64_t pending_qs = 0;
+    auto list_needs = [&]() {
+        needs.clear();
+        pending_qs = 0;
+        for (int gi : pending) {
+            const Gate& g = gates[gi];
+            const uint64_t qs = (1ull << g.q0) | (n_qubits_of(g) == 2 ? (1ull << g.q1) : 0);
+            const int b = need_bit(g);
+            needs.push_back({qs, b < 0 ? 0u : 1u << b});
+            pending_qs |= qs;
+        }
+    };
     auto phase_gates = [&](uint32_t regmask) {
         uint64_t blocked = 0;
         int cnt = 0;
-        for (int gi : pending) {
-            const Gate& g = gates[gi];
-            uint64_t qs = (1ull << g.q0) | (n_qubits_of(g) == 2 ? (1ull << g.q1) : 0);
-            int b = need_bit(g);
-            if (!(qs & blocked) && (b < 0 || (regmask >> b & 1))) cnt++;
-            else blocked |= qs;
+        for (const Need& x : needs) {
+            if (!(x.qs & blocked) && !(x.bit & ~regmask)) {
+                cnt++;
+            } else {
+                blocked |= x.qs;
+                if (blocked == pending_qs) break;
+            }
         }
         return cnt;
     };
@@ -183,6 +203,7 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
         return chosen;
     };
     auto choose = [&](uint32_t forbid, const std::vector<int>& keep) {
+        list_needs();
         std::vector<int> chosen = choose_scan(forbid, keep);
         uint32_t best = 0;
         for (int b : chosen) best |= 1u << b;
@@ -280,7 +301,7 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
     // exchange the whole tile's LDS traffic and two barriers); else the best
     // set overall
     auto choose_next = [&]() {
-        std::vector<int> best = choose(0, regs);
+        std::vector<int> best = choose(0, regs);  // (lists the needs for phase_gates below)
         uint32_t bm = 0;
         for (int x : best) bm |= 1u << x;
         if (reachable(bm)) return best;
@@ -305,7 +326,9 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
     phases.push_back(make_phase(pp.qubits, regs, thr, amp));
     pp.first_phase = cur_phase;
 
-    // gradient accumulators: one per rotation in this pass
+    // rotations of this pass, in the order they are placed: each takes one
+    // gradient accumulator, or shares its run's three (numbered at the end)
+    std::vector<int> rot_slots;
     int n_gs = 0;
 
     // location of qubit q in the current layout
@@ -326,8 +349,14 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
     };
     // bwd_arg: the argument of the op's backward form (a layout change takes
     // the backward sweep back to the previous layout)
-    struct Rec { DevOp op; uint32_t bwd_arg; };
+    // run: the rotation run whose RY this op is (its backward form takes the
+    // run's sums first; an RZ joined to it runs before that on its own,
+    // bwd_rz its slot)
+    struct Rec { DevOp op; uint32_t bwd_arg; int run = -1; int bwd_rz = -1; };
     std::vector<Rec> recs;
+    struct Run { std::vector<uint32_t> gs; };  // the members' rotation numbers, by run - run0
+    const int run0 = runs ? (int)runs->size() : 0;
+    std::vector<Run> my_runs;
 
     // layout changes; the backward op list takes each one back to the previous layout
     auto new_phase = [&]() {
@@ -370,6 +399,62 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
             return;
         }
         for (size_t i = 0; i < in.size(); i++) lane_swap(slot_of(regs, out[i]), slot_of(thr, in[i]));
+    };
+
+    // Rotation runs: consecutive rotations on one register bit (no other op
+    // on that bit between them) that cost more than RZ RY RZ (96 operations
+    // per 16 registers and state: RX and RY 48 each, RZ 24) become the three
+    // rotations of their product. Runs that follow each other on different
+    // bits put out their first RZs together, then their RYs, then their last
+    // RZs, so that the RZs of a layer of runs form groups.
+    auto fuse_runs = [&](size_t seg0) {
+        if (!runs) return;
+        std::vector<Rec> out(recs.begin(), recs.begin() + (long)seg0);
+        std::vector<Rec> seq;  // rotations since the last other op
+        auto bit_of_rec = [](const Rec& rc) { return (int)((rc.op.h - H_G1) % 5); };
+        auto put_out = [&]() {
+            int cost[MAX_LOG_R] = {}, run_of[MAX_LOG_R];
+            std::fill(run_of, run_of + MAX_LOG_R, -1);
+            for (const Rec& rc : seq) cost[bit_of_rec(rc)] += (rc.op.h - H_G1) / 5 == 3 ? 24 : 48;
+            std::vector<Rec> mid, last;
+            for (const Rec& rc : seq) {
+                const int j = bit_of_rec(rc);
+                if (cost[j] <= 96 || (run_of[j] < 0 && runs->size() >= (1u << 24))) {
+                    mid.push_back(rc);  // as it is, in its place
+                    continue;
+                }
+                if (run_of[j] < 0) {
+                    const int run = run_of[j] = (int)runs->size(), s = RUN_SLOT + 4 * run;
+                    runs->push_back({(int32_t)run_members->size(), 0});
+                    my_runs.push_back({});
+                    for (const Rec& m : seq)
+                        if (bit_of_rec(m) == j) {
+                            run_members->push_back({(int32_t)((m.op.h - H_G1) / 5), m.op.slot});
+                            runs->back().count++;
+                            my_runs.back().gs.push_back(m.op.arg);
+                        }
+                    out.push_back({make_op(H_G1 + 15 + (uint32_t)j, NO_GSLOT, s, K_RZ), NO_GSLOT});
+                    Rec ry{make_op(H_G1 + 10 + (uint32_t)j, NO_GSLOT, s + 1, K_RY), NO_GSLOT};
+                    ry.run = run;
+                    mid.push_back(ry);
+                    last.push_back({make_op(H_G1 + 15 + (uint32_t)j, NO_GSLOT, s + 2, K_RZ), NO_GSLOT});
+                }
+            }
+            out.insert(out.end(), mid.begin(), mid.end());
+            out.insert(out.end(), last.begin(), last.end());
+            seq.clear();
+        };
+        for (size_t i = seg0; i < recs.size(); i++) {
+            const uint32_t h = recs[i].op.h;
+            if (h >= H_G1 + 5 && h < H_G1 + 20) {
+                seq.push_back(recs[i]);
+                continue;
+            }
+            put_out();
+            out.push_back(recs[i]);
+        }
+        put_out();
+        recs.swap(out);
     };
 
     // RZ groups: within the ops of one layout, each RZ on a register bit is
@@ -434,8 +519,17 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
                 const uint32_t hk = recs[k].op.h;
                 if (hk == H_G1 + 10 + j) {
                     if (fuses->size() >= 65536) break;
+                    // a run's RZ joins a run's RY only (in the forward sweep)
+                    if ((recs[k].run >= 0) != (recs[i].op.arg == NO_GSLOT)) break;
                     const uint32_t idx = (uint32_t)fuses->size();
                     fuses->push_back({recs[i].op.slot, recs[i].op.arg});
+                    if (recs[k].run >= 0) {
+                        recs[k].bwd_rz = recs[i].op.slot;
+                        recs[k].op.h = H_RYZ + j;
+                        recs[k].op.arg = idx << 16;
+                        gone[i] = true;
+                        break;
+                    }
                     const uint32_t arg = recs[k].op.arg | recs[i].op.arg << 8 | idx << 16;
                     recs[k].op.h = H_RYZ + j;
                     recs[k].op.arg = arg;
@@ -536,7 +630,7 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
             uint32_t gs = NO_GSLOT;
             if (is_rotation(g.kind)) {
                 gs = (uint32_t)n_gs++;
-                pp.gslots.push_back(g.slot);
+                rot_slots.push_back(g.slot);
             }
             uint32_t ta, pa, tb, pb;
             DevOp op{};
@@ -573,6 +667,7 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
             }
             recs.push_back({op, op.arg});
         }
+        fuse_runs(seg0);
         group_rz(seg0);
         pair_ryz(seg0);
         group_cz(seg0);
@@ -593,11 +688,50 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
         lds_exchange_to(R, fresh_thr(R));
     }
     pp.last_phase = cur_phase;
-    for (auto& rc : recs) pp.fwd_ops.push_back(rc.op);
+    // Number the gradient accumulators: three per run, then one per rotation
+    // outside any (a run has three members or more, so there are never more
+    // accumulators than rotations).
+    std::vector<int> acc(n_gs, -1);
+    pp.n_acc = 3 * (int)my_runs.size();
+    for (size_t u = 0; u < my_runs.size(); u++)
+        for (size_t m = 0; m < my_runs[u].gs.size(); m++) {
+            const uint32_t gs = my_runs[u].gs[m];
+            acc[gs] = 3 * (int)u;
+            pp.gouts.push_back({rot_slots[gs], 3 * (int)u, (*runs)[run0 + (int)u].first + (int)m});
+        }
+    for (int gs = 0; gs < n_gs; gs++)
+        if (acc[gs] < 0) {
+            acc[gs] = pp.n_acc++;
+            pp.gouts.push_back({rot_slots[gs], acc[gs], -1});
+        }
+    auto renumber = [&](DevOp op) {
+        const uint32_t h = op.h;
+        if ((h >= H_G1 + 5 && h < H_G1 + 20) || (h >= H_RZN && h < H_RZN + 5)) {
+            if (op.arg != NO_GSLOT) op.arg = (uint32_t)acc[op.arg];
+        } else if (h == H_RZU) {
+            op.arg = (op.arg & 0xffffu) | (uint32_t)acc[op.arg >> 16] << 16;
+        } else if (h >= H_RYZ && h < H_RYZ + 5) {
+            op.arg = (op.arg & 0xffff0000u) | (uint32_t)acc[(op.arg >> 8) & 0xffu] << 8 | (uint32_t)acc[op.arg & 0xffu];
+        }
+        return op;
+    };
+    for (const Rec& rc : recs)
+        if (rc.op.h == H_DZ)
+            for (uint32_t& gs : (*diags)[rc.op.arg].gslot)
+                if (gs != NO_GSLOT) gs = (uint32_t)acc[gs];
+    for (const Rec& rc : recs) pp.fwd_ops.push_back(rc.run >= 0 ? rc.op : renumber(rc.op));
     for (int i = (int)recs.size() - 1; i >= 0; i--) {
-        DevOp op = recs[i].op;
-        op.arg = recs[i].bwd_arg;
-        pp.bwd_ops.push_back(op);
+        const Rec& rc = recs[i];
+        DevOp op = rc.op;
+        op.arg = rc.bwd_arg;
+        if (rc.run >= 0) {
+            const uint32_t j = (rc.op.h >= H_RYZ ? rc.op.h - H_RYZ : rc.op.h - H_G1) % 5;
+            if (rc.bwd_rz >= 0) pp.bwd_ops.push_back(make_op(H_G1 + 15 + j, NO_GSLOT, rc.bwd_rz, K_RZ));
+            op = make_op(H_SRY + j, 3u * (uint32_t)(rc.run - run0), RUN_SLOT + 4 * rc.run + 1, K_RY);
+            pp.bwd_ops.push_back(op);
+            continue;
+        }
+        pp.bwd_ops.push_back(renumber(op));
     }
     // A backward layout change refreshes the thread's Im<lambda|psi> sum only
     // when an RZ-type gradient term (RZ on a register, thread or fixed bit,
@@ -605,7 +739,7 @@ void schedule_pass(const std::vector<Gate>& gates, PassPlan& pp, int k, int log_
     auto layout_change = [](uint32_t h) { return h == H_TRANSPOSE || (h >= H_LSWAP && h < H_PX); };
     auto reads_ival = [](uint32_t h) {
         return (h >= H_G1 + 15 && h < H_G1 + 20) || h == H_RZU || (h >= H_RZN && h < H_RZN + 5) || h == H_DZ ||
-               (h >= H_RYZ && h < H_RYZN + 5);
+               (h >= H_RYZ && h < H_RYZN + 5) || (h >= H_SRY && h < H_SRY + 5);
     };
     for (size_t i = 0; i < pp.bwd_ops.size(); i++) {
         if (!layout_change(pp.bwd_ops[i].h)) continue;
@@ -800,6 +934,7 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
             }
         }
     }
+    const uint64_t all_qubits = c.n >= 64 ? ~0ull : (1ull << c.n) - 1;
     const uint64_t low_tile = (low >= 64) ? ~0ull : ((1ull << low) - 1);
     // Candidate tiles of the next pass: first-need greedy growth, and
     // contiguous windows of the high qubits.
@@ -810,12 +945,14 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
     auto candidates = [&](const std::vector<char>& dn) {
         std::vector<Cand> out;
         uint64_t t = low_tile;
-        std::vector<int> e = scan(c.gates, dn, t, k, true, o.max_gates_per_pass);
+        int from = 0;
+        while (from < G && dn[from]) from++;
+        std::vector<int> e = scan(c.gates, dn, from, all_qubits, t, k, true, o.max_gates_per_pass);
         out.push_back({std::move(e), t});
         const int h = k - low;
         for (int s = low; s + h <= c.n; s++) {
             uint64_t w = low_tile | (((1ull << h) - 1) << s);
-            std::vector<int> ew = scan(c.gates, dn, w, k, false, o.max_gates_per_pass);
+            std::vector<int> ew = scan(c.gates, dn, from, all_qubits, w, k, false, o.max_gates_per_pass);
             out.push_back({std::move(ew), w});
         }
         return out;
@@ -959,7 +1096,8 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
             pp.gates = std::move(cd.gates);
             schedule_pass(c.gates, pp, k, log_r, low, dtype == 0 ? 8u : 16u, to.phases,
                           o.rz_groups == 0 ? &to.diags : nullptr, o.rz_groups == 0 ? &to.fuses : nullptr,
-                          o.cz_groups == 0 ? &to.czgs : nullptr);
+                          o.cz_groups == 0 ? &to.czgs : nullptr, o.rz_groups == 0 ? &to.runs : nullptr,
+                          o.rz_groups == 0 ? &to.run_members : nullptr);
             to.passes.push_back(std::move(pp));
         }
     };
@@ -1002,6 +1140,8 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
                 to.diags = std::move(t.diags);
                 to.fuses = std::move(t.fuses);
                 to.czgs = std::move(t.czgs);
+                to.runs = std::move(t.runs);
+                to.run_members = std::move(t.run_members);
             }
         }
         return best;
@@ -1023,6 +1163,8 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
         pl.diags = std::move(t.diags);
         pl.fuses = std::move(t.fuses);
         pl.czgs = std::move(t.czgs);
+        pl.runs = std::move(t.runs);
+        pl.run_members = std::move(t.run_members);
         pl.product = true;
         pl.pre_gates = absorbed;
         std::vector<std::vector<DevPrefix>> mine(c.n);

@@ -82,11 +82,31 @@ enum HandlerId : uint32_t {
     H_NOP = 149,
     H_END = 150,
     H_CZG = 151,       // CZ group: the CZs of one layout in one sign op; arg = group index (DevCzg)
+    H_SRY = 152,       // + J: backward form of a rotation run's RY on register bit J: the run's three
+                       //      gradient sums Im<lambda|P|psi>, P = X, Y, Z, then the inverse RY; arg =
+                       //      first of their three accumulators
 };
 // The RZ of an RY-RZ pair op (H_RYZ): its rotation slot and gradient slot.
 struct DevFuse {
     int32_t slot;
     uint32_t gslot;
+};
+// A rotation run: RUN_MIN_COST or more of consecutive rotations of one qubit
+// on a register bit become RZ(alpha) RY(beta) RZ(gamma), angles from
+// k_bind_runs per sample. Their "slots" are RUN_SLOT + 4 * run + (0 alpha, 1
+// beta, 2 gamma). The gradient of every rotation of the run is the scalar
+// product of the run's three sums with an axis (k_bind_runs).
+constexpr int32_t RUN_SLOT = 1 << 28;
+struct DevRotRun {
+    int32_t first, count;  // members
+};
+struct DevRotMember {
+    int32_t kind, slot;
+};
+// One rotation's gradient of a pass: its slot, its accumulator (axis < 0) or
+// the first of its run's three and its axis (index of k_bind_runs' table).
+struct DevGradOut {
+    int32_t slot, acc, axis;
 };
 // Register bits an RZ group can span (its gradient slots travel in the op
 // record's two coefficient words, 16 bits each).
@@ -208,19 +228,20 @@ struct DevPass {
     int32_t bwd_begin, bwd_end;
     int32_t load_phase;      // layout at the start of the forward ops
     int32_t bwd_phase;       // layout at the start of the backward ops
-    int32_t gslot_base;      // first entry in the plan's gslot -> rotation-slot table
+    int32_t gout_base;       // first of the pass's entries in the plan's DevGradOut table
     int32_t n_exchanges;     // LDS layout changes in the forward ops
     int32_t index;           // pass index in the plan
     int32_t tile_qubit[MAX_TILE_BITS];  // tile bit -> qubit
     int32_t fixed_qubit[32];            // ascending qubits outside the tile
-    int32_t pad[3];
+    int32_t n_gouts;
+    int32_t pad[2];
 };
 
 struct Options {
     int log_regs = 0, log_threads = 0, low_qubits = 0, max_gates_per_pass = 0;
     int force_tiled = 0, wg_per_sample = 0;
-    int rz_groups = 0;  // 0: RZs on register bits are grouped into H_DZ ops or joined to their
-                        // bit's RY (H_RYZ); -1: every RZ runs on its own
+    int rz_groups = 0;  // 0: rotation runs become RZ RY RZ, and RZs on register bits are grouped into
+                        // H_DZ ops or joined to their bit's RY (H_RYZ); -1: every rotation runs on its own
     int product_prefix = 0;  // each qubit's leading one-qubit gates form the initial product state
                              // (tile plans without an embedding): 0 when the rest plans no worse,
                              // 1 always, -1 never (they run as ops)
@@ -238,7 +259,8 @@ struct PassPlan {
     std::vector<int> gates;           // gate indices in execution order
     std::vector<DevOp> fwd_ops;       // with TRANSPOSE entries
     std::vector<DevOp> bwd_ops;
-    std::vector<int> gslots;          // pass-local gradient accumulator -> rotation slot
+    std::vector<DevGradOut> gouts;    // the rotations' gradients
+    int n_acc = 0;                    // gradient accumulators
     int first_phase = 0;              // phase index at pass start (forward)
     int last_phase = 0;               // phase index at pass end (forward)
     int n_transposes = 0;             // layout changes through LDS
@@ -252,6 +274,8 @@ struct Plan {
     std::vector<DevPhase> phases;
     std::vector<DevDiag> diags;  // RZ groups (H_DZ ops), all passes
     std::vector<DevFuse> fuses;  // RZs of RY-RZ pair ops (H_RYZ), all passes
+    std::vector<DevRotRun> runs; // rotation runs, all passes
+    std::vector<DevRotMember> run_members;
     std::vector<DevCzg> czgs;    // CZ groups (H_CZG ops), all passes
     int n_slots = 0;           // rotation slots
     // Product prefix (tile plans): the gates of pre_ops[pre_ptr[q] .. pre_ptr[q+1])

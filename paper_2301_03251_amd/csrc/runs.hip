@@ -261,47 +261,6 @@ __device__ __forceinline__ void flip_signs(T2* a, uint32_t m) {
     }
 }
 
-struct Z2 {  // 2x2 complex fp64
-    double2 a, b, c, d;
-};
-// gate * m for the gate of a member (cs: cos, sin of half its angle; a Pauli's index)
-__device__ __forceinline__ void left_row(int kind, double2 cs, double2 u, double2 v, double2& o0, double2& o1) {
-    switch (kind) {
-        case K_H: {
-            const double r = 0.70710678118654752440;
-            o0 = make_double2(r * (u.x + v.x), r * (u.y + v.y));
-            o1 = make_double2(r * (u.x - v.x), r * (u.y - v.y));
-        } break;
-        case K_RX:  // [[c, -i s], [-i s, c]]
-            o0 = make_double2(cs.x * u.x + cs.y * v.y, cs.x * u.y - cs.y * v.x);
-            o1 = make_double2(cs.x * v.x + cs.y * u.y, cs.x * v.y - cs.y * u.x);
-            break;
-        case K_RY:
-            o0 = make_double2(cs.x * u.x - cs.y * v.x, cs.x * u.y - cs.y * v.y);
-            o1 = make_double2(cs.y * u.x + cs.x * v.x, cs.y * u.y + cs.x * v.y);
-            break;
-        case K_RZ:
-            o0 = cxmul(u, make_double2(cs.x, -cs.y));
-            o1 = cxmul(v, make_double2(cs.x, cs.y));
-            break;
-        default: {
-            const int w = (int)cs.x;
-            o0 = w == 1 ? v : w == 2 ? make_double2(v.y, -v.x) : u;
-            o1 = w == 1 ? u : w == 2 ? make_double2(-u.y, u.x) : w == 3 ? make_double2(-v.x, -v.y) : v;
-        }
-    }
-}
-__device__ __forceinline__ Z2 left_mul(int kind, double2 cs, const Z2& m) {
-    Z2 r;
-    left_row(kind, cs, m.a, m.c, r.a, r.c);
-    left_row(kind, cs, m.b, m.d, r.b, r.d);
-    return r;
-}
-__device__ __forceinline__ Z2 zident() {
-    const double2 o = make_double2(1.0, 0.0), z = make_double2(0.0, 0.0);
-    return {o, z, z, o};
-}
-
 // Gate record of a step held by a lane (see run_record).
 struct Step {
     uint32_t op, mat, y;
@@ -673,13 +632,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
                 const int2 sl = *(const int2*)&members[e.first + k].slot;
                 gs[sl.x] = own;
                 if (sl.y >= 0) gs[sl.y] = -own;  // the half-angle pair: scales +1/2 and -1/2
-                // the next two axes in cyclic order, (u, v) -> (c u + s v, c v - s u)
-                const double u = kind == K_RX ? S[1] : kind == K_RY ? S[2] : S[0];
-                const double v = kind == K_RX ? S[2] : kind == K_RY ? S[0] : S[1];
-                const double u2 = c * u + sn * v, v2 = c * v - sn * u;
-                S[0] = kind == K_RX ? S[0] : kind == K_RY ? v2 : u2;
-                S[1] = kind == K_RX ? u2 : kind == K_RY ? S[1] : v2;
-                S[2] = kind == K_RX ? v2 : kind == K_RY ? u2 : S[2];
+                sums_before(kind, c, sn, S);
             }
         }
     }

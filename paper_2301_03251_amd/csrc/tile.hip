@@ -548,10 +548,11 @@ __device__ __forceinline__ void run_op(uint32_t h, uint32_t arg, Real ca, Real c
 #define QL_G1_CASE(KIND, J)                                                                 \
     case H_G1 + KIND * 5 + J:                                                               \
         if constexpr (J < LOG_R) {                                                          \
-            if constexpr (OPM == OP_BWD && KIND == 3)                                       \
-                grad_add(gacc, arg, fma((Real)-2, im_sum<LOG_R, J, T2, Real>(ps, lm), ival),  \
-                         lane, wave, nw);                                                   \
-            else if constexpr (OPM == OP_BWD && KIND != 0)                                  \
+            if constexpr (OPM == OP_BWD && KIND == 3) {                                     \
+                if (arg != NO_GSLOT) /* else a rotation run's RZ */                          \
+                    grad_add(gacc, arg, fma((Real)-2, im_sum<LOG_R, J, T2, Real>(ps, lm), ival), \
+                             lane, wave, nw);                                               \
+            } else if constexpr (OPM == OP_BWD && KIND != 0)                                  \
                 grad_add(gacc, arg, gpart<LOG_R, KIND, J, T2, Real>(ps, lm), lane, wave, nw); \
             if constexpr (OPM != OP_ONE) g1<LOG_R, KIND, J, T2, Real>(lm, ca, cb);            \
             g1<LOG_R, KIND, J, T2, Real>(ps, ca, cb);                                       \
@@ -561,8 +562,9 @@ __device__ __forceinline__ void run_op(uint32_t h, uint32_t arg, Real ca, Real c
     case H_RZN + J:                                                                         \
         if constexpr (J < LOG_R) {                                                          \
             if constexpr (OPM == OP_BWD)                                                    \
-                grad_add(gacc, arg, fma((Real)-2, im_sum<LOG_R, J, T2, Real>(ps, lm), ival),  \
-                         lane, wave, nw);                                                   \
+                if (arg != NO_GSLOT)                                                        \
+                    grad_add(gacc, arg, fma((Real)-2, im_sum<LOG_R, J, T2, Real>(ps, lm), ival), \
+                             lane, wave, nw);                                               \
             if constexpr (OPM != OP_ONE) g1<LOG_R, 3, J, T2, Real, true>(lm, ca, cb);         \
             g1<LOG_R, 3, J, T2, Real, true>(ps, ca, cb);                                    \
         }                                                                                   \
@@ -653,6 +655,18 @@ __device__ __forceinline__ void run_op(uint32_t h, uint32_t arg, Real ca, Real c
         }                                                                                   \
         break;
 #define QL_RYZ_J(J) QL_RYZ_CASE(J, false) QL_RYZ_CASE(J, true)
+// a rotation run's sums (X and Y by pairs, Z as for an RZ), then its RY's inverse
+#define QL_SRY_CASE(J)                                                                      \
+    case H_SRY + J:                                                                         \
+        if constexpr (J < LOG_R && OPM == OP_BWD) {                                         \
+            grad_add(gacc, arg, gpart<LOG_R, 1, J, T2, Real>(ps, lm), lane, wave, nw);      \
+            grad_add(gacc, arg + 1, gpart<LOG_R, 2, J, T2, Real>(ps, lm), lane, wave, nw);  \
+            grad_add(gacc, arg + 2, fma((Real)-2, im_sum<LOG_R, J, T2, Real>(ps, lm), ival), \
+                     lane, wave, nw);                                                       \
+            g1<LOG_R, 2, J, T2, Real>(lm, ca, cb);                                          \
+            g1<LOG_R, 2, J, T2, Real>(ps, ca, cb);                                          \
+        }                                                                                   \
+        break;
 #define QL_CZ_RX(A)                                                                         \
     case H_CZ_RX + A:                                                                       \
         if constexpr (A < LOG_R) {                                                          \
@@ -670,6 +684,7 @@ __device__ __forceinline__ void run_op(uint32_t h, uint32_t arg, Real ca, Real c
         QL_LSWAP_M(0) QL_LSWAP_M(1) QL_LSWAP_M(2) QL_LSWAP_M(3) QL_LSWAP_M(4)
         QL_PAULI_J(0) QL_PAULI_J(1) QL_PAULI_J(2) QL_PAULI_J(3) QL_PAULI_J(4)
         QL_RYZ_J(0) QL_RYZ_J(1) QL_RYZ_J(2) QL_RYZ_J(3) QL_RYZ_J(4)
+        QL_SRY_CASE(0) QL_SRY_CASE(1) QL_SRY_CASE(2) QL_SRY_CASE(3) QL_SRY_CASE(4)
         case H_NOP:
             break;
         case H_DZ:
@@ -737,6 +752,7 @@ __device__ __forceinline__ void run_op(uint32_t h, uint32_t arg, Real ca, Real c
 #undef QL_PAULI_CASE
 #undef QL_PAULI_J
 #undef QL_RYZ_CASE
+#undef QL_SRY_CASE
 #undef QL_RYZ_J
 }
 
@@ -797,7 +813,7 @@ template <typename Real, int LOG_R, int KM, int MAXT>
 __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(2)))
 k_tile(const TileArgs a, const DevPass* __restrict__ pass, const DevPhase* __restrict__ phases,
        const XOp<Real>* __restrict__ xops_all, const Real* __restrict__ gout_all,
-       const int32_t* __restrict__ gslots, const typename Cx<Real>::T* __restrict__ dz_all,
+       const DevGradOut* __restrict__ gouts, const typename Cx<Real>::T* __restrict__ dz_all,
        const typename Cx<Real>::T* __restrict__ fz_all) {
     using T2 = typename Cx<Real>::T;
     constexpr bool BWD = KM == KM_BWD, PAIR = KM == KM_FWD2;
@@ -1042,10 +1058,19 @@ k_tile(const TileArgs a, const DevPass* __restrict__ pass, const DevPhase* __res
             a.zpart[((size_t)b * a.n_wg + w) * n + q] = t;
         }
     if (BWD && (flags & PF_BWD))
-        for (int g = tid; g < a.n_gslots; g += nt) {
-            double t = 0;
-            for (int v = 0; v < NW * GW; ++v) t += (double)gacc[g * NW * GW + v];
-            a.gpart[((size_t)gslots[g] * a.B + b) * a.n_wg + w] = t;
+        for (int g = tid; g < a.n_gouts; g += nt) {
+            const DevGradOut o = gouts[g];
+            auto total = [&](int c) {
+                double t = 0;
+                for (int v = 0; v < NW * GW; ++v) t += (double)gacc[c * NW * GW + v];
+                return t;
+            };
+            double t = total(o.acc);
+            if (o.axis >= 0) {  // a rotation run's member: its axis times the run's sums
+                const double* n3 = a.axes + ((size_t)b * a.n_members + o.axis) * 3;
+                t = n3[0] * t + n3[1] * total(o.acc + 1) + n3[2] * total(o.acc + 2);
+            }
+            a.gpart[((size_t)o.slot * a.B + b) * a.n_wg + w] = t;
         }
 }
 
@@ -1060,13 +1085,13 @@ static hipError_t launch_tile_t(bool bwd, const TileArgs& a, int threads, size_t
     const typename Cx<Real>::T* fzt = (const typename Cx<Real>::T*)a.fzc;
     if (bwd)
         hipLaunchKernelGGL((k_tile<Real, LOG_R, KM_BWD, MAXT>), grid, dim3(threads), lds, s, a, a.pass,
-                           a.phases, xo, gout, a.gslots, dzt, fzt);
+                           a.phases, xo, gout, a.gouts, dzt, fzt);
     else if (a.tiles >= 2)  // forward passes carry two tiles per iteration when there are two
         hipLaunchKernelGGL((k_tile<Real, LOG_R, KM_FWD2, MAXT>), grid, dim3(threads), lds, s, a, a.pass,
-                           a.phases, xo, gout, a.gslots, dzt, fzt);
+                           a.phases, xo, gout, a.gouts, dzt, fzt);
     else
         hipLaunchKernelGGL((k_tile<Real, LOG_R, KM_FWD1, MAXT>), grid, dim3(threads), lds, s, a, a.pass,
-                           a.phases, xo, gout, a.gslots, dzt, fzt);
+                           a.phases, xo, gout, a.gouts, dzt, fzt);
     return hipGetLastError();
 }
 

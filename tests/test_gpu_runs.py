@@ -1,0 +1,192 @@
+"""The run kernel (small states) and the tile kernel's rotation runs against
+the CPU oracle, at the sizes where they can go wrong (needs an MI355X).
+
+Tolerances as in test_gpu_parity: 1e-5 (complex64) and 1e-12 (complex128)
+absolute, the bounds every comparison with the oracle holds.
+"""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+from parity import check, close
+
+torch = pytest.importorskip("torch")
+import paper_2301_03251_amd as Q  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"c64": 1e-5, "c128": 1e-12}
+ALL = (W.H, W.RX, W.RY, W.RZ, W.CNOT, W.CZ, W.CRX, W.CRY, W.CRZ)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    Q.load()
+
+
+def _dev(a, dtype):
+    real = torch.float32 if dtype == "c64" else torch.float64
+    return torch.from_numpy(np.ascontiguousarray(a)).to(device="cuda", dtype=real)
+
+
+def _fb(runner, dtype, x, w, g):
+    e, gx, gw = runner.forward_backward(_dev(x, dtype), _dev(w, dtype), _dev(g, dtype))
+    torch.cuda.synchronize()
+    return {"expz": e.cpu().double().numpy(), "grad_inputs": gx.cpu().double().numpy(),
+            "grad_weights": gw.cpu().double().numpy()}
+
+
+def _all_paths(n, gates, F, P, B, dtype, seed, embed=None, pauli_p=None, amplitude=False):
+    """Forward + adjoint, forward alone and final states, each against the oracle."""
+    x, w, g = W.random_inputs(B, F, P, n, seed=seed, dtype=dtype)
+    if pauli_p is not None:
+        x[:, F - len(pauli_p):] = np.random.default_rng(seed).random((B, len(pauli_p))).astype(x.dtype)
+    x[0, 0] = 9.0  # well outside [-pi, pi]
+    r = Q.Runner(Q.Circuit(n, gates, F, P, embed=embed, pauli_p=pauli_p), dtype)
+    what = f"n={n} {dtype} B={B} G={len(gates)}"
+    want = oracle.run(n, gates, x, w, grad_out=g, embed=embed, pauli_p=pauli_p, want_state=True)
+    check(_fb(r, dtype, x, w, g), want, TOL[dtype], what)
+    e = r.forward(_dev(x, dtype), _dev(w, dtype))
+    psi = r.state(_dev(x, dtype), _dev(w, dtype))
+    torch.cuda.synchronize()
+    close(e.cpu().double().numpy(), want["expz"], TOL[dtype], what, "forward")
+    close(psi.cpu().numpy(), want["state"], TOL[dtype], what, "state")
+
+
+@pytest.mark.parametrize("dtype", ["c64", "c128"])
+@pytest.mark.parametrize("n", list(range(1, 13)))
+def test_every_gate_kind(n, dtype):
+    """Every size of the kernel's layouts (registers, lanes, wavefronts): runs,
+    controlled runs, exchanges, signs and Pauli channels."""
+    F, P = 4, 6
+    gates = W.random_circuit(n, 30 + 8 * n, F, P, seed=900 + n, kinds=ALL)
+    channels = np.array([[W.PAULI, q % n, -1, W.SRC_INPUT, F + q] for q in range(3)], np.int32)
+    half = len(gates) // 2
+    gates = np.concatenate([gates[:half], channels, gates[half:]])
+    _all_paths(n, gates, F + 3, P, 3, dtype, seed=n, pauli_p=[[0.3, 0.3, 0.3], [0.2, 0.5, 0.1], [0.1, 0.1, 0.6]])
+
+
+@pytest.mark.parametrize("n,G,B", [(5, 700, 2), (10, 500, 1), (3, 0, 2), (9, 0, 1)])
+def test_long_and_empty(n, G, B):
+    """More steps than one chunk of 64 records, no gates at all, and a single
+    sample (whose weight gradients the kernel writes itself)."""
+    _all_paths(n, W.random_circuit(n, G, 3, 4, seed=G + n, kinds=ALL), 3, 4, B, "c128", seed=n)
+
+
+@pytest.mark.parametrize("n,dtype", [(2, "c64"), (6, "c128"), (9, "c64"), (12, "c128")])
+def test_real_layers(n, dtype):
+    """Layers of RY and H only, and one that a later RZ makes complex."""
+    gates = np.concatenate([W.random_circuit(n, 60, 3, 5, seed=n, kinds=(W.RY, W.H, W.CZ, W.CNOT)),
+                            W.random_circuit(n, 40, 3, 5, seed=n + 1, kinds=(W.RY, W.H, W.RZ, W.CZ))])
+    _all_paths(n, gates, 3, 5, 4, dtype, seed=40 + n)
+
+
+@pytest.mark.parametrize("kind", ["basis", "amplitude"])
+@pytest.mark.parametrize("n,dtype", [(1, "c128"), (7, "c64"), (9, "c128"), (12, "c64")])
+def test_embeddings(n, dtype, kind):
+    F = n if kind == "basis" else 1 << n
+    gates = W.random_circuit(n, 50, F, 4, seed=60 + n, kinds=ALL)
+    _all_paths(n, gates, F, 4, 3, dtype, seed=61 + n,
+               embed=(W.EMBED_BASIS if kind == "basis" else W.EMBED_AMPLITUDE, 0))
+
+
+@pytest.mark.parametrize("n,dtype", [(4, "c64"), (7, "c128"), (10, "c128")])
+def test_param_shift(n, dtype):
+    """Shifted circuits, controlled rotations (each half shifted on its own)
+    and chunks that cut a sample's circuits apart."""
+    F, P, B = 3, 4, 3
+    gates = W.random_circuit(n, 30, F, P, seed=80 + n, kinds=ALL)
+    x, w, g = W.random_inputs(B, F, P, n, seed=81 + n, dtype=dtype)
+    r = Q.Runner(Q.Circuit(n, gates, F, P), dtype)
+    e, gx, gw = r.param_shift(_dev(x, dtype), _dev(w, dtype), _dev(g, dtype), max_chunk=29)
+    torch.cuda.synchronize()
+    got = {"expz": e.cpu().double().numpy(), "grad_inputs": gx.cpu().double().numpy(),
+           "grad_weights": gw.cpu().double().numpy()}
+    check(got, oracle.run(n, gates, x, w, grad_out=g), TOL[dtype], f"shift n={n} {dtype}")
+
+
+@pytest.mark.parametrize("n,dtype,limit", [(11, "c128", 512), (12, "c64", 256)])
+def test_batch_rule(n, dtype, limit):
+    """On both sides of the batch from which the tile kernel takes the step:
+    the rows of the smaller batch agree, and the last row with the oracle."""
+    F, P = 3, 4
+    gates = W.random_circuit(n, 40, F, P, seed=n)
+    x, w, g = W.random_inputs(limit + 1, F, P, n, seed=n, dtype=dtype)
+    r = Q.Runner(Q.Circuit(n, gates, F, P), dtype)
+    big, small = _fb(r, dtype, x, w, g), _fb(r, dtype, x[:limit], w, g[:limit])
+    for k in ("expz", "grad_inputs"):
+        close(big[k][:limit], small[k], 2 * TOL[dtype], f"n={n} {dtype}", k)  # each within TOL of the truth
+        close(big[k][-1:], oracle.run(n, gates, x[-1:], w, grad_out=g[-1:])[k], TOL[dtype], f"n={n} {dtype}", k)
+
+
+def run_layers(n, layers, F, P, seed):
+    """Layers of two to four rotations per qubit (all orders, so some qubits
+    have runs and others do not) and CNOTs, CZs over a brick."""
+    rng = np.random.default_rng(seed)
+    gates = []
+    for _ in range(layers):
+        for q in range(n):
+            for kind in rng.choice([W.RX, W.RY, W.RZ], size=int(rng.integers(2, 5))):
+                src = (W.SRC_INPUT, int(rng.integers(F))) if rng.random() < 0.3 else (W.SRC_WEIGHT, int(rng.integers(P)))
+                gates.append((int(kind), q, -1) + src)
+        gates += [(W.CNOT if rng.random() < 0.7 else W.CZ, a, b, 0, 0) for a, b in W.entangler_pairs(n, "brick")]
+    return np.array(gates, np.int32)
+
+
+@pytest.mark.parametrize("n,dtype,opts", [(13, "c64", {}), (14, "c128", {}), (15, "c64", dict(log_regs=5, log_threads=7)),
+                                          (12, "c64", dict(log_regs=2, log_threads=8)),
+                                          (12, "c128", dict(log_regs=3, log_threads=6, max_gates_per_pass=30))])
+def test_tile_rotation_runs(n, dtype, opts):
+    """Rotation runs of the tile plans, with and without the product prefix:
+    forward + adjoint, exact states, and the plan without runs."""
+    F, P, B = 4, 6, 2
+    gates = run_layers(n, 3, F, P, seed=100 + n)
+    x, w, g = W.random_inputs(B, F, P, n, seed=101 + n, dtype=dtype)
+    x[0, 0], w[1] = 9.0, -7.5
+    want = oracle.run(n, gates, x, w, grad_out=g, want_state=True)
+    for extra in (dict(), dict(product_prefix=-1), dict(rz_groups=-1)):
+        r = Q.Runner(Q.Circuit(n, gates, F, P, **opts, **extra), dtype)
+        check(_fb(r, dtype, x, w, g), want, TOL[dtype], f"runs n={n} {dtype} {extra}")
+        psi = r.state(_dev(x, dtype), _dev(w, dtype))
+        torch.cuda.synchronize()
+        close(psi.cpu().numpy(), want["state"], TOL[dtype], f"runs n={n} {dtype} {extra}", "state")
+
+
+def test_tile_rotation_runs_param_shift():
+    n, F, P, B = 13, 3, 5, 2
+    gates = run_layers(n, 1, F, P, seed=7)
+    x, w, g = W.random_inputs(B, F, P, n, seed=8, dtype="c128")
+    r = Q.Runner(Q.Circuit(n, gates, F, P, product_prefix=-1), "c128")
+    e, gx, gw = r.param_shift(_dev(x, "c128"), _dev(w, "c128"), _dev(g, "c128"), max_chunk=37)
+    torch.cuda.synchronize()
+    got = {"expz": e.cpu().numpy(), "grad_inputs": gx.cpu().numpy(), "grad_weights": gw.cpu().numpy()}
+    check(got, oracle.run(n, gates, x, w, grad_out=g), 1e-12, "runs shift")
+
+
+def test_captured_calls():
+    """A captured forward + adjoint call (tables already on the device) replays
+    to the eager results, for a run-kernel and a tile circuit."""
+    for n in (9, 13):
+        gates = W.random_circuit(n, 60, 3, 4, seed=n)
+        x, w, g = (_dev(a, "c64") for a in W.random_inputs(4, 3, 4, n, seed=n, dtype="c64"))
+        r = Q.Runner(Q.Circuit(n, gates, 3, 4), "c64")
+        want = [t.clone() for t in r.forward_backward(x, w, g)]
+        outs = tuple(torch.empty_like(t) for t in want)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            r.forward_backward(x, w, g, outs=outs)
+        for _ in range(3):
+            for t in outs:
+                t.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            for a, b in zip(outs, want):
+                assert torch.equal(a, b)
+            r.forward_backward(x, w, g)
