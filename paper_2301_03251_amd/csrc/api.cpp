@@ -585,6 +585,7 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ba.B = B;
         ba.n_ops = x.T.n_ops;
         ba.bwd_first = x.T.bwd_first;
+        ba.bwd = x.L.gpart ? 1 : 0;
         ba.F = x.c.n_inputs;
         ba.v0 = v0;
         ba.vper = vper;

@@ -322,18 +322,29 @@ __global__ void __launch_bounds__(256) k_bind_runs(const BindRunsArgs a) {
     }
 }
 
+// Shear coefficients of a plane rotation by phi (|phi| <= pi/2): tan(phi/2) and
+// sin(phi), from one sincos of the half angle.
+__device__ __forceinline__ void shear_coef(double phi, double& a, double& b) {
+    double s, c;
+    sincos(0.5 * phi, &s, &c);
+    a = s / c;
+    b = 2.0 * s * c;
+}
+
 template <typename Real>
 __global__ void k_bind_tile(const BindTileArgs a) {
     using T2 = typename Cx<Real>::T;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t per = (int64_t)a.n_ops + 1;
-    if (t >= a.B * per) return;
-    const int64_t b = t / per;
-    const int o = (int)(t - b * per);
+    // the forward ops' records alone when nothing reads the backward ones
+    const int64_t per = (int64_t)a.n_ops + 1, n_bound = a.bwd ? per : (int64_t)a.bwd_first + 1;
+    if (t >= a.B * n_bound) return;
+    const int64_t b = t / n_bound;
+    const int o = (int)(t - b * n_bound);
+    XOp<Real>* out = (XOp<Real>*)a.opc + b * per + o;
     XOp<Real> e{};
-    if (o == a.n_ops) {  // the record after the last op (read by the op-loop prefetch)
+    if (o == n_bound - 1) {  // the record after the last op (read by the op-loop prefetch)
         e.h = H_END;
-        ((XOp<Real>*)a.opc)[t] = e;
+        *out = e;
         return;
     }
     const DevOp op = a.ops[o];
@@ -353,20 +364,19 @@ __global__ void k_bind_tile(const BindTileArgs a) {
             e.a = __builtin_bit_cast(double, w);
         }
         if (o < a.bwd_first) {
-            double th[MAX_DZ_BITS];
+            // a phase per register: products of the members' phases
+            double2 ph[DZ_REGS];
+            ph[0] = make_double2(1.0, 0.0);
+#pragma unroll
             for (int j = 0; j < MAX_DZ_BITS; ++j) {
-                th[j] = 0.0;
-                if (d.slot[j] >= 0) th[j] = op_angle<Real>(a, d.slot[j], b);
+                double2 f = make_double2(1.0, 0.0);
+                if (d.slot[j] >= 0) sincos(op_angle<Real>(a, d.slot[j], b), &f.y, &f.x);
+#pragma unroll
+                for (int i = 0; i < (1 << j); ++i) ph[i | 1 << j] = cxmul(ph[i], f);
             }
             T2* tab = (T2*)a.dzc + ((size_t)b * a.n_diags + op.arg) * DZ_REGS;
-            for (int i = 0; i < DZ_REGS; ++i) {
-                double phi = 0.0;
-                for (int j = 0; j < MAX_DZ_BITS; ++j)
-                    if (i >> j & 1) phi += th[j];
-                double sn, cs;
-                sincos(phi, &sn, &cs);
-                tab[i] = mk<T2>((Real)cs, (Real)sn);
-            }
+#pragma unroll
+            for (int i = 0; i < DZ_REGS; ++i) tab[i] = to_real<T2, Real>(ph[i]);
         }
     } else if (op.kind == K_PAULI) {
         // the Pauli this sample's trajectory draws, on the op's register bit
@@ -377,6 +387,7 @@ __global__ void k_bind_tile(const BindTileArgs a) {
         const double two_pi = 6.283185307179586476925;
         th -= two_pi * rint(th / two_pi);  // [-pi, pi]; the dropped sign is common to psi and lambda
         if (o >= a.bwd_first) th = -th;     // backward ops apply the inverse
+        double ca, cb;
         if (op.h >= H_G1 + 15 && op.h < H_G1 + 20) {
             // RZ on a register bit: phase exp(i phi) on the bit-1 amplitudes,
             // phi = theta moved into [-pi/2, pi/2] (a move by pi negates them)
@@ -385,13 +396,12 @@ __global__ void k_bind_tile(const BindTileArgs a) {
             if (phi > half_pi) phi -= 2.0 * half_pi;
             else if (phi < -half_pi) phi += 2.0 * half_pi;
             if (phi != th) e.h = H_RZN + (op.h - (H_G1 + 15));
-            e.a = (Real)tan(0.5 * phi);
-            e.b = (Real)sin(phi);
+            shear_coef(phi, ca, cb);
         } else {
-            // plane rotation by phi = theta/2: a = tan(phi/2), b = sin(phi)
-            e.a = (Real)tan(0.25 * th);
-            e.b = (Real)sin(0.5 * th);
+            shear_coef(0.5 * th, ca, cb);  // plane rotation by theta/2
         }
+        e.a = (Real)ca;
+        e.b = (Real)cb;
         if (op.h >= H_RYZ && op.h < H_RYZ + 5) {
             // RY-RZ pair: the RZ's phase, reduced as for a single RZ, from the
             // forward angle in both records (the backward form inverts it);
@@ -404,11 +414,13 @@ __global__ void k_bind_tile(const BindTileArgs a) {
             if (phi > half_pi) phi -= 2.0 * half_pi;
             else if (phi < -half_pi) phi += 2.0 * half_pi;
             if (phi != tz) e.h = H_RYZN + (op.h - H_RYZ);
-            if (o < a.bwd_first)
-                ((T2*)a.fzc)[(size_t)b * a.n_fuses + fi] = mk<T2>((Real)tan(0.5 * phi), (Real)sin(phi));
+            if (o < a.bwd_first) {
+                shear_coef(phi, ca, cb);
+                ((T2*)a.fzc)[(size_t)b * a.n_fuses + fi] = mk<T2>((Real)ca, (Real)cb);
+            }
         }
     }
-    ((XOp<Real>*)a.opc)[t] = e;
+    *out = e;
 }
 
 // ---------------------------------------------------------------------------
@@ -1222,7 +1234,7 @@ hipError_t launch_whole(int dtype, const WholeArgs& a, int threads, size_t lds, 
 }
 
 hipError_t launch_bind_tile(int dtype, const BindTileArgs& a, hipStream_t s) {
-    const int64_t total = a.B * ((int64_t)a.n_ops + 1);
+    const int64_t total = a.B * ((int64_t)(a.bwd ? a.n_ops : a.bwd_first) + 1);
     const unsigned grid = (unsigned)((total + 255) / 256);
     if (dtype == 0) hipLaunchKernelGGL(k_bind_tile<float>, dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL(k_bind_tile<double>, dim3(grid), dim3(256), 0, s, a);

@@ -53,6 +53,7 @@ struct BindTileArgs {
     int32_t n_fuses;
     int64_t B;
     int32_t n_ops, bwd_first, F;
+    int32_t bwd;           // 0: the forward ops only (no backward sweep follows)
     int64_t v0;            // parameter-shift chunks: first virtual circuit
     int32_t vper;          // circuits per sample (2 * n_slots + 1), 0 = plain batch
 };
