@@ -203,14 +203,9 @@ struct ql_circuit {
     RunPlan rp;
     bool runs[2][2] = {};  // [dtype][with a backward]: the run kernel can take the call
     Tables t[2][2];        // [dtype][0: tile or whole-state plan, 1: run plan]
-    // pinned host copies of the table blobs (made on the first call that uses
-    // each), so the per-call upload is an asynchronous DMA
-    void* pinned[2][2] = {};
-    std::once_flag pin_once[2][2];
-    // an event per stream that copied from a pinned blob, recorded after each
-    // such copy: destruction waits for these copies only
-    std::mutex up_mu;
-    std::vector<std::pair<hipStream_t, hipEvent_t>> uploads;
+    // device copies of the tables (device, memory), see place_tables
+    std::mutex res_mu;
+    std::vector<std::pair<int, void*>> resident[2][2];
     // timing
     int timing = 0;
     struct Ev {
@@ -410,8 +405,7 @@ std::mutex g_dev_mu;
 std::set<int> g_dev_ready;
 size_t g_lds_limit = 65536;
 
-int ensure_device() {
-    int dev = 0;
+int ensure_device(int& dev) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return fail(QL_EHIP, std::string("hipGetDevice: ") + hipGetErrorString(e));
     std::lock_guard<std::mutex> lk(g_dev_mu);
@@ -463,6 +457,7 @@ struct Ctx {
     hipStream_t stream;
     Timer tm;
     bool runs = false;      // the run kernel takes the call
+    const uint8_t* tab = nullptr;  // the plan tables on the device
     bool no_alloc = false;  // make no host or device allocation (no pinned copy, no event)
     // the angle sources of the current circuits (set by bind(); the run
     // kernel binds the angles itself)
@@ -473,38 +468,37 @@ struct Ctx {
     double* phase = nullptr;  // ql_state: factor on every circuit's initial state
 };
 
-int upload_tables(Ctx& x) {
-    if (x.no_alloc) {  // from the handle's own (pageable) copy
-        hipError_t e = hipMemcpyAsync(x.W + x.L.tables, x.T.blob.data(), x.T.blob.size(), hipMemcpyHostToDevice,
-                                      x.stream);
-        return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("table upload: ") + hipGetErrorString(e));
-    }
-    void*& pinned = x.h->pinned[x.dt][x.runs];
-    std::call_once(x.h->pin_once[x.dt][x.runs], [&] {
+// The call's plan tables on the device (x.tab): the handle's own copy, made on
+// the first call on each device and kept until the handle is destroyed; in the
+// workspace, copied on the call's stream, where nothing may be allocated (the
+// allocation-free entry point, a stream being captured) or the allocation
+// fails. (A copy and an event on every call cost 10 us of the smallest calls.)
+int place_tables(Ctx& x, int dev) {
+    const Tables& T = x.T;
+    auto& copies = x.h->resident[x.dt][x.runs];
+    if (!x.no_alloc) {
+        std::lock_guard<std::mutex> lk(x.h->res_mu);
+        for (const auto& r : copies)
+            if (r.first == dev) {
+                x.tab = (const uint8_t*)r.second;
+                return QL_OK;
+            }
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         void* p = nullptr;
-        if (hipHostMalloc(&p, x.T.blob.size(), hipHostMallocDefault) == hipSuccess) {
-            std::memcpy(p, x.T.blob.data(), x.T.blob.size());
-            pinned = p;
-        } else {
-            (void)hipGetLastError();  // keep the pageable copy
+        if (hipStreamIsCapturing(x.stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
+            hipMalloc(&p, T.blob.size()) == hipSuccess) {
+            if (hipMemcpy(p, T.blob.data(), T.blob.size(), hipMemcpyHostToDevice) == hipSuccess) {
+                copies.push_back({dev, p});
+                x.tab = (const uint8_t*)p;
+                return QL_OK;
+            }
+            (void)hipFree(p);
         }
-    });
-    const void* src = pinned ? pinned : (const void*)x.T.blob.data();
-    hipError_t e = hipMemcpyAsync(x.W + x.L.tables, src, x.T.blob.size(), hipMemcpyHostToDevice, x.stream);
-    if (e != hipSuccess) return fail(QL_EHIP, std::string("table upload: ") + hipGetErrorString(e));
-    if (!pinned) return QL_OK;
-    // mark the copy's completion on this stream for ql_circuit_destroy
-    std::lock_guard<std::mutex> lk(x.h->up_mu);
-    hipEvent_t ev = nullptr;
-    for (auto& u : x.h->uploads)
-        if (u.first == x.stream) ev = u.second;
-    if (!ev) {
-        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
-        if (e != hipSuccess) return fail(QL_EHIP, std::string("hipEventCreate: ") + hipGetErrorString(e));
-        x.h->uploads.push_back({x.stream, ev});
+        (void)hipGetLastError();
     }
-    e = hipEventRecord(ev, x.stream);
-    return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("hipEventRecord: ") + hipGetErrorString(e));
+    hipError_t e = hipMemcpyAsync(x.W + x.L.tables, T.blob.data(), T.blob.size(), hipMemcpyHostToDevice, x.stream);
+    x.tab = x.W + x.L.tables;
+    return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("table upload: ") + hipGetErrorString(e));
 }
 
 // Arguments of the product-prefix kernels for B circuits of this call.
@@ -512,9 +506,9 @@ PrefixArgs prefix_args(const Ctx& x, int64_t B) {
     PrefixArgs pa{};
     pa.inputs = x.inputs;
     pa.weights = x.weights;
-    pa.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
-    pa.pre_ptr = (const int32_t*)(x.W + x.L.tables + x.T.off_pptr);
-    pa.pre_ops = (const DevPrefix*)(x.W + x.L.tables + x.T.off_pops);
+    pa.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
+    pa.pre_ptr = (const int32_t*)(x.tab + x.T.off_pptr);
+    pa.pre_ops = (const DevPrefix*)(x.tab + x.T.off_pops);
     pa.phi = (double*)(x.W + x.L.phi);
     pa.lam = x.L.lam ? (const void*)(x.W + x.L.lam) : nullptr;
     pa.envpart = x.L.env ? (double*)(x.W + x.L.env) : nullptr;
@@ -543,7 +537,7 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         BindArgs ba{};
         ba.inputs = inputs;
         ba.weights = weights;
-        ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+        ba.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
         ba.coef = x.W + x.L.coef;
         ba.B = B;
         ba.n_slots = (int)x.c.slots.size();
@@ -557,9 +551,9 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         BindRunsArgs ra{};
         ra.inputs = inputs;
         ra.weights = weights;
-        ra.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
-        ra.runs = (const DevRotRun*)(x.W + x.L.tables + x.T.off_rrun);
-        ra.members = (const DevRotMember*)(x.W + x.L.tables + x.T.off_rmemb);
+        ra.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
+        ra.runs = (const DevRotRun*)(x.tab + x.T.off_rrun);
+        ra.members = (const DevRotMember*)(x.tab + x.T.off_rmemb);
         ra.euler = (double*)(x.W + x.L.euler);
         ra.axes = x.L.axes ? (double*)(x.W + x.L.axes) : nullptr;
         ra.B = B;
@@ -571,15 +565,15 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         BindTileArgs ba{};
         ba.inputs = inputs;
         ba.weights = weights;
-        ba.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+        ba.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
         ba.euler = ra.euler;
         ba.n_runs = ra.n_runs;
-        ba.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
+        ba.ops = (const DevOp*)(x.tab + x.T.off_ops);
         ba.opc = x.W + x.L.opc;
-        ba.diags = (const DevDiag*)(x.W + x.L.tables + x.T.off_diag);
+        ba.diags = (const DevDiag*)(x.tab + x.T.off_diag);
         ba.dzc = x.W + x.L.dzc;
         ba.n_diags = x.T.n_diags;
-        ba.fuses = (const DevFuse*)(x.W + x.L.tables + x.T.off_fuse);
+        ba.fuses = (const DevFuse*)(x.tab + x.T.off_fuse);
         ba.fzc = x.W + x.L.fzc;
         ba.n_fuses = x.T.n_fuses;
         ba.B = B;
@@ -633,7 +627,7 @@ int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, voi
               void* psi_out) {
     const Circuit& c = x.c;
     const RunPlan& rp = x.h->rp;
-    const uint8_t* tab = x.W + x.L.tables;
+    const uint8_t* tab = x.tab;
     RunArgs a{};
     a.steps = (const uint2*)(tab + x.T.off_rstep);
     a.entries = (const DevRunEntry*)(tab + x.T.off_rent);
@@ -697,7 +691,7 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
     auto kept = [&](int p) -> void* { return x.W + x.L.keep + (size_t)p * x.L.state_bytes; };
     if (pl.whole_state) {
         WholeArgs wa{};
-        wa.gates = (const DevGate*)(x.W + x.L.tables + x.T.off_gates);
+        wa.gates = (const DevGate*)(x.tab + x.T.off_gates);
         wa.n_gates = (int)c.gates.size();
         wa.n = c.n;
         wa.n_slots = (int)c.slots.size();
@@ -729,10 +723,10 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         ta.psi = psi_in;
         ta.psi_out = psi_out;
         ta.lam = x.L.lam ? (void*)(x.W + x.L.lam) : nullptr;
-        ta.pass = (const DevPass*)(x.W + x.L.tables + x.T.off_pass) + p;
-        ta.phases = (const DevPhase*)(x.W + x.L.tables + x.T.off_phase);
-        ta.ops = (const DevOp*)(x.W + x.L.tables + x.T.off_ops);
-        ta.gouts = (const DevGradOut*)(x.W + x.L.tables + x.T.off_gslot) + d.gout_base;
+        ta.pass = (const DevPass*)(x.tab + x.T.off_pass) + p;
+        ta.phases = (const DevPhase*)(x.tab + x.T.off_phase);
+        ta.ops = (const DevOp*)(x.tab + x.T.off_ops);
+        ta.gouts = (const DevGradOut*)(x.tab + x.T.off_gslot) + d.gout_base;
         ta.n_gouts = d.n_gouts;
         ta.axes = x.L.axes ? (const double*)(x.W + x.L.axes) : nullptr;
         ta.n_members = x.T.n_rmemb;
@@ -741,8 +735,8 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         ta.n_diags = x.T.n_diags;
         ta.fzc = x.W + x.L.fzc;
         ta.n_fuses = x.T.n_fuses;
-        ta.czg = (const DevCzg*)(x.W + x.L.tables + x.T.off_czg);
-        ta.pthr = (const uint32_t*)(x.W + x.L.tables + x.T.off_pthr);
+        ta.czg = (const DevCzg*)(x.tab + x.T.off_czg);
+        ta.pthr = (const uint32_t*)(x.tab + x.T.off_pthr);
         ta.grad_out = grad_out;
         ta.zpart = zpart;
         ta.gpart = gpart;
@@ -804,11 +798,11 @@ int reduce(Ctx& x, int64_t B, bool grads, void* expz, void* grad_inputs, void* g
     ra.expz = expz;
     ra.grad_inputs = grad_inputs;
     ra.grad_weights = grad_weights;
-    ra.x_ptr = (const int32_t*)(x.W + x.L.tables + x.T.off_xptr);
-    ra.x_slot = (const int32_t*)(x.W + x.L.tables + x.T.off_xslot);
-    ra.w_ptr = (const int32_t*)(x.W + x.L.tables + x.T.off_wptr);
-    ra.w_slot = (const int32_t*)(x.W + x.L.tables + x.T.off_wslot);
-    ra.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+    ra.x_ptr = (const int32_t*)(x.tab + x.T.off_xptr);
+    ra.x_slot = (const int32_t*)(x.tab + x.T.off_xslot);
+    ra.w_ptr = (const int32_t*)(x.tab + x.T.off_wptr);
+    ra.w_slot = (const int32_t*)(x.tab + x.T.off_wslot);
+    ra.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
     ra.B = B;
     ra.n = x.c.n;
     ra.n_wg = x.L.n_wg;
@@ -853,12 +847,13 @@ int run(const ql_circuit* hc, ql_dtype dtype, int64_t B, int mode, const void* i
     if (ws_bytes < L.total)
         return fail(QL_ENOMEM, "workspace too small: need " + std::to_string(L.total) + " bytes, got " +
                                    std::to_string(ws_bytes));
-    rc = ensure_device();
+    int dev = 0;
+    rc = ensure_device(dev);
     if (rc) return rc;
     Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
     x.no_alloc = no_alloc;
     if (no_alloc) x.tm.h = nullptr;  // no timing events either
-    if ((rc = upload_tables(x))) return rc;
+    if ((rc = place_tables(x, dev))) return rc;
     if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
     if (x.runs) {
         if ((rc = run_steps(x, B, bwd, grad_out, expz, grad_inputs, grad_weights, nullptr))) return rc;
@@ -942,10 +937,11 @@ int param_shift(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inp
     if (ws_bytes < S.bytes)
         return fail(QL_ENOMEM, "workspace too small: need " + std::to_string(S.bytes) + " bytes, got " +
                                    std::to_string(ws_bytes));
-    rc = ensure_device();
+    int dev = 0;
+    rc = ensure_device(dev);
     if (rc) return rc;
     Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][S.L.runs], (uint8_t*)ws, S.L, stream, Timer{h, stream}, S.L.runs};
-    if ((rc = upload_tables(x))) return rc;
+    if ((rc = place_tables(x, dev))) return rc;
     const int32_t V = (int32_t)(2 * h->c.n_param_slots + 1);
     void* ev = x.W + S.ev;
     double* dv = (double*)(x.W + S.dv);
@@ -977,11 +973,11 @@ int param_shift(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inp
     ga.dv = dv;
     ga.grad_inputs = grad_inputs;
     ga.grad_weights = grad_weights;
-    ga.x_ptr = (const int32_t*)(x.W + x.L.tables + x.T.off_xptr);
-    ga.x_slot = (const int32_t*)(x.W + x.L.tables + x.T.off_xslot);
-    ga.w_ptr = (const int32_t*)(x.W + x.L.tables + x.T.off_wptr);
-    ga.w_slot = (const int32_t*)(x.W + x.L.tables + x.T.off_wslot);
-    ga.slots = (const SlotSrc*)(x.W + x.L.tables + x.T.off_slots);
+    ga.x_ptr = (const int32_t*)(x.tab + x.T.off_xptr);
+    ga.x_slot = (const int32_t*)(x.tab + x.T.off_xslot);
+    ga.w_ptr = (const int32_t*)(x.tab + x.T.off_wptr);
+    ga.w_slot = (const int32_t*)(x.tab + x.T.off_wslot);
+    ga.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
     ga.B = B;
     ga.vper = V;
     ga.F = h->c.n_inputs;
@@ -1007,10 +1003,11 @@ int state(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inputs, c
     if (ws_bytes < L.total)
         return fail(QL_ENOMEM, "workspace too small: need " + std::to_string(L.total) + " bytes, got " +
                                    std::to_string(ws_bytes));
-    rc = ensure_device();
+    int dev = 0;
+    rc = ensure_device(dev);
     if (rc) return rc;
     Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
-    if ((rc = upload_tables(x))) return rc;
+    if ((rc = place_tables(x, dev))) return rc;
     // the tile path drops global phases: the initial states start with their inverse
     if (!x.runs && !x.pl.whole_state) x.phase = (double*)(x.W + x.L.zpart);
     if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
@@ -1130,15 +1127,10 @@ int ql_circuit_create(int32_t n_qubits, const ql_gate* gates, int32_t n_gates, i
 
 void ql_circuit_destroy(ql_circuit* h) {
     if (!h) return;
-    // table uploads of calls still queued read the pinned copies: wait for
-    // the last one on each stream that made any (not for the whole device)
-    for (auto& u : h->uploads) {
-        (void)hipEventSynchronize(u.second);
-        (void)hipEventDestroy(u.second);
-    }
-    for (auto& d : h->pinned)
-        for (void* p : d)
-            if (p) (void)hipHostFree(p);
+    // (freeing waits for the device, so for every queued call that reads the tables)
+    for (auto& d : h->resident)
+        for (auto& v : d)
+            for (auto& r : v) (void)hipFree(r.second);
     for (auto& e : h->ev) {
         (void)hipEventDestroy(e.a);
         (void)hipEventDestroy(e.b);
@@ -1259,7 +1251,8 @@ int ql_sample(ql_dtype dtype, int32_t n_qubits, int64_t batch, const void* psi, 
         return fail(QL_ENOMEM, "workspace too small: need " + std::to_string(need) + " bytes, got " +
                                    std::to_string(ws_bytes));
     if (batch > ((int64_t)1 << 40) / std::max<int64_t>(shots, 1)) return fail(QL_EINVAL, "batch * shots too large");
-    rc = ensure_device();
+    int dev = 0;
+    rc = ensure_device(dev);
     if (rc) return rc;
     SampleArgs a{};
     a.psi = psi;

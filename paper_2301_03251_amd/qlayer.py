@@ -239,7 +239,16 @@ def _torch():
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _stream(device):
+    """The device's current stream (hipStream_t as an int)."""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)  # no Stream object per call
+    if raw is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(torch.cuda.current_device() if device.index is None else device.index)
 
 
 class Runner:
@@ -312,7 +321,7 @@ class Runner:
         x = inputs if inputs is not None else torch.empty((B, 0), dtype=self.real, device=self.device)
         w = weights if weights is not None else torch.empty(0, dtype=self.real, device=self.device)
         for t in (x, w):
-            if t.dtype != self.real or t.device.type != "cuda" or not t.is_contiguous():
+            if t.dtype != self.real or not t.is_cuda or not t.is_contiguous():
                 raise ValueError("inputs/weights must be contiguous CUDA tensors of the layer's real dtype")
         return x, w
 
@@ -324,7 +333,7 @@ class Runner:
         ws = self.workspace(B, MODE_FWD)
         self.c.forward_raw(self.dtype, B, _ptr(x) if self.c.n_inputs else None,
                            _ptr(w) if self.c.n_weights else None, _ptr(expz), _ptr(ws), ws.numel(),
-                           ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+                           _stream(self.device))
         return expz
 
     def forward_backward(self, inputs, weights, grad_out, want_inputs=True, want_weights=True,
@@ -349,7 +358,7 @@ class Runner:
             self.dtype, B, _ptr(x) if self.c.n_inputs else None, _ptr(w) if self.c.n_weights else None,
             _ptr(grad_out), _ptr(expz), _ptr(gx) if (gx is not None and self.c.n_inputs) else None,
             _ptr(gw) if (gw is not None and self.c.n_weights) else None, _ptr(ws), ws_bytes,
-            ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+            _stream(self.device))
         return expz, gx, gw
 
 
@@ -369,7 +378,7 @@ class Runner:
             self.dtype, B, _ptr(x) if self.c.n_inputs else None, _ptr(w) if self.c.n_weights else None,
             _ptr(grad_out), _ptr(expz), _ptr(gx) if (gx is not None and self.c.n_inputs) else None,
             _ptr(gw) if (gw is not None and self.c.n_weights) else None,
-            ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+            _stream(self.device))
         return expz, gx, gw
 
     def param_shift(self, inputs, weights, grad_out, max_chunk=0, want_inputs=True, want_weights=True,
@@ -395,7 +404,7 @@ class Runner:
             self.dtype, B, _ptr(x) if self.c.n_inputs else None, _ptr(w) if self.c.n_weights else None,
             _ptr(grad_out), _ptr(expz), _ptr(gx) if (gx is not None and self.c.n_inputs) else None,
             _ptr(gw) if (gw is not None and self.c.n_weights) else None, max_chunk, _ptr(ws), ws.numel(),
-            ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+            _stream(self.device))
         return expz, gx, gw
 
 
@@ -411,7 +420,7 @@ class Runner:
             self._ws = torch.empty(max(need, 256), dtype=torch.uint8, device=self.device)
         self.c.state_raw(self.dtype, B, _ptr(x) if self.c.n_inputs else None,
                          _ptr(w) if self.c.n_weights else None, _ptr(psi), _ptr(self._ws),
-                         self._ws.numel(), ctypes.c_void_p(torch.cuda.current_stream(self.device).cuda_stream))
+                         self._ws.numel(), _stream(self.device))
         return psi
 
 
@@ -444,7 +453,7 @@ def sample(psi, uniforms, want_z=True):
     zhat = torch.empty((B, n), dtype=real, device=psi.device) if want_z else None
     ws = torch.empty(max(sample_workspace_bytes(n, B), 256), dtype=torch.uint8, device=psi.device)
     sample_raw(dtype, n, B, _ptr(psi), shots, _ptr(uniforms), _ptr(out), _ptr(zhat), _ptr(ws), ws.numel(),
-               ctypes.c_void_p(torch.cuda.current_stream(psi.device).cuda_stream))
+               _stream(psi.device))
     return out, zhat
 
 
