@@ -267,13 +267,15 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
         int64_t nwg = c.opts.wg_per_sample ? c.opts.wg_per_sample : (8192 + B - 1) / B;
         const int64_t cap = c.opts.wg_per_sample ? tiles : std::max<int64_t>(1, tiles / 2);
         nwg = std::max<int64_t>(1, std::min<int64_t>(nwg, cap));
+        // With few tiles in all each workgroup takes one tile instead of
+        // looping over two on half of the CUs. Backward passes (one tile per
+        // iteration): up to two workgroups per CU (14 qubits, 33 samples, 2
+        // tiles each: step 335 -> 242 us; 20 qubits, complex128, 256 tiles: 509
+        // -> 384; 64 samples of 8 tiles: 434 -> 405; with 1024 tiles it would
+        // cost 5 to 12 %). Forward passes (else two tiles per iteration): up to
+        // one workgroup per CU.
+        if (!c.opts.wg_per_sample && tiles <= 256 / B) nwg = tiles;
         L.n_wg_fwd = (int)nwg;
-        // A backward pass carries one tile per workgroup and iteration: with
-        // at most two workgroups per CU in all, each takes one tile instead of
-        // looping over two on half of the CUs (14 qubits, 33 samples, 2 tiles
-        // each: 335 -> 242 us; 20 qubits, complex128, 256 tiles: 509 -> 384;
-        // 64 samples of 8 tiles: 434 -> 405). With 1024 tiles it would cost
-        // 5 to 12 %. The forward passes keep two tiles per workgroup.
         if (mode != QL_MODE_FWD && !c.opts.wg_per_sample && tiles <= 512 / B) nwg = tiles;
         if (nwg * B > (int64_t)INT32_MAX) return fail(QL_ENOMEM, "grid too large");
         L.n_wg = (int)nwg;

@@ -260,6 +260,14 @@ __device__ __forceinline__ double row_sum(double v) {
     return v;
 }
 
+__device__ __forceinline__ double lane_value(double v, int l) {  // of lane l (uniform)
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    uint2 r;
+    r.x = (uint32_t)__builtin_amdgcn_readlane((int)u.x, l);
+    r.y = (uint32_t)__builtin_amdgcn_readlane((int)u.y, l);
+    return __builtin_bit_cast(double, r);
+}
+
 // ---------------------------------------------------------------------------
 // products of one-qubit gates in fp64
 

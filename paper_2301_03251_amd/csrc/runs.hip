@@ -216,18 +216,28 @@ __device__ __forceinline__ int row_bit(int pos, int sid) {
     return (sid >> b) & 1;
 }
 
-// The wavefront's gradient sums of one run into its words of the table.
+// The wavefront's gradient sums of one run into its words of the table. The
+// three sums share the first two levels of the reduction: a permlane swap of
+// two of them leaves one's halves in the lower lanes and the other's in the
+// upper, so one add folds both (10 instructions in fp32, 21 in fp64, against
+// 18 and 54 for three reductions of their own). Rows 0, 1, 2 end with X, Z, Y.
 template <bool REAL, typename Real>
 __device__ __forceinline__ void store_sums(Real* o, Real sx, Real sy, Real sz, int lane) {
-    sy = wave_to_last(sy);
-    if constexpr (!REAL) {
-        sx = wave_to_last(sx);
-        sz = wave_to_last(sz);
-    }
-    if (lane == 63) {
-        o[0] = sx;
-        o[1] = sy;
-        o[2] = sz;
+    if constexpr (REAL) {
+        sy = wave_to_last(sy);
+        if (lane == 63) {
+            o[0] = (Real)0;
+            o[1] = sy;
+            o[2] = (Real)0;
+        }
+    } else {
+        swap_real<5>(sx, sy);
+        Real u = sx + sy, v = sz;  // lower half: X, upper half: Y
+        swap_real<5>(sz, v);
+        v += sz;
+        swap_real<4>(u, v);
+        u = row_sum(u + v);
+        if ((lane & 15) == 0 && lane < 48) o[lane == 0 ? 0 : lane == 16 ? 2 : 1] = u;
     }
 }
 

@@ -1086,7 +1086,7 @@ static hipError_t launch_tile_t(bool bwd, const TileArgs& a, int threads, size_t
     if (bwd)
         hipLaunchKernelGGL((k_tile<Real, LOG_R, KM_BWD, MAXT>), grid, dim3(threads), lds, s, a, a.pass,
                            a.phases, xo, gout, a.gouts, dzt, fzt);
-    else if (a.tiles >= 2)  // forward passes carry two tiles per iteration when there are two
+    else if (a.n_wg < a.tiles)  // forward passes carry two tiles per iteration, unless each workgroup has one
         hipLaunchKernelGGL((k_tile<Real, LOG_R, KM_FWD2, MAXT>), grid, dim3(threads), lds, s, a, a.pass,
                            a.phases, xo, gout, a.gouts, dzt, fzt);
     else
