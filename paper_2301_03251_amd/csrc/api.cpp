@@ -200,7 +200,7 @@ bool mul_ok(size_t a, size_t b, size_t& out) {
 
 struct ql_circuit {
     Circuit c;
-    RunPlan rp;
+    RunPlan rp[2];         // per dtype
     bool runs[2][2] = {};  // [dtype][with a backward]: the run kernel can take the call
     Tables t[2][2];        // [dtype][0: tile or whole-state plan, 1: run plan]
     // device copies of the tables (device, memory), see place_tables
@@ -221,23 +221,26 @@ namespace {
 // Whether the run kernel takes a call. Below 32 KiB of state per sample (n <=
 // 10, and 11 in complex64) it is faster at every batch (1.0 to 3.4 times the
 // tile kernel; circuits of 4 layers, batches of 256 to 30000). Larger states
-// have fewer passes over the matrices' 8 FMAs per amplitude hidden behind
-// anything: with every wavefront slot taken once (256 CUs of 1024 threads) the
-// run kernel still wins, beyond that the tile kernel's 3 FMAs per rotation do.
-// Training step, tile / run kernel: 12 qubits complex64, 256 samples 150 / 104
-// us, 300 samples of a random circuit 219 / 266 us; 11 qubits complex128, 512
-// samples 183 / 173 us, 1000 samples 251 / 312 us. Forward only, four rounds
-// (32 KiB): 12 qubits complex64, 1000 samples 128 / 115 us, 2000 samples 183 /
-// 201 us; 11 qubits complex128, 2000 samples 146 / 145 us. 12 qubits complex128
-// forward: 512 samples 72 / 78 us.
+// fill the chip with fewer samples, and from there on the tile kernel's 3 FMAs
+// per RY cost less than a matrix's 8. Tile / run kernel, us, for the circuits
+// of layers that the run kernel gains least on: complex64, 12 qubits, forward
+// of 2000 samples 141 (noise) / 144, of 1000 93 / 74, step of 512 193 / 154, of 700
+// (noise) 181 / 216; complex128, 11 qubits, forward of 512 samples 101 / 88,
+// of 2000 145 / 170, step of 512 181 / 132, of 700 (noise) 167 / 179; 12
+// qubits, forward of 768 samples (noise) 102 / 99, of 2000 247 / 262. Runs
+// under controls take a step each, a layer's runs share one, so circuits with
+// such runs turn earlier (400 random gates): complex64, forward of 512 samples
+// 239 / 239, of 768 297 / 353, step of 256 459 / 453, of 700 (150 gates) 343 /
+// 447; complex128, 11 qubits, forward of 512 250 / 218, of 768 276 / 318, step
+// of 256 511 / 485, of 700 (150 gates) 299 / 413; 12 qubits, forward of 512
+// 295 / 333, step of 256 622 / 613.
 bool runs_take(const ql_circuit* h, int dt, int64_t B, int mode) {
     const bool bwd = mode != QL_MODE_FWD;
-    const int n = h->c.n;
     if (!h->runs[dt][bwd]) return false;
-    const int64_t state = (int64_t)(dt == 0 ? 8 : 16) << n;
-    if (state < 32768) return true;
-    const int64_t round = ((int64_t)256 * 1024) >> (n - 2);  // workgroups of 2^(n-2) threads
-    return B <= (!bwd && state == 32768 ? 4 * round : round);
+    const int64_t bytes = (int64_t)(dt == 0 ? 8 : 16) << h->c.n;
+    if (bytes < 32768) return true;
+    if (h->rp[dt].controlled) return B <= (bwd || bytes > 32768 ? 256 : 512);
+    return B <= (bwd ? 512 : dt == 1 ? 768 : 1536);
 }
 
 // own_psi = false: the caller's state buffer holds psi (ql_state), so the
@@ -628,7 +631,7 @@ int embed(Ctx& x, int64_t B, const void* inputs, void* psi, int64_t v0, int32_t 
 int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, void* grad_inputs, void* grad_weights,
               void* psi_out) {
     const Circuit& c = x.c;
-    const RunPlan& rp = x.h->rp;
+    const RunPlan& rp = x.h->rp[x.dt];
     const uint8_t* tab = x.tab;
     RunArgs a{};
     a.steps = (const uint2*)(tab + x.T.off_rstep);
@@ -1066,11 +1069,13 @@ void choose_runs(ql_circuit* h) {
     const bool plain = !o.log_regs && !o.log_threads && !o.low_qubits && !o.max_gates_per_pass && !o.force_tiled &&
                        !o.wg_per_sample && !o.rz_groups && !o.pass_search && !o.product_prefix && !o.cz_groups;
     if (c.n > RUNS_MAX_QUBITS || (c.n >= 8 && !plain)) return;
-    build_run_plan(c, h->rp);
-    if (!h->rp.ok) return;
-    for (int dt = 0; dt < 2; dt++)
+    for (int dt = 0; dt < 2; dt++) {
+        if (dt == 1 && runs_log_regs(c.n, 0) == runs_log_regs(c.n, 1)) h->rp[1] = h->rp[0];
+        else build_run_plan(c, runs_log_regs(c.n, dt), h->rp[dt]);
+        if (!h->rp[dt].ok) continue;
         for (int bwd = 0; bwd < 2; bwd++)
-            h->runs[dt][bwd] = runs_lds(dt, h->rp, (int)c.slots.size(), bwd != 0).total <= RUNS_LDS_MAX;
+            h->runs[dt][bwd] = runs_lds(dt, h->rp[dt], (int)c.slots.size(), bwd != 0).total <= RUNS_LDS_MAX;
+    }
 }
 
 }  // namespace
@@ -1101,7 +1106,7 @@ int ql_circuit_create_desc(int32_t n_qubits, const ql_gate* gates, int32_t n_gat
             choose_runs(h);
             for (int dt = 0; dt < 2; dt++) {
                 build_tables(h->c, dt, nullptr, h->t[dt][0]);
-                if (h->runs[dt][0]) build_tables(h->c, dt, &h->rp, h->t[dt][1]);
+                if (h->runs[dt][0]) build_tables(h->c, dt, &h->rp[dt], h->t[dt][1]);
             }
         }
     } catch (const std::bad_alloc&) {

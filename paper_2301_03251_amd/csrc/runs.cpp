@@ -249,6 +249,7 @@ struct Planner {
             e.mat = (uint32_t)p.n_mat;
             p.n_mat += 8;
             e.grad = (uint32_t)p.n_grads++;
+            p.controlled = true;
             p.steps.push_back({RS_CRUN + (uint32_t)at[q], e.mat, (uint32_t)(at[ctl] - p.log_r), e.grad});
         } else if (c.embed == E_NONE && !(touched & qs) && p.n_exchanges == 0) {
             p.prefix |= bit;
@@ -368,11 +369,11 @@ struct Planner {
 
 }  // namespace
 
-void build_run_plan(const Circuit& c, RunPlan& out) {
+void build_run_plan(const Circuit& c, int log_r, RunPlan& out) {
     out = RunPlan{};
     if (c.n > RUNS_MAX_QUBITS || c.gates.size() > (1u << 14)) return;
     out.n = c.n;
-    out.log_r = c.n <= 6 ? 0 : c.n == 7 ? 1 : 2;
+    out.log_r = log_r;
     out.log_t = c.n - out.log_r;
     out.n_waves = out.log_t > 6 ? 1 << (out.log_t - 6) : 1;
     Planner(c, out).run();

@@ -442,13 +442,13 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
                                               sx, sy, sz);                                        \
             if constexpr (MODE != RUN_FWD) {                                                      \
                 if (!((sid >> (cur.y & 31u)) & 1)) sx = sy = sz = 0; /* the control's 1 half */   \
-                store_sums<false>(my_sums + (cur.y >> 8) * sum_stride, sx, sy, sz, lane);                \
+                store_sums<false>(my_sums + (cur.y >> 9) * sum_stride, sx, sy, sz, lane);                \
             }                                                                                     \
         }                                                                                         \
         break;
 #define QL_CRUN_CASES(MODE)                                                                       \
     QL_CRUN_CASE(0, MODE) QL_CRUN_CASE(1, MODE) QL_CRUN_CASE(2, MODE) QL_CRUN_CASE(3, MODE)        \
-    QL_CRUN_CASE(4, MODE) QL_CRUN_CASE(5, MODE) QL_CRUN_CASE(6, MODE) QL_CRUN_CASE(7, MODE)
+    QL_CRUN_CASE(4, MODE) QL_CRUN_CASE(5, MODE) QL_CRUN_CASE(6, MODE) QL_CRUN_CASE(7, MODE) QL_CRUN_CASE(8, MODE)
     for (int c0 = 0; c0 < a.n_steps; c0 += 64) {
         if (c0 > 0) rec = steps[min(c0 + lane, a.n_steps)];
         const int cnt = min(64, a.n_steps - c0);
@@ -458,13 +458,13 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
                 QL_CRUN_CASES(RUN_FWD)
                 case RS_LAYER_REAL: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_FWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                    layer<LOG_R, RUN_FWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0x1ffu,
                                                              load_rows(base, row_bit<LOG_R>(0, sid)), (Real*)nullptr, 0,
                                                              sid, lane);
                 } break;
                 case RS_LAYER: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_FWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                    layer<LOG_R, RUN_FWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0x1ffu,
                                                               load_rows(base, row_bit<LOG_R>(0, sid)), (Real*)nullptr, 0,
                                                               sid, lane);
                 } break;
@@ -562,15 +562,15 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
                 QL_CRUN_CASES(RUN_BWD)
                 case RS_LAYER_REAL: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_BWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                    layer<LOG_R, RUN_BWD, 0, true, T2, Real>(ps, lm, base, cur.y & 0x1ffu,
                                                              load_rows(base, row_bit<LOG_R>(0, sid)),
-                                                             my_sums + (cur.y >> 8) * sum_stride, sum_stride, sid, lane);
+                                                             my_sums + (cur.y >> 9) * sum_stride, sum_stride, sid, lane);
                 } break;
                 case RS_LAYER: {
                     const T2* base = mat + cur.mat;
-                    layer<LOG_R, RUN_BWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0xffu,
+                    layer<LOG_R, RUN_BWD, 0, false, T2, Real>(ps, lm, base, cur.y & 0x1ffu,
                                                               load_rows(base, row_bit<LOG_R>(0, sid)),
-                                                              my_sums + (cur.y >> 8) * sum_stride, sum_stride, sid, lane);
+                                                              my_sums + (cur.y >> 9) * sum_stride, sum_stride, sid, lane);
                 } break;
                 case RS_SIGN: {
                     const uint32_t m = signs_of(cur.mat);
@@ -706,7 +706,7 @@ RunLds runs_lds(int dtype, const RunPlan& p, int n_slots, bool bwd) {
         off = at + bytes;
         return (uint32_t)at;
     };
-    l.mat = put((size_t)(p.n_mat + 4 * 8) * amp);  // a layer fetches the rows of all 8 positions
+    l.mat = put((size_t)(p.n_mat + 4 * 9) * amp);  // a layer fetches the rows of all 9 positions
     l.cs = put((size_t)p.n_cs * 16);
     l.kind = put(p.members.size());
     l.words = put(p.words.size() * 4);
@@ -727,10 +727,12 @@ static hipError_t launch_runs_t(int log_r, const RunArgs& a, int threads, hipStr
         if (log_r == 0) QL_LR(0, 64);
         else if (log_r == 1) QL_LR(1, 64);
         else QL_LR(2, 64);
+    } else if (log_r == 3 && threads <= 512) {  // 11 (complex128) and 12 qubits
+        QL_LR(3, 512);
     } else if (log_r == 2 && threads <= 256) {
         QL_LR(2, 256);
-    } else if (log_r == 2 && threads <= 1024) {
-        QL_LR(2, 1024);
+    } else if (log_r == 2 && threads <= 512) {
+        QL_LR(2, 512);
     } else {
         return hipErrorInvalidValue;
     }
@@ -748,7 +750,7 @@ hipError_t configure_runs_kernels(size_t max_lds) {
     if (e == hipSuccess)                                                                                 \
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_runs<REAL, LR, MT>),                     \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
-#define QL_ATS(REAL) QL_AT(REAL, 0, 64) QL_AT(REAL, 1, 64) QL_AT(REAL, 2, 64) QL_AT(REAL, 2, 256) QL_AT(REAL, 2, 1024)
+#define QL_ATS(REAL) QL_AT(REAL, 0, 64) QL_AT(REAL, 1, 64) QL_AT(REAL, 2, 64) QL_AT(REAL, 2, 256) QL_AT(REAL, 2, 512) QL_AT(REAL, 3, 512)
     QL_ATS(float)
     QL_ATS(double)
 #undef QL_ATS

@@ -38,7 +38,7 @@ enum RunOp : uint32_t {
 };
 
 constexpr uint32_t RUNS_NONE = 0xffffffffu;
-// Most qubits of a plan: 2^12 amplitudes as 4 registers of 1024 threads.
+// Most qubits of a plan: 2^12 amplitudes as 8 registers of 512 threads.
 constexpr int RUNS_MAX_QUBITS = 12;
 // Most words of the tables (they are held in LDS).
 constexpr size_t RUNS_MAX_WORDS = 12288;
@@ -77,12 +77,12 @@ struct DevRunMember {
 };
 
 // A step as the kernel reads it: op | mat << 8, and for a run or layer ctl |
-// grad << 8, for an exchange its sign table + 1 (0: no signs).
+// grad << 9, for an exchange its sign table + 1 (0: no signs).
 struct RunRecord {
     uint32_t x, y;
 };
 constexpr RunRecord run_record(const DevRunStep& s) {
-    return {s.op | s.mat << 8, s.op < RS_EXCHANGE ? s.ctl | s.grad << 8 : s.op == RS_EXCHANGE ? s.ctl + 1u : 0u};
+    return {s.op | s.mat << 8, s.op < RS_EXCHANGE ? s.ctl | s.grad << 9 : s.op == RS_EXCHANGE ? s.ctl + 1u : 0u};
 }
 
 struct RunPlan {
@@ -105,13 +105,24 @@ struct RunPlan {
     int n_cs = 0;                          // (cos, sin) pairs
     int n_grads = 0;                       // gradient sums (three each)
     int n_exchanges = 0;
+    bool controlled = false;               // has runs under a control
 };
 
 // Bank-spreading permutation of the exchange slots, linear over GF(2): folds
 // the higher bits into the lowest four.
 constexpr uint32_t runs_bank(uint32_t s) { return s ^ (((s >> 4) ^ (s >> 8)) & 15u); }
 
-// Plan a circuit of at most RUNS_MAX_QUBITS qubits (ok = false: too long).
-void build_run_plan(const Circuit& c, RunPlan& out);
+// Register bits of a plan: one wavefront while 4 registers hold the state (n
+// <= 8), 4 registers up to 11 qubits, 8 where workgroups get large: 12 qubits
+// (1024 threads left room for one workgroup per CU: 1000 samples forward,
+// complex64, 90 against 74 us) and 11 in complex128 (64 against 57 us; in
+// complex64 4 registers step 45 against 49 us at 37 samples).
+constexpr int runs_log_regs(int n, int dtype) {
+    return n <= 6 ? 0 : n == 7 ? 1 : n <= 10 || (n == 11 && dtype == 0) ? 2 : 3;
+}
+
+// Plan a circuit of at most RUNS_MAX_QUBITS qubits for 2^log_r registers (ok =
+// false: too long).
+void build_run_plan(const Circuit& c, int log_r, RunPlan& out);
 
 }  // namespace qlayer

@@ -207,11 +207,14 @@ int main(int argc, char** argv) {
             std::printf("case %d: %s\n", n_cases, err.c_str());
             return 4;
         }
-        RunPlan p;
-        build_run_plan(c, p);
-        if (!p.ok) return fail(n_cases, "no plan");
         const long x0 = exchanges, r0 = runs;
-        if (check(n_cases, c, p, exchanges, runs)) return 5;
+        RunPlan p;
+        for (int dt = 1; dt >= 0; dt--) {
+            if (dt == 1 && runs_log_regs(c.n, 0) == runs_log_regs(c.n, 1)) continue;
+            build_run_plan(c, runs_log_regs(c.n, dt), p);
+            if (!p.ok) return fail(n_cases, "no plan");
+            if (check(n_cases, c, p, exchanges, runs)) return 5;
+        }
         if (argc > 2)
             std::printf("case %d: n %d gates %d: %ld exchanges, %ld runs, %d prefix, %zu words, %zu steps\n", n_cases, hdr[0], hdr[1],
                         (exchanges - x0) / 2, (runs - r0) / 2, __builtin_popcount(p.prefix), p.words.size(), p.steps.size());

@@ -111,12 +111,13 @@ def test_param_shift(n, dtype):
     check(got, oracle.run(n, gates, x, w, grad_out=g), TOL[dtype], f"shift n={n} {dtype}")
 
 
-@pytest.mark.parametrize("n,dtype,limit", [(11, "c128", 512), (12, "c64", 256)])
-def test_batch_rule(n, dtype, limit):
+@pytest.mark.parametrize("n,dtype,limit,circuit", [(11, "c128", 256, "random"), (12, "c64", 256, "random"),
+                                                   (11, "c128", 512, "layers"), (12, "c64", 512, "layers")])
+def test_batch_rule(n, dtype, limit, circuit):
     """On both sides of the batch from which the tile kernel takes the step:
     the rows of the smaller batch agree, and the last row with the oracle."""
     F, P = 3, 4
-    gates = W.random_circuit(n, 40, F, P, seed=n)
+    gates = W.random_circuit(n, 40, F, P, seed=n) if circuit == "random" else run_layers(n, 2, F, P, seed=n)
     x, w, g = W.random_inputs(limit + 1, F, P, n, seed=n, dtype=dtype)
     r = Q.Runner(Q.Circuit(n, gates, F, P), dtype)
     big, small = _fb(r, dtype, x, w, g), _fb(r, dtype, x[:limit], w, g[:limit])
