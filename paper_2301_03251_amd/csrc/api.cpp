@@ -224,7 +224,7 @@ namespace {
 // fill the chip with fewer samples, and from there on the tile kernel's 3 FMAs
 // per RY cost less than a matrix's 8. Tile / run kernel, us, for the circuits
 // of layers that the run kernel gains least on: complex64, 12 qubits, forward
-// of 2000 samples 141 (noise) / 144, of 1000 93 / 74, step of 512 193 / 154, of 700
+// of 2000 samples 141 (noise) / 144, of 1000 95 / 58, step of 512 193 / 154, of 700
 // (noise) 181 / 216; complex128, 11 qubits, forward of 512 samples 101 / 88,
 // of 2000 145 / 170, step of 512 181 / 132, of 700 (noise) 167 / 179; 12
 // qubits, forward of 768 samples (noise) 102 / 99, of 2000 247 / 262. Runs

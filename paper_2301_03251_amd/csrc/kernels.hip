@@ -536,8 +536,8 @@ __device__ __forceinline__ double2 zmul(double2 a, double2 b) {
 }
 
 // v <- G v for prefix gate kind k with angle t (G = exp(-i t P / 2) for RX,
-// RY, RZ; the Hadamard for H); inv applies G^dagger.
-__device__ __forceinline__ void apply_gate1(int kind, double t, bool inv, double2& v0, double2& v1) {
+// RY, RZ; the Hadamard for H).
+__device__ __forceinline__ void apply_gate1(int kind, double t, double2& v0, double2& v1) {
     if (kind == K_H) {
         const double r = 0.70710678118654752440;
         const double2 a = v0, b = v1;
@@ -545,7 +545,6 @@ __device__ __forceinline__ void apply_gate1(int kind, double t, bool inv, double
         v1 = make_double2(r * (a.x - b.x), r * (a.y - b.y));
         return;
     }
-    if (inv) t = -t;
     double s, c;
     sincos(0.5 * t, &s, &c);
     const double2 a = v0, b = v1;
@@ -577,7 +576,7 @@ __global__ void __launch_bounds__(256) k_bind_prefix(const PrefixArgs a) {
             th = angle_of<Real>(a.inputs, a.weights, a.F, a.slots[g.slot], b, a.v0, a.vper, bs) +
                  shift_of(b, a.v0, a.vper, g.slot);
         }
-        apply_gate1(g.kind, th, false, v0, v1);
+        apply_gate1(g.kind, th, v0, v1);
     }
     if (a.phase && q == 0) {  // the state's global phase, on one qubit's factor
         const double2 f = make_double2(a.phase[2 * b], a.phase[2 * b + 1]);
