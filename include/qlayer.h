@@ -34,12 +34,15 @@
  * Memory: all array arguments of ql_forward / ql_forward_backward are DEVICE
  * pointers on the current HIP device, row-major and contiguous, owned by the
  * caller. The caller also provides the device workspace (size from
- * ql_workspace_bytes). The library never allocates device memory in these
- * calls; it only writes the workspace and the outputs. (The first call of
- * each dtype on a handle makes a pinned host copy of the handle's plan tables,
- * which later calls upload by DMA; ql_circuit_destroy waits, through an event
- * per stream that uploaded from it, for the last such upload on each of those
- * streams before freeing it.) Outputs are
+ * ql_workspace_bytes). The library writes only the workspace and the outputs.
+ * It allocates device memory in one place: the first call of a dtype on a
+ * handle and device makes a device copy of the handle's plan tables (some KiB),
+ * which later calls read and ql_circuit_destroy frees. Where nothing may be
+ * allocated (a stream in capture, ql_forward_backward_static), where that
+ * allocation fails, or where the stream belongs to another device than the
+ * current one, the call copies the tables to the workspace instead. A graph
+ * captured from calls on a handle reads the handle's tables when it is
+ * replayed: keep the handle until the last replay has ended. Outputs are
  * overwritten (not accumulated). Buffers must not alias each other or the
  * workspace.
  *
@@ -216,9 +219,8 @@ int ql_circuit_create_desc(int32_t n_qubits, const ql_gate* gates, int32_t n_gat
                            int32_t n_inputs, int32_t n_weights, const ql_circuit_desc* desc,
                            const ql_options* opts, ql_circuit** out);
 
-/* Free a handle (NULL is a no-op). Waits only for the queued table uploads
- * of calls made with it (an event per stream that made any), not for other
- * work on the device. The handle must not be used afterwards. */
+/* Free a handle (NULL is a no-op). Freeing its plan tables waits for the queued
+ * work of the devices it ran on. The handle must not be used afterwards. */
 void ql_circuit_destroy(ql_circuit* c);
 
 /* Bytes of device workspace a call with this dtype, batch and mode

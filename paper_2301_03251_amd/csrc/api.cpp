@@ -463,7 +463,7 @@ struct Ctx {
     Timer tm;
     bool runs = false;      // the run kernel takes the call
     const uint8_t* tab = nullptr;  // the plan tables on the device
-    bool no_alloc = false;  // make no host or device allocation (no pinned copy, no event)
+    bool no_alloc = false;  // make no allocation (the tables go to the workspace)
     // the angle sources of the current circuits (set by bind(); the run
     // kernel binds the angles itself)
     const void* inputs = nullptr;
@@ -476,12 +476,18 @@ struct Ctx {
 // The call's plan tables on the device (x.tab): the handle's own copy, made on
 // the first call on each device and kept until the handle is destroyed; in the
 // workspace, copied on the call's stream, where nothing may be allocated (the
-// allocation-free entry point, a stream being captured) or the allocation
-// fails. (A copy and an event on every call cost 10 us of the smallest calls.)
+// allocation-free entry point, a stream being captured), the stream belongs to
+// another device than the current one or the allocation fails. (A copy and an
+// event on every call cost 10 us of the smallest calls.)
 int place_tables(Ctx& x, int dev) {
     const Tables& T = x.T;
     auto& copies = x.h->resident[x.dt][x.runs];
-    if (!x.no_alloc) {
+    hipDevice_t at = dev;  // a null stream is the current device's
+    if (x.stream && hipStreamGetDevice(x.stream, &at) != hipSuccess) {
+        (void)hipGetLastError();
+        at = -1;
+    }
+    if (!x.no_alloc && at == dev) {
         std::lock_guard<std::mutex> lk(x.h->res_mu);
         for (const auto& r : copies)
             if (r.first == dev) {
