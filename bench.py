@@ -250,8 +250,8 @@ def main():
     timing = not args.no_timing
     # events around the dominant kernel's launches only: each event pair costs
     # host time, which would show in the step time of launch-bound workloads
-    dominant = 1 if circ.plan_info(wl.dtype)["kernel"] == 1 else 2
-    circ.timing(timing, dominant)
+    # (tile passes, or the run or whole-state kernel: a call launches one of the two classes)
+    circ.timing(timing, 3)
     start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     torch.cuda.synchronize()
     start.record()
@@ -354,7 +354,9 @@ def main():
         alu = (shift_flops(gates, wl.batch, wl.n) if shift else
                algorithmic_flops(gates, wl.batch, wl.n)) / (whole_ms / 1e3) / 1e12
         peak = ALU_PEAK_TFLOPS[wl.dtype]
-        line["roofline"] = {"bound": "alu", "kernel": "k_whole", "achieved": alu,
+        # planner options describe tile plans: with any, 8 and more qubits do not take the run kernel
+        kernel = "k_whole" if opts and wl.n >= 8 else "k_runs"
+        line["roofline"] = {"bound": "alu", "kernel": kernel, "achieved": alu,
                             "peak": peak, "unit": "TFLOP/s", "frac": alu / peak,
                             "traffic": None, "kernel_ms_per_step": whole_ms,
                             "issue_peak": ISSUE_PEAK_TFLOPS, "frac_of_issue_peak": alu / ISSUE_PEAK_TFLOPS}
