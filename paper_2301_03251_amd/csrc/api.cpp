@@ -60,10 +60,8 @@ size_t put(std::vector<uint8_t>& blob, const std::vector<T>& v) {
     return off;
 }
 
-// Tables of a circuit that the run kernel takes (rp), or of its tile or
-// whole-state plan.
-void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
-    const Plan& pl = c.plan[dt];
+// Tables of a tile or whole-state plan, or of a run plan (rp).
+void build_tables(const Circuit& c, int dt, const Plan& pl, const RunPlan* rp, Tables& T) {
     std::vector<DevPass> passes;
     std::vector<DevOp> ops;
     std::vector<DevGradOut> gouts;
@@ -178,6 +176,13 @@ void build_tables(const Circuit& c, int dt, const RunPlan* rp, Tables& T) {
 // The run kernel's LDS budget (gfx950 has 160 KiB per CU).
 constexpr size_t RUNS_LDS_MAX = 160 * 1024;
 
+// Which plan and kernels take a call.
+enum Route {
+    TILE = 0,   // the handle's tile or whole-state plan
+    RUNS = 1,   // the run kernel
+    PLAIN = 2,  // the tile plan without rotation runs
+};
+
 struct Layout {
     size_t tables = 0, coef = 0, opc = 0, dzc = 0, fzc = 0, euler = 0, axes = 0, zpart = 0, gpart = 0, psi = 0, lam = 0, total = 0;
     size_t enorm = 0, edot = 0;  // embedding: per-circuit |x| or basis index; L_b
@@ -187,7 +192,7 @@ struct Layout {
     int n_keep = 0;
     int n_wg = 1;
     int n_wg_fwd = 1;            // workgroups per sample of the forward passes before the last
-    bool runs = false;           // the run kernel takes the call
+    int route = TILE;
 };
 
 bool mul_ok(size_t a, size_t b, size_t& out) {
@@ -202,10 +207,10 @@ struct ql_circuit {
     Circuit c;
     RunPlan rp[2];         // per dtype
     bool runs[2][2] = {};  // [dtype][with a backward]: the run kernel can take the call
-    Tables t[2][2];        // [dtype][0: tile or whole-state plan, 1: run plan]
+    Tables t[2][3];        // [dtype][Route]
     // device copies of the tables (device, memory), see place_tables
     std::mutex res_mu;
-    std::vector<std::pair<int, void*>> resident[2][2];
+    std::vector<std::pair<int, void*>> resident[2][3];
     // timing
     int timing = 0;
     struct Ev {
@@ -243,20 +248,33 @@ bool runs_take(const ql_circuit* h, int dt, int64_t B, int mode) {
     return B <= (bwd ? 512 : dt == 1 ? 768 : 1536);
 }
 
+// The kernels of a call. Final states (psi_out) of complex64 take those that
+// join no rotations: shots are whole numbers drawn by the states' bits (runs of
+// gates as one matrix, or as three rotations, move about 2e-4 of 1000 shots of
+// 16 qubits to the next index), so a state's rounding is kept.
+int route_of(const ql_circuit* h, int dt, int64_t B, int mode, bool psi_out) {
+    if (psi_out && dt == 0) return h->c.plain[dt].passes.empty() ? TILE : PLAIN;
+    return runs_take(h, dt, B, mode) ? RUNS : TILE;
+}
+const Plan& plan_of(const ql_circuit* h, int dt, int route) {
+    return route == PLAIN ? h->c.plain[dt] : h->c.plan[dt];
+}
+
 // own_psi = false: the caller's state buffer holds psi (ql_state), so the
 // workspace has none.
 int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, bool own_psi = true) {
     const Circuit& c = h->c;
-    const Plan& pl = c.plan[dt];
+    const int route = route_of(h, dt, B, mode, !own_psi);
+    const Plan& pl = plan_of(h, dt, route);
     const size_t amp = dt == 0 ? 8 : 16;
     if (B < 1) return fail(QL_EINVAL, "batch must be >= 1");
     if (B > (int64_t)1 << 30) return fail(QL_EINVAL, "batch too large");
     const int maxq = dt == 0 ? QL_MAX_QUBITS_C64 : QL_MAX_QUBITS_C128;
     if (c.n > maxq) return fail(QL_EUNSUPPORTED, "too many qubits for this dtype");
     L = Layout{};
-    const bool runs = runs_take(h, dt, B, mode), one = runs || pl.whole_state;  // one workgroup per sample, state on chip
-    const Tables& T = h->t[dt][runs];
-    L.runs = runs;
+    const bool runs = route == RUNS, one = runs || pl.whole_state;  // one workgroup per sample, state on chip
+    const Tables& T = h->t[dt][route];
+    L.route = route;
     if (one) {
         L.n_wg = 1;
     } else {
@@ -318,7 +336,7 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     L.zpart = off;
     if (!mul_ok((size_t)B * (size_t)L.n_wg, (size_t)c.n * 8, sz)) return fail(QL_ENOMEM, "size overflow");
     off = align256(off + sz);
-    if ((pl.product || !own_psi) && !one) {
+    if (pl.product && !one) {
         // per circuit and qubit the prefix factor (phi(0), phi(1)), complex fp64
         L.phi = off;
         if (!mul_ok((size_t)B, (size_t)c.n * 32, sz)) return fail(QL_ENOMEM, "size overflow");
@@ -470,8 +488,12 @@ struct Ctx {
     const void* weights = nullptr;
     int64_t v0 = 0;
     int32_t vper = 0;
-    double* phase = nullptr;  // ql_state: factor on every circuit's initial state
 };
+
+Ctx context(ql_circuit* h, int dt, const Layout& L, void* ws, hipStream_t stream) {
+    return {h, dt, h->c, plan_of(h, dt, L.route), h->t[dt][L.route], (uint8_t*)ws, L, stream, Timer{h, stream},
+            L.route == RUNS};
+}
 
 // The call's plan tables on the device (x.tab): the handle's own copy, made on
 // the first call on each device and kept until the handle is destroyed; in the
@@ -481,7 +503,7 @@ struct Ctx {
 // event on every call cost 10 us of the smallest calls.)
 int place_tables(Ctx& x, int dev) {
     const Tables& T = x.T;
-    auto& copies = x.h->resident[x.dt][x.runs];
+    auto& copies = x.h->resident[x.dt][x.L.route];
     hipDevice_t at = dev;  // a null stream is the current device's
     if (x.stream && hipStreamGetDevice(x.stream, &at) != hipSuccess) {
         (void)hipGetLastError();
@@ -529,8 +551,33 @@ PrefixArgs prefix_args(const Ctx& x, int64_t B) {
     pa.F = x.c.n_inputs;
     pa.n_wg = x.L.n_wg;
     pa.env_wg = env_workgroups(x.dt, x.c.n, B);
-    pa.phase = x.phase;
     return pa;
+}
+
+// Arguments of the tile ops' binding for B circuits of this call.
+BindTileArgs tile_binding(const Ctx& x, int64_t B) {
+    BindTileArgs ba{};
+    ba.inputs = x.inputs;
+    ba.weights = x.weights;
+    ba.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
+    ba.euler = (const double*)(x.W + x.L.euler);
+    ba.n_runs = x.T.n_runs;
+    ba.ops = (const DevOp*)(x.tab + x.T.off_ops);
+    ba.opc = x.W + x.L.opc;
+    ba.diags = (const DevDiag*)(x.tab + x.T.off_diag);
+    ba.dzc = x.W + x.L.dzc;
+    ba.n_diags = x.T.n_diags;
+    ba.fuses = (const DevFuse*)(x.tab + x.T.off_fuse);
+    ba.fzc = x.W + x.L.fzc;
+    ba.n_fuses = x.T.n_fuses;
+    ba.B = B;
+    ba.n_ops = x.T.n_ops;
+    ba.bwd_first = x.T.bwd_first;
+    ba.bwd = x.L.gpart ? 1 : 0;
+    ba.F = x.c.n_inputs;
+    ba.v0 = x.v0;
+    ba.vper = x.vper;
+    return ba;
 }
 
 // Angle binding for B circuits. With vper > 0 the circuits are the shifted
@@ -544,6 +591,7 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
     x.v0 = v0;
     x.vper = vper;
     if (x.runs) return QL_OK;  // bound in the kernel
+    if (x.pl.whole_state && whole_uses_wave(x.c.n, x.L.gpart != 0, B)) return QL_OK;  // bound in the kernel
     if (x.pl.whole_state) {
         BindArgs ba{};
         ba.inputs = inputs;
@@ -573,32 +621,11 @@ int bind(Ctx& x, int64_t B, const void* inputs, const void* weights, int64_t v0,
         ra.n_members = x.T.n_rmemb;
         ra.F = x.c.n_inputs;
         ra.vper = vper;
-        BindTileArgs ba{};
-        ba.inputs = inputs;
-        ba.weights = weights;
-        ba.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
-        ba.euler = ra.euler;
-        ba.n_runs = ra.n_runs;
-        ba.ops = (const DevOp*)(x.tab + x.T.off_ops);
-        ba.opc = x.W + x.L.opc;
-        ba.diags = (const DevDiag*)(x.tab + x.T.off_diag);
-        ba.dzc = x.W + x.L.dzc;
-        ba.n_diags = x.T.n_diags;
-        ba.fuses = (const DevFuse*)(x.tab + x.T.off_fuse);
-        ba.fzc = x.W + x.L.fzc;
-        ba.n_fuses = x.T.n_fuses;
-        ba.B = B;
-        ba.n_ops = x.T.n_ops;
-        ba.bwd_first = x.T.bwd_first;
-        ba.bwd = x.L.gpart ? 1 : 0;
-        ba.F = x.c.n_inputs;
-        ba.v0 = v0;
-        ba.vper = vper;
+        const BindTileArgs ba = tile_binding(x, B);
         x.tm.start(2);
         e = launch_bind_runs(x.dt, ra, x.stream);
         if (e == hipSuccess) e = launch_bind_tile(x.dt, ba, x.stream);
-        if (e == hipSuccess && x.phase) e = launch_state_phase(x.dt, ba, x.phase, x.stream);
-        if (e == hipSuccess && (x.pl.product || (x.phase && x.c.embed == E_NONE))) {
+        if (e == hipSuccess && x.pl.product) {
             PrefixArgs pa = prefix_args(x, B);
             pa.v0 = v0;
             pa.vper = vper;
@@ -625,7 +652,6 @@ int embed(Ctx& x, int64_t B, const void* inputs, void* psi, int64_t v0, int32_t 
     ea.first = x.c.embed_first;
     ea.F = x.c.n_inputs;
     ea.n = x.c.n;
-    ea.phase = x.phase;
     x.tm.start(2);
     hipError_t e = launch_embed(x.dt, ea, x.stream);
     x.tm.stop();
@@ -709,6 +735,12 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         wa.bwd = bwd ? 1 : 0;
         wa.B = B;
         wa.coef = x.W + x.L.coef;
+        wa.slots = (const SlotSrc*)(x.tab + x.T.off_slots);
+        wa.inputs = x.inputs;
+        wa.weights = x.weights;
+        wa.F = c.n_inputs;
+        wa.v0 = x.v0;
+        wa.vper = x.vper;
         wa.grad_out = grad_out;
         wa.zpart = zpart;
         wa.gpart = gpart;
@@ -758,7 +790,7 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
         ta.n_wg = (flags & (PF_BWD | PF_ZPART)) ? x.L.n_wg : x.L.n_wg_fwd;
         ta.flags = flags;
         ta.n_gslots = (flags & PF_BWD) ? d.n_gslots : 0;
-        ta.phi = pl.product || x.phase ? (const double*)(x.W + x.L.phi) : nullptr;
+        ta.phi = pl.product ? (const double*)(x.W + x.L.phi) : nullptr;
         // dynamic LDS: <Z> scratch and gradient accumulators (the exchange
         // buffer is static)
         const size_t st = tile_static_lds(x.dt, pl.log_r, threads), real = x.dt == 0 ? 4 : 8;
@@ -776,7 +808,7 @@ int state_passes(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* psi_ex
     // factors) in registers unless an embedding wrote the initial state; the
     // last backward pass stores lambda_0 when the amplitude-embedding gradient
     // or the product prefix's environment needs it
-    const int init = emb ? 0 : (pl.product || x.phase ? PF_PRODUCT : PF_INIT);
+    const int init = emb ? 0 : (pl.product ? PF_PRODUCT : PF_INIT);
     const int lam0 = (amp_bwd || pl.product) ? PF_STORE_LAM : 0;
     for (int p = 0; p + 1 < m; p++) {
         void* out = keep ? kept(p) : psi_buf;
@@ -861,7 +893,7 @@ int run(const ql_circuit* hc, ql_dtype dtype, int64_t B, int mode, const void* i
     int dev = 0;
     rc = ensure_device(dev);
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
+    Ctx x = context(h, dt, L, ws, stream);
     x.no_alloc = no_alloc;
     if (no_alloc) x.tm.h = nullptr;  // no timing events either
     if ((rc = place_tables(x, dev))) return rc;
@@ -951,7 +983,7 @@ int param_shift(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inp
     int dev = 0;
     rc = ensure_device(dev);
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][S.L.runs], (uint8_t*)ws, S.L, stream, Timer{h, stream}, S.L.runs};
+    Ctx x = context(h, dt, S.L, ws, stream);
     if ((rc = place_tables(x, dev))) return rc;
     const int32_t V = (int32_t)(2 * h->c.n_param_slots + 1);
     void* ev = x.W + S.ev;
@@ -1017,14 +1049,15 @@ int state(const ql_circuit* hc, ql_dtype dtype, int64_t B, const void* inputs, c
     int dev = 0;
     rc = ensure_device(dev);
     if (rc) return rc;
-    Ctx x{h, dt, h->c, h->c.plan[dt], h->t[dt][L.runs], (uint8_t*)ws, L, stream, Timer{h, stream}, L.runs};
+    Ctx x = context(h, dt, L, ws, stream);
     if ((rc = place_tables(x, dev))) return rc;
-    // the tile path drops global phases: the initial states start with their inverse
-    if (!x.runs && !x.pl.whole_state) x.phase = (double*)(x.W + x.L.zpart);
     if ((rc = bind(x, B, inputs, weights, 0, 0))) return rc;
     if (x.runs) return run_steps(x, B, false, nullptr, nullptr, nullptr, nullptr, psi);
     if ((rc = embed(x, B, inputs, psi, 0, 0))) return rc;
-    return state_passes(x, B, false, nullptr, psi);
+    if ((rc = state_passes(x, B, false, nullptr, psi))) return rc;
+    if (x.pl.whole_state) return QL_OK;  // exact gates: no phase to undo
+    hipError_t e = launch_state_phase(dt, tile_binding(x, B), (double*)(x.W + x.L.zpart), psi, h->c.n, stream);
+    return e == hipSuccess ? QL_OK : fail(QL_EHIP, std::string("state phase: ") + hipGetErrorString(e));
 }
 
 // Blocks of 2^bb amplitudes for shot sampling.
@@ -1111,8 +1144,9 @@ int ql_circuit_create_desc(int32_t n_qubits, const ql_gate* gates, int32_t n_gat
         if (err.empty()) {
             choose_runs(h);
             for (int dt = 0; dt < 2; dt++) {
-                build_tables(h->c, dt, nullptr, h->t[dt][0]);
-                if (h->runs[dt][0]) build_tables(h->c, dt, &h->rp[dt], h->t[dt][1]);
+                build_tables(h->c, dt, h->c.plan[dt], nullptr, h->t[dt][TILE]);
+                if (h->runs[dt][0]) build_tables(h->c, dt, h->c.plan[dt], &h->rp[dt], h->t[dt][RUNS]);
+                if (!h->c.plain[dt].passes.empty()) build_tables(h->c, dt, h->c.plain[dt], nullptr, h->t[dt][PLAIN]);
             }
         }
     } catch (const std::bad_alloc&) {

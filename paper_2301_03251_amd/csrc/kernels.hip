@@ -6,9 +6,12 @@
 //
 // Kernels:
 //   k_bind   -- angle -> (cos(t/2), sin(t/2)) per (sample, rotation slot), in fp64
-//   k_whole  -- small states that k_runs does not take (very long circuits, or
-//               asked for): one workgroup per sample keeps psi and lambda in LDS and runs the forward pass, <Z_q>, the lambda seed and the
-//               adjoint sweep in one launch (no HBM state traffic)
+//   k_whole  -- small states that k_runs does not take (complex64 final states,
+//               long circuits): one workgroup per sample keeps psi and lambda
+//               in LDS and runs the forward pass, <Z_q>, the lambda seed and
+//               the adjoint sweep in one launch (no HBM state traffic)
+//   k_wave   -- the same for n <= 8 qubits: one wavefront per sample holds psi
+//               and lambda in registers (no LDS, no barriers)
 //   k_tile   -- (tile.hip) one tile pass over every sample: each workgroup
 //               streams 2^k amplitudes (a tile) from HBM into registers,
 //               applies the pass's gates there (LDS only to change which tile
@@ -28,7 +31,7 @@
 //               factors of the first pass's initial state, the environment sums
 //               of lambda at the end of the backward sweep, and the prefix
 //               gates' gradient terms
-//   k_state_phase -- the global phase of the tile path's final states
+//   k_state_phase, k_phase_fix -- the global phase of the tile path's final states
 //   k_block_sums, k_block_scan, k_shots, k_shot_z -- shot sampling by inverse CDF
 #include "kcommon.hpp"
 #include "runs_launch.hpp"
@@ -250,6 +253,338 @@ __global__ void __launch_bounds__(256) k_whole(const WholeArgs a) {
     }
     if (a.lam_out)
         for (int j = tid; j < dim; j += nt) ((T2*)a.lam_out)[b * dim + j] = lam[j];
+}
+
+// ---------------------------------------------------------------------------
+// k_wave: the whole state of one sample in one wavefront's registers (n <= 8)
+//
+// Amplitude j = lane + 64 i sits in register i of lane j mod 64: 2^(n-6)
+// registers per lane, one for n <= 6 (lanes >= 2^n then hold zeros and never
+// mix with the others). A gate on qubit q < 6 pairs each lane with lane ^ 2^q
+// through a cross-lane shuffle; on qubit q >= 6, register i with register
+// i ^ 2^(q-6) of the same lane. Every lane computes its own new amplitude from
+// its old one and its partner's, so there is no LDS traffic and no barrier:
+// each gate is wavefront-synchronous. Same arguments, coefficient table and
+// partial layouts as k_whole.
+
+// bit q of amplitude lane + 64 r
+__device__ __forceinline__ int amp_bit(int q, int lane, int r) {
+    return q < 6 ? (lane >> q) & 1 : (r >> (q - 6)) & 1;
+}
+
+// The value of lane ^ 2^B, without the LDS pipe: quad permutes (B = 0, 1),
+// two row shifts under bank masks (B = 2, 3: lanes with bit B clear read from
+// +2^B, the others from -2^B), a permlane swap of two copies and a select
+// (B = 4, 5).
+template <int B>
+__device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v, int lane) {
+    if constexpr (B == 0) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false);
+    } else if constexpr (B == 1) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false);
+    } else if constexpr (B <= 3) {
+        constexpr int SHL = 0x100 + (1 << B), SHR = 0x110 + (1 << B);
+        constexpr int LOW = B == 2 ? 0x5 : 0x3, HIGH = B == 2 ? 0xA : 0xC;  // banks by lane bit B
+        const int lo = __builtin_amdgcn_update_dpp(0, (int)v, SHL, 0xF, LOW, false);
+        return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)v, SHR, 0xF, HIGH, false);
+    } else {
+        const auto r = B == 4 ? __builtin_amdgcn_permlane16_swap(v, v, false, false)
+                              : __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        return ((lane >> B) & 1) ? r[0] : r[1];
+    }
+}
+template <int B>
+__device__ __forceinline__ float xor_lane(float v, int lane) {
+    return __builtin_bit_cast(float, xor_lane_u32<B>(__builtin_bit_cast(uint32_t, v), lane));
+}
+template <int B>
+__device__ __forceinline__ double xor_lane(double v, int lane) {
+    uint2 u = __builtin_bit_cast(uint2, v);
+    u.x = xor_lane_u32<B>(u.x, lane);
+    u.y = xor_lane_u32<B>(u.y, lane);
+    return __builtin_bit_cast(double, u);
+}
+template <typename T2>
+__device__ __forceinline__ T2 xlane(T2 v, int q, int lane) {
+    switch (q) {
+        case 0: return mk<T2>(xor_lane<0>(v.x, lane), xor_lane<0>(v.y, lane));
+        case 1: return mk<T2>(xor_lane<1>(v.x, lane), xor_lane<1>(v.y, lane));
+        case 2: return mk<T2>(xor_lane<2>(v.x, lane), xor_lane<2>(v.y, lane));
+        case 3: return mk<T2>(xor_lane<3>(v.x, lane), xor_lane<3>(v.y, lane));
+        case 4: return mk<T2>(xor_lane<4>(v.x, lane), xor_lane<4>(v.y, lane));
+        default: return mk<T2>(xor_lane<5>(v.x, lane), xor_lane<5>(v.y, lane));
+    }
+}
+
+// New value of one amplitude (bit `bit` of the gate's qubit) from its old value
+// and its partner's: H, RX (both bits alike), RY; Pauli X (1), Y (2), Z (3) by
+// `which` for K_PAULI. (c, s) = (cos t/2, sin t/2); the inverse passes -s.
+template <typename T2, typename Real>
+__device__ __forceinline__ T2 mix_el(int kind, T2 own, T2 par, int bit, Real c, Real s, int which) {
+    const Real sg = bit ? (Real)1 : (Real)-1;
+    switch (kind) {
+        case K_H: {
+            const Real r = (Real)0.70710678118654752440;
+            return mk<T2>((par.x - sg * own.x) * r, (par.y - sg * own.y) * r);
+        }
+        case K_RX:
+            return mk<T2>(c * own.x + s * par.y, c * own.y - s * par.x);
+        case K_RY:
+            return mk<T2>(c * own.x + sg * s * par.x, c * own.y + sg * s * par.y);
+        default:  // K_PAULI
+            if (which == 1) return par;
+            if (which == 2) return mk<T2>(-sg * par.y, sg * par.x);
+            return bit ? mk<T2>(-own.x, -own.y) : own;
+    }
+}
+
+// This element's term of Im<l | P | p> for the rotation's generator P.
+template <typename T2, typename Real>
+__device__ __forceinline__ Real grad_el(int kind, T2 l, T2 own, T2 par, int bit) {
+    if (kind == K_RX) return l.x * par.y - l.y * par.x;
+    if (kind == K_RY) return (bit ? (Real)1 : (Real)-1) * (l.x * par.x + l.y * par.y);
+    const Real t = l.x * own.y - l.y * own.x;  // K_RZ
+    return bit ? -t : t;
+}
+
+// Apply gate g to st (and, when GRAD, return this lane's gradient term taken
+// before the gate with l = lambda). Uniform branches only.
+template <int R, typename T2, typename Real>
+__device__ __forceinline__ void wave_gate(T2* st, const DevGate g, Real c, Real s, int which, int lane) {
+    const int q = g.kind == K_CNOT ? g.q1 : g.q0;
+    if (g.kind == K_RZ) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const Real sg = amp_bit(q, lane, r) ? (Real)1 : (Real)-1;
+            const T2 u = st[r];
+            st[r] = mk<T2>(c * u.x - sg * s * u.y, c * u.y + sg * s * u.x);
+        }
+        return;
+    }
+    if (g.kind == K_CZ) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (amp_bit(g.q0, lane, r) & amp_bit(g.q1, lane, r)) st[r] = mk<T2>(-st[r].x, -st[r].y);
+        return;
+    }
+    if (g.kind == K_PAULI && which == 0) return;
+    T2 old[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) old[r] = st[r];
+    if (q < 6) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const T2 par = xlane(old[r], q, lane);
+            if (g.kind == K_CNOT) st[r] = amp_bit(g.q0, lane, r) ? par : old[r];
+            else st[r] = mix_el<T2, Real>(g.kind, old[r], par, amp_bit(q, lane, r), c, s, which);
+        }
+    } else {
+        const int m = 1 << (q - 6);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            T2 par = old[r];
+            // registers are compile-time indices: pick the partner by a
+            // uniform comparison instead of a runtime array index
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                if (u == (r ^ m)) par = old[u];
+            if (g.kind == K_CNOT) st[r] = amp_bit(g.q0, lane, r) ? par : old[r];
+            else st[r] = mix_el<T2, Real>(g.kind, old[r], par, (r & m) ? 1 : 0, c, s, which);
+        }
+    }
+}
+
+template <int R, typename T2, typename Real>
+__device__ __forceinline__ Real wave_grad(const T2* p, const T2* l, const DevGate g, int lane) {
+    const int q = g.q0;
+    Real acc = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        T2 par = p[r];
+        if (g.kind != K_RZ) {
+            if (q < 6) {
+                par = xlane(p[r], q, lane);
+            } else {
+#pragma unroll
+                for (int u = 0; u < R; ++u)
+                    if (u == (r ^ (1 << (q - 6)))) par = p[u];
+            }
+        }
+        acc += grad_el<T2, Real>(g.kind, l[r], p[r], par, amp_bit(q, lane, r));
+    }
+    return acc;
+}
+
+// Handler id of a gate for the one-wavefront kernel: one-qubit kinds (H, RX,
+// RY, RZ, Pauli) 8 * kind + q, CNOT 40 + 8 c + t, CZ 104 + 8 a + b (a < b).
+// Each id is a case of wave_op whose gate is a compile-time constant, so the
+// lane and register choices of wave_gate and wave_grad fold away.
+__device__ __forceinline__ int wave_handler(const DevGate& g) {
+    if (g.kind == K_CNOT) return 40 + 8 * g.q0 + g.q1;
+    if (g.kind == K_CZ) return 104 + 8 * min(g.q0, g.q1) + max(g.q0, g.q1);
+    return 8 * (g.kind == K_PAULI ? 4 : g.kind) + g.q0;
+}
+
+// BWD = false: the gate on ps. BWD = true: when `want`, this lane's term of
+// the gradient (before the gate) into *grad, then the inverse on ps and lm.
+template <int R, bool BWD, typename T2, typename Real>
+__device__ __forceinline__ void wave_op(int h, T2* ps, T2* lm, Real c, Real s, int which, int lane, Real* grad,
+                                        bool want) {
+    constexpr int NQ = R == 1 ? 6 : R == 2 ? 7 : 8;  // qubits a sample's registers hold
+#define QL_W(H, KIND, Q0, Q1)                                                             \
+    case H:                                                                               \
+        if constexpr (Q0 < NQ && Q1 < NQ && Q0 != Q1) {                                   \
+            constexpr DevGate g{KIND, Q0, Q1, 0};                                         \
+            if constexpr (BWD) {                                                          \
+                if (want) *grad = wave_grad<R, T2, Real>(ps, lm, g, lane);                \
+                wave_gate<R, T2, Real>(ps, g, c, -s, which, lane);                        \
+                wave_gate<R, T2, Real>(lm, g, c, -s, which, lane);                        \
+            } else {                                                                      \
+                wave_gate<R, T2, Real>(ps, g, c, s, which, lane);                         \
+            }                                                                             \
+        }                                                                                 \
+        break;
+#define QL_W1(Q)                                                                          \
+    QL_W(Q, K_H, Q, -1) QL_W(8 + Q, K_RX, Q, -1) QL_W(16 + Q, K_RY, Q, -1)                 \
+    QL_W(24 + Q, K_RZ, Q, -1) QL_W(32 + Q, K_PAULI, Q, -1)
+#define QL_W2(BASE, KIND, A)                                                              \
+    QL_W(BASE + 8 * A + 0, KIND, A, 0) QL_W(BASE + 8 * A + 1, KIND, A, 1)                 \
+    QL_W(BASE + 8 * A + 2, KIND, A, 2) QL_W(BASE + 8 * A + 3, KIND, A, 3)                 \
+    QL_W(BASE + 8 * A + 4, KIND, A, 4) QL_W(BASE + 8 * A + 5, KIND, A, 5)                 \
+    QL_W(BASE + 8 * A + 6, KIND, A, 6) QL_W(BASE + 8 * A + 7, KIND, A, 7)
+    switch (h) {
+        QL_W1(0) QL_W1(1) QL_W1(2) QL_W1(3) QL_W1(4) QL_W1(5) QL_W1(6) QL_W1(7)
+        QL_W2(40, K_CNOT, 0) QL_W2(40, K_CNOT, 1) QL_W2(40, K_CNOT, 2) QL_W2(40, K_CNOT, 3)
+        QL_W2(40, K_CNOT, 4) QL_W2(40, K_CNOT, 5) QL_W2(40, K_CNOT, 6) QL_W2(40, K_CNOT, 7)
+        QL_W2(104, K_CZ, 0) QL_W2(104, K_CZ, 1) QL_W2(104, K_CZ, 2) QL_W2(104, K_CZ, 3)
+        QL_W2(104, K_CZ, 4) QL_W2(104, K_CZ, 5) QL_W2(104, K_CZ, 6) QL_W2(104, K_CZ, 7)
+        default:
+            break;
+    }
+#undef QL_W
+#undef QL_W1
+#undef QL_W2
+}
+
+// Up to 64 consecutive gates held by the lanes of a wavefront: lane i holds
+// gate base + i (its handler id, slot and kind) and this sample's (cos t/2,
+// sin t/2) of its angle (a Pauli channel: the Pauli's index in c), bound in
+// fp64 as k_bind does. The gate loop then reads them with readlane: no
+// memory access per gate.
+template <typename Real>
+struct WaveChunk {
+    int h, slot, kind;
+    Real c, s;
+};
+
+template <typename Real>
+__device__ __forceinline__ WaveChunk<Real> wave_chunk(const WholeArgs& a, const DevGate* __restrict__ gates,
+                                                      int base, int lane, int64_t b) {
+    WaveChunk<Real> w{0, -1, K_H, (Real)1, (Real)0};
+    const int i = base + lane;
+    if (i >= a.n_gates) return w;
+    const DevGate g = gates[i];
+    w.h = wave_handler(g);
+    w.slot = g.slot;
+    w.kind = g.kind;
+    if (g.slot < 0) return w;
+    const SlotSrc src = a.slots[g.slot];
+    if (src.src == S_PAULI) {
+        w.c = (Real)pauli_of<Real>(a.inputs, a.F, src, b, a.v0, a.vper);
+        return w;
+    }
+    int64_t bs = b;
+    const double th = angle_of<Real>(a.inputs, a.weights, a.F, src, b, a.v0, a.vper, bs) +
+                      shift_of(b, a.v0, a.vper, g.slot);
+    double sn, cs;
+    sincos(0.5 * th, &sn, &cs);
+    w.c = (Real)cs;
+    w.s = (Real)sn;
+    return w;
+}
+
+__device__ __forceinline__ int rl(int v, int i) { return __builtin_amdgcn_readlane(v, i); }
+__device__ __forceinline__ float rl(float v, int i) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), i));
+}
+__device__ __forceinline__ double rl(double v, int i) {
+    const long long u = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffff), i);
+    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), i);
+    return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
+}
+
+// One wavefront (one sample) per workgroup. The gates stream through the
+// lanes 64 at a time (wave_chunk): the forward walks the chunks in order, the
+// backward in reverse (a circuit of at most 64 gates keeps its one chunk).
+template <typename Real, int R>
+__global__ void __launch_bounds__(64) k_wave(const WholeArgs a, const DevGate* __restrict__ gates) {
+    using T2 = typename Cx<Real>::T;
+    const int lane = threadIdx.x;
+    const int64_t b = blockIdx.x;
+    const int n = a.n, dim = 1 << n, G = a.n_gates;
+    T2 ps[R], lm[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int j = lane + 64 * r;
+        if (j >= dim) ps[r] = mk<T2>((Real)0, (Real)0);
+        else if (a.psi_in) ps[r] = ((const T2*)a.psi_in)[b * dim + j];
+        else ps[r] = mk<T2>((Real)(j == 0), (Real)0);
+    }
+    WaveChunk<Real> ch{};
+    int loaded = -1;  // base of the chunk in `ch`
+    for (int base = 0; base < G; base += 64) {
+        ch = wave_chunk<Real>(a, gates, base, lane, b);
+        loaded = base;
+        const int cnt = min(64, G - base);
+        for (int i = 0; i < cnt; ++i) {
+            const Real c = rl(ch.c, i);
+            wave_op<R, false, T2, Real>(rl(ch.h, i), ps, lm, c, rl(ch.s, i), (int)c, lane, nullptr, false);
+        }
+    }
+    if (a.psi_out)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (lane + 64 * r < dim) ((T2*)a.psi_out)[b * dim + lane + 64 * r] = ps[r];
+    for (int q = 0; q < n; ++q) {
+        Real acc = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const Real p = ps[r].x * ps[r].x + ps[r].y * ps[r].y;
+            acc += amp_bit(q, lane, r) ? -p : p;
+        }
+        const Real t = wave_to_last(acc);
+        if (lane == 63) a.zpart[b * n + q] = (double)t;
+    }
+    if (!a.bwd) return;
+    const Real* go = (const Real*)a.grad_out + b * n;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        Real d = 0;
+        for (int q = 0; q < n; ++q) d += amp_bit(q, lane, r) ? -go[q] : go[q];
+        lm[r] = mk<T2>(d * ps[r].x, d * ps[r].y);
+    }
+    for (int base = G > 0 ? ((G - 1) / 64) * 64 : -64; base >= 0; base -= 64) {
+        if (base != loaded) {
+            ch = wave_chunk<Real>(a, gates, base, lane, b);
+            loaded = base;
+        }
+        for (int i = min(64, G - base) - 1; i >= 0; --i) {
+            const int slot = rl(ch.slot, i);
+            const bool want = slot >= 0 && rl(ch.kind, i) != K_PAULI;
+            const Real c = rl(ch.c, i);
+            Real part = 0;
+            wave_op<R, true, T2, Real>(rl(ch.h, i), ps, lm, c, rl(ch.s, i), (int)c, lane, &part, want);
+            if (want) {
+                const Real t = wave_to_last(part);
+                if (lane == 63) a.gpart[(size_t)slot * a.B + b] = (double)t;
+            }
+        }
+    }
+    if (a.lam_out)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            if (lane + 64 * r < dim) ((T2*)a.lam_out)[b * dim + lane + 64 * r] = lm[r];
 }
 
 // ---------------------------------------------------------------------------
@@ -578,11 +913,6 @@ __global__ void __launch_bounds__(256) k_bind_prefix(const PrefixArgs a) {
         }
         apply_gate1(g.kind, th, v0, v1);
     }
-    if (a.phase && q == 0) {  // the state's global phase, on one qubit's factor
-        const double2 f = make_double2(a.phase[2 * b], a.phase[2 * b + 1]);
-        v0 = zmul(v0, f);
-        v1 = zmul(v1, f);
-    }
     double2* out = (double2*)a.phi + 2 * t;
     out[0] = v0;
     out[1] = v1;
@@ -834,12 +1164,13 @@ __global__ void __launch_bounds__(256) k_env_grad(const PrefixArgs a) {
 // (a factor (-1)^k per rotation whose angle moved by 2 pi k) and an RZ on a
 // register bit as diag(1, exp(i t)) (dropping exp(-i t / 2)); both are global
 // phases per sample. k_state_phase sums them over the forward ops, from the
-// same angle sources and reduction as k_bind_tile, and stores the inverse
-// phase factor (cos, sin) per sample; the initial state starts with that
-// factor (k_bind_prefix, k_embed_write), so the final state needs no pass of
-// its own. One wavefront per sample, the lanes over the ops: one thread per
-// sample walked the ops' loads one after another (16 qubits, 8 layers, 256
-// samples: 86 us, and 43 us more to multiply the final states).
+// same angle sources and reduction as k_bind_tile, and stores the inverse phase
+// factor (cos, sin) per sample; k_phase_fix multiplies the final state by it.
+// Shots are drawn from complex64 states by their bits, so the place of the
+// phase (on the initial state it would cost no pass of its own) and the order
+// of its sum are fixed. One wavefront per sample: the lanes find 64 ops' terms
+// at a time, which are then added in gate order (one thread per sample walked
+// the ops' loads one after another: 16 qubits, 8 layers, 256 samples 86 us).
 
 template <typename Real>
 __global__ void __launch_bounds__(256) k_state_phase(const BindTileArgs a, double* phase) {
@@ -848,28 +1179,52 @@ __global__ void __launch_bounds__(256) k_state_phase(const BindTileArgs a, doubl
     if (b >= a.B) return;
     const double pi = 3.141592653589793238463, two_pi = 2.0 * pi;
     double ph = 0.0;
-    for (int o = lane; o < a.bwd_first; o += 64) {
-        const DevOp op = a.ops[o];
-        if (op.h == H_DZ) {  // an RZ group drops exp(-i theta / 2) per member, unreduced
-            const DevDiag d = a.diags[op.arg];
-            for (int j = 0; j < MAX_DZ_BITS; ++j)
-                if (d.slot[j] >= 0) ph += 0.5 * op_angle<Real>(a, d.slot[j], b);
-            continue;
+    for (int base = 0; base < a.bwd_first; base += 64) {
+        // an op's terms: turns (each a factor -1), then up to MAX_DZ_BITS dropped angles
+        double turns = 0.0, th[MAX_DZ_BITS] = {};
+        if (base + lane < a.bwd_first) {
+            const DevOp op = a.ops[base + lane];
+            if (op.h == H_DZ) {  // an RZ group drops exp(-i theta / 2) per member, unreduced
+                const DevDiag d = a.diags[op.arg];
+#pragma unroll
+                for (int j = 0; j < MAX_DZ_BITS; ++j)
+                    if (d.slot[j] >= 0) th[j] = op_angle<Real>(a, d.slot[j], b);
+            } else if (op.slot >= 0 && op.kind != K_PAULI) {  // (Paulis are applied exactly)
+                const double t = op_angle<Real>(a, op.slot, b);
+                turns = rint(t / two_pi);
+                if (op.h >= H_G1 + 15 && op.h < H_G1 + 20) th[0] = fma(-two_pi, turns, t);
+                if (op.h >= H_RYZ && op.h < H_RYZ + 5)  // the pair's RZ, as a single RZ on a register bit
+                    th[0] = op_angle<Real>(a, a.fuses[op.arg >> 16].slot, b);
+            }
         }
-        if (op.slot < 0 || op.kind == K_PAULI) continue;  // Paulis are applied exactly
-        const double th = op_angle<Real>(a, op.slot, b);
-        const double k = rint(th / two_pi);
-        ph += pi * k;
-        if (op.h >= H_G1 + 15 && op.h < H_G1 + 20) ph += 0.5 * (th - two_pi * k);
-        if (op.h >= H_RYZ && op.h < H_RYZ + 5)  // the pair's RZ, as a single RZ on a register bit
-            ph += 0.5 * op_angle<Real>(a, a.fuses[op.arg >> 16].slot, b);
+        uint64_t some = __ballot(turns != 0.0 || th[0] != 0.0 || th[1] != 0.0 || th[2] != 0.0 || th[3] != 0.0);
+        while (some) {
+            const int l = (int)__builtin_ctzll(some);
+            some &= some - 1;
+            ph = fma(pi, lane_value(turns, l), ph);
+#pragma unroll
+            for (int j = 0; j < MAX_DZ_BITS; ++j) ph = fma(0.5, lane_value(th[j], l), ph);
+        }
     }
-    ph = wave_sum(ph);
     if (lane != 0) return;
     double sn, cs;  // the inverse phase factor, once per sample
     sincos(-ph, &sn, &cs);
     phase[2 * b] = cs;
     phase[2 * b + 1] = sn;
+}
+
+template <typename T2>
+__global__ void k_phase_fix(void* psi, const double* phase, int64_t B, int n) {
+    const int64_t total = B << n;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const double cs = phase[2 * (i >> n)], sn = phase[2 * (i >> n) + 1];
+        T2 v = ((T2*)psi)[i];
+        const double x = (double)v.x, y = (double)v.y;
+        v.x = (decltype(v.x))(x * cs - y * sn);
+        v.y = (decltype(v.y))(x * sn + y * cs);
+        ((T2*)psi)[i] = v;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -929,13 +1284,8 @@ __global__ void __launch_bounds__(256) k_embed_write(const EmbedArgs a) {
             const int64_t bs = a.vper > 0 ? (a.v0 + i) / a.vper : i;
             const Real v = ((const Real*)a.inputs)[bs * a.F + a.first + j];
             re = r > 0 ? (Real)((double)v / r) : (Real)0;
-            if (a.phase && r > 0) {
-                ((T2*)a.psi)[t] = mk<T2>((Real)((double)v / r * a.phase[2 * i]), (Real)((double)v / r * a.phase[2 * i + 1]));
-                continue;
-            }
         }
-        ((T2*)a.psi)[t] = a.phase ? mk<T2>((Real)((double)re * a.phase[2 * i]), (Real)((double)re * a.phase[2 * i + 1]))
-                                  : mk<T2>(re, (Real)0);
+        ((T2*)a.psi)[t] = mk<T2>(re, (Real)0);
     }
 }
 
@@ -1219,7 +1569,32 @@ hipError_t launch_bind(int dtype, const BindArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Circuits per launch from which a forward-only whole-state launch of n <= 8
+// qubits takes the LDS kernel: with that many wavefronts in flight its LDS
+// partner exchanges outrun k_wave's DPP and permlane ones (parameter-shift
+// chunks of the 7-qubit autoencoder: 0.53 against 0.72 ms at 49408 circuits,
+// 1.56 against 1.78 ms at 2048, even at 512).
+constexpr int64_t WAVE_MAX_FWD_CIRCUITS = 2048;
+
+bool whole_uses_wave(int n, bool bwd, int64_t B) { return n <= 8 && (bwd || B < WAVE_MAX_FWD_CIRCUITS); }
+
 hipError_t launch_whole(int dtype, const WholeArgs& a, int threads, size_t lds, hipStream_t s) {
+    if (whole_uses_wave(a.n, a.bwd != 0, a.B)) {  // one wavefront per sample
+        const dim3 grid((unsigned)a.B), block(64);
+#define QL_WAVE(REAL)                                                                     \
+    {                                                                                     \
+        if (a.n <= 6) hipLaunchKernelGGL((k_wave<REAL, 1>), grid, block, 0, s, a, a.gates);      \
+        else if (a.n == 7) hipLaunchKernelGGL((k_wave<REAL, 2>), grid, block, 0, s, a, a.gates); \
+        else hipLaunchKernelGGL((k_wave<REAL, 4>), grid, block, 0, s, a, a.gates);               \
+    }
+        if (dtype == 0) {
+            QL_WAVE(float)
+        } else {
+            QL_WAVE(double)
+        }
+#undef QL_WAVE
+        return hipGetLastError();
+    }
     if (dtype == 0) hipLaunchKernelGGL(k_whole<float>, dim3((unsigned)a.B), dim3(threads), lds, s, a);
     else hipLaunchKernelGGL(k_whole<double>, dim3((unsigned)a.B), dim3(threads), lds, s, a);
     return hipGetLastError();
@@ -1354,10 +1729,18 @@ hipError_t launch_env_grad(int dtype, const PrefixArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, hipStream_t s) {
-    const unsigned grid = (unsigned)((a.B + 3) / 4);
-    if (dtype == 0) hipLaunchKernelGGL(k_state_phase<float>, dim3(grid), dim3(256), 0, s, a, phase);
-    else hipLaunchKernelGGL(k_state_phase<double>, dim3(grid), dim3(256), 0, s, a, phase);
+hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, void* psi, int n,
+                              hipStream_t s) {
+    const unsigned g1 = (unsigned)((a.B + 3) / 4);
+    const int64_t total = a.B << n;
+    const unsigned g2 = (unsigned)std::min<int64_t>((total + 255) / 256, 65536);
+    if (dtype == 0) {
+        hipLaunchKernelGGL(k_state_phase<float>, dim3(g1), dim3(256), 0, s, a, phase);
+        hipLaunchKernelGGL(k_phase_fix<float2>, dim3(g2), dim3(256), 0, s, psi, (const double*)phase, a.B, n);
+    } else {
+        hipLaunchKernelGGL(k_state_phase<double>, dim3(g1), dim3(256), 0, s, a, phase);
+        hipLaunchKernelGGL(k_phase_fix<double2>, dim3(g2), dim3(256), 0, s, psi, (const double*)phase, a.B, n);
+    }
     return hipGetLastError();
 }
 

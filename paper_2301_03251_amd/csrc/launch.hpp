@@ -106,7 +106,14 @@ struct WholeArgs {
     int32_t n_gates, n, n_slots;
     int32_t bwd;          // 1: run the adjoint sweep
     int64_t B;
-    const void* coef;     // [B][n_slots] from k_bind
+    const void* coef;     // [B][n_slots]: from k_bind (LDS kernel), unused by the wavefront kernel
+    // the angle sources, which the one-wavefront kernel binds itself (as k_bind does)
+    const SlotSrc* slots; // [n_slots]
+    const void* inputs;   // [B][F] Real
+    const void* weights;  // [P] Real
+    int32_t F;
+    int32_t vper;         // parameter-shift chunks: circuits per sample, 0 = plain batch
+    int64_t v0;           // parameter-shift chunks: first virtual circuit
     const void* grad_out; // [B][n] Real
     double* zpart;        // [B][n]           (one workgroup per sample)
     double* gpart;        // [n_slots][B]
@@ -127,7 +134,6 @@ struct EmbedArgs {
     int64_t v0;
     int32_t vper;         // 0: circuit i is sample i
     int32_t kind, first, F, n;
-    const double* phase;  // [count] complex: a factor on the initial state, or null
 };
 
 // Amplitude-embedding VJP: grad_inputs[b][first + j] += (2 / |x|) (Re lam_j -
@@ -209,7 +215,6 @@ struct PrefixArgs {
     int32_t vper;
     int32_t n, F, n_wg;
     int32_t env_wg;            // workgroups per sample of the environment kernel
-    const double* phase;       // [count] complex: a factor on the product state, or null
 };
 // Workgroups per sample of the environment kernel for n qubits and batch B.
 int env_workgroups(int dtype, int n, int64_t B);
@@ -244,14 +249,18 @@ size_t tile_static_lds(int dtype, int log_r, int threads);
 hipError_t launch_bind(int dtype, const BindArgs& a, hipStream_t s);
 hipError_t launch_bind_tile(int dtype, const BindTileArgs& a, hipStream_t s);
 hipError_t launch_whole(int dtype, const WholeArgs& a, int threads, size_t lds, hipStream_t s);
+// Whether launch_whole runs the one-wavefront kernel (which binds the angles
+// itself, so no k_bind launch is needed) for this call.
+bool whole_uses_wave(int n, bool bwd, int64_t B);
 hipError_t launch_tile(int dtype, int log_r, bool bwd, const TileArgs& a, int threads, size_t lds,
                        hipStream_t s);
 hipError_t launch_reduce(int dtype, const ReduceArgs& a, hipStream_t s);
 hipError_t launch_shift_dot(int dtype, const ShiftDotArgs& a, hipStream_t s);
 hipError_t launch_sample(int dtype, const SampleArgs& a, hipStream_t s);
-// Inverse of the per-sample global phase that the forward ops leave (phase:
-// [B] complex fp64).
-hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, hipStream_t s);
+// Undo the per-sample global phase the tile kernel leaves on final states
+// (phase: [2B] fp64 scratch: the inverse phase factor per sample).
+hipError_t launch_state_phase(int dtype, const BindTileArgs& a, double* phase, void* psi, int n,
+                              hipStream_t s);
 hipError_t launch_embed(int dtype, const EmbedArgs& a, hipStream_t s);
 hipError_t launch_embed_grad(int dtype, const EmbedGradArgs& a, hipStream_t s);
 hipError_t launch_shift_grad(int dtype, const ShiftGradArgs& a, hipStream_t s);

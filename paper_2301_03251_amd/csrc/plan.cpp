@@ -867,14 +867,15 @@ std::string build_circuit(int n, const int32_t* g5, int n_gates, int n_inputs, i
     if (o.product_prefix < -1 || o.product_prefix > 1) return "option: product_prefix must be -1, 0 or 1";
     if (o.pass_search < -1 || o.pass_search > 1) return "option: pass_search must be -1, 0 or 1";
     for (int dt = 0; dt < 2; dt++) {
-        std::string e = build_plan(out, dt, out.plan[dt]);
+        std::string e = build_plan(out, dt, out.plan[dt], out.plain[dt]);
         if (!e.empty()) return e;
     }
     return "";
 }
 
-std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
+std::string build_plan(const Circuit& c, int dtype, Plan& pl, Plan& plain) {
     pl = Plan{};
+    plain = Plan{};
     pl.n = c.n;
     pl.n_slots = (int)c.slots.size();
     const Options& o = c.opts;
@@ -1086,7 +1087,8 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
         return seq;
     };
     // Lay out a pass sequence: each pass's register phases, exchanges and ops.
-    auto lay_out = [&](std::vector<Cand> seq, Plan& to) {
+    const bool rot_runs = o.rz_groups == 0;
+    auto lay_out = [&](std::vector<Cand> seq, Plan& to, bool runs) {
         for (Cand& cd : seq) {
             uint64_t tile = cd.tile;
             // fill the tile up to k qubits with the lowest unused qubits
@@ -1096,8 +1098,8 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
             pp.gates = std::move(cd.gates);
             schedule_pass(c.gates, pp, k, log_r, low, dtype == 0 ? 8u : 16u, to.phases,
                           o.rz_groups == 0 ? &to.diags : nullptr, o.rz_groups == 0 ? &to.fuses : nullptr,
-                          o.cz_groups == 0 ? &to.czgs : nullptr, o.rz_groups == 0 ? &to.runs : nullptr,
-                          o.rz_groups == 0 ? &to.run_members : nullptr);
+                          o.cz_groups == 0 ? &to.czgs : nullptr, runs ? &to.runs : nullptr,
+                          runs ? &to.run_members : nullptr);
             to.passes.push_back(std::move(pp));
         }
     };
@@ -1130,7 +1132,7 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
         int best = -1;
         for (auto& p : plans) {
             Plan t;
-            lay_out(std::move(p), t);
+            lay_out(std::move(p), t, rot_runs);
             int score = 0;
             for (const PassPlan& pp : t.passes) score += 3 * pp.n_transposes + pp.n_lane_swaps;
             if (best < 0 || score < best) {
@@ -1214,7 +1216,7 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
                     seq.push_back(std::move(cd));
                 }
                 Plan t2;
-                lay_out(std::move(seq), t2);
+                lay_out(std::move(seq), t2, rot_runs);
                 int score = 0;
                 for (const PassPlan& pp : t2.passes) score += 3 * pp.n_transposes + pp.n_lane_swaps;
                 if (score <= score_ops) take(t2, absorbed);
@@ -1222,6 +1224,26 @@ std::string build_plan(const Circuit& c, int dtype, Plan& pl) {
         }
     }
     if (pl.phases.size() > 65535) return "plan too large (phases)";
+    if (!pl.runs.empty()) {
+        std::vector<Cand> seq;
+        for (const PassPlan& pp : pl.passes) {
+            Cand cd;
+            cd.tile = 0;
+            for (int q : pp.qubits) cd.tile |= 1ull << q;
+            cd.gates = pp.gates;
+            seq.push_back(std::move(cd));
+        }
+        plain = pl;
+        plain.passes.clear();
+        plain.phases.clear();
+        plain.diags.clear();
+        plain.fuses.clear();
+        plain.czgs.clear();
+        plain.runs.clear();
+        plain.run_members.clear();
+        lay_out(std::move(seq), plain, false);
+        if (plain.phases.size() > 65535) return "plan too large (phases)";
+    }
     return "";
 }
 

@@ -304,6 +304,7 @@ struct Circuit {
     int n_user_gates = 0;        // gates as given
     Options opts;
     Plan plan[2];                // per dtype (0 = c64, 1 = c128)
+    Plan plain[2];               // the same passes without rotation runs (empty where plan has none)
 };
 
 // Validate and copy gates, rewrite controlled rotations and Pauli channels
@@ -314,8 +315,9 @@ std::string build_circuit(int n, const int32_t* gates5, int n_gates, int n_input
 // Largest qubit count for amplitude embedding (2^n features per sample).
 constexpr int AMPLITUDE_MAX_QUBITS = 30;
 
-// Build the plan for one dtype. Returns "" or an error message.
-std::string build_plan(const Circuit& c, int dtype, Plan& out);
+// Build the plan for one dtype and, where it has rotation runs, the same
+// passes without them. Returns "" or an error message.
+std::string build_plan(const Circuit& c, int dtype, Plan& out, Plan& plain);
 
 // Largest qubit count that the whole-state kernel handles for a dtype.
 int whole_state_max_qubits(int dtype);
