@@ -701,6 +701,7 @@ int run_steps(Ctx& x, int64_t B, bool bwd, const void* grad_out, void* expz, voi
     a.n_entries = (int)rp.entries.size();
     a.n_members = (int)rp.members.size();
     a.n_words = (int)rp.words.size();
+    a.n_mats = rp.n_mat / 4;
     a.embed = c.embed;
     a.first = c.embed_first;
     a.lds = runs_lds(x.dt, rp, a.n_slots, bwd);

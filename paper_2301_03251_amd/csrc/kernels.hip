@@ -1327,28 +1327,6 @@ __global__ void __launch_bounds__(256) k_embed_grad(const EmbedGradArgs a) {
 // block totals and the in-block search both lane-scan those stored sums, so
 // they see bitwise the same numbers.
 
-// A DPP move (lanes outside the move's source or the row mask read 0).
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_or0(double v) {
-    const uint2 u = __builtin_bit_cast(uint2, v);
-    uint2 r;
-    r.x = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.x, CTRL, ROWS, 0xF, false);
-    r.y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)u.y, CTRL, ROWS, 0xF, false);
-    return __builtin_bit_cast(double, r);
-}
-
-// Inclusive scan over the 64 lanes in a fixed order: inside each 16-lane row
-// by row shifts, then row totals broadcast to the rows above (all moves on the
-// VALU; the shuffles of a scan through LDS bounded the sampling kernels).
-__device__ __forceinline__ double lane_scan(double v) {
-    v += dpp_or0<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
-    v += dpp_or0<0x112, 0xF>(v);
-    v += dpp_or0<0x114, 0xF>(v);
-    v += dpp_or0<0x118, 0xF>(v);
-    v += dpp_or0<0x142, 0xA>(v);  // row 0's total to row 1, row 2's to row 3
-    v += dpp_or0<0x143, 0xC>(v);  // lane 31's to rows 2 and 3
-    return v;
-}
 // Sum over all lanes of 64 values per lane, lane l keeping value l's: log2(64)
 // levels, each halving the values. On lane bit B, lanes with the bit clear keep
 // the lower half of the values and the others the upper half, and each adds

@@ -250,6 +250,8 @@ struct Planner {
             p.n_mat += 8;
             e.grad = (uint32_t)p.n_grads++;
             p.controlled = true;
+            e.layer_first = (int)e.mat / 4;
+            e.layer_end = e.layer_first + 2;
             p.steps.push_back({RS_CRUN + (uint32_t)at[q], e.mat, (uint32_t)(at[ctl] - p.log_r), e.grad});
         } else if (c.embed == E_NONE && !(touched & qs) && p.n_exchanges == 0) {
             p.prefix |= bit;
@@ -265,6 +267,8 @@ struct Planner {
             DevRunStep& s = p.steps[layer];
             s.ctl |= bit;
             e.mat = s.mat + 4u * (uint32_t)at[q];
+            e.layer_first = (int)s.mat / 4;
+            e.layer_end = e.layer_first + p.n_pos;
             e.grad = s.grad + (uint32_t)at[q];
         }
         if (!rot) e.grad = RUNS_NONE;

@@ -216,18 +216,23 @@ __device__ __forceinline__ int row_bit(int pos, int sid) {
     return (sid >> b) & 1;
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return dpp_f32<CTRL>(v); }
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) { return dpp_f64<CTRL>(v); }
+
 // The wavefront's gradient sums of one run into its words of the table. The
 // three sums share the first two levels of the reduction: a permlane swap of
 // two of them leaves one's halves in the lower lanes and the other's in the
-// upper, so one add folds both (10 instructions in fp32, 21 in fp64, against
-// 18 and 54 for three reductions of their own). Rows 0, 1, 2 end with X, Z, Y.
+// upper, so one add folds both. Rows 0, 1, 2 end with X, Z, Y. The last two
+// levels are fp64: 16 lanes are added in fp32.
 template <bool REAL, typename Real>
 __device__ __forceinline__ void store_sums(Real* o, Real sx, Real sy, Real sz, int lane) {
     if constexpr (REAL) {
-        sy = wave_to_last(sy);
-        if (lane == 63) {
+        const double y = wave_total(sy);
+        if (lane == 0) {
             o[0] = (Real)0;
-            o[1] = sy;
+            o[1] = (Real)y;
             o[2] = (Real)0;
         }
     } else {
@@ -236,8 +241,13 @@ __device__ __forceinline__ void store_sums(Real* o, Real sx, Real sy, Real sz, i
         swap_real<5>(sz, v);
         v += sz;
         swap_real<4>(u, v);
-        u = row_sum(u + v);
-        if ((lane & 15) == 0 && lane < 48) o[lane == 0 ? 0 : lane == 16 ? 2 : 1] = u;
+        u += v;
+        u += dpp<0xB1>(u);
+        u += dpp<0x4E>(u);
+        double t = (double)u;  // the last levels in fp64
+        t += dpp_f64<0x141>(t);
+        t += dpp_f64<0x140>(t);
+        if ((lane & 15) == 0 && lane < 48) o[lane == 0 ? 0 : lane == 16 ? 2 : 1] = (Real)t;
     }
 }
 
@@ -271,10 +281,33 @@ __device__ __forceinline__ void flip_signs(T2* a, uint32_t m) {
     }
 }
 
+// |m|^2 - 1 of a run's rounded matrix with first column (u, v). Such a matrix
+// is a rotation times its norm (its entries round in pairs), so the states of a
+// plan differ from normed ones by one factor, the same for every amplitude, and
+// taking it out of the sums at the end leaves the rounding of the angles: 8
+// layers of RY at 10 qubits, relative errors of <Z>, input and weight gradients
+// 4.3e-7, 5.3e-7, 6.4e-7 -> 2.1e-7, 2.6e-7, 3.1e-7. Complex64 only (a reference
+// in fp64 rounds its own rotations alike). A controlled run scales the halves of
+// the state apart and is left as it is.
+__device__ __forceinline__ double deviation(float2 u, float2 v) {
+    const double a = u.x, b = u.y, c = v.x, d = v.y;
+    return fma(a, a, fma(b, b, fma(c, c, fma(d, d, -1.0))));
+}
+
 // Gate record of a step held by a lane (see run_record).
 struct Step {
     uint32_t op, mat, y;
 };
+
+// The kernel's arguments, read again: what only the ends of the kernel use would
+// else hold scalar registers through the steps (59 spilled, shift of 10 qubits
+// and 256 samples 1.88 ms).
+typedef const __attribute__((address_space(4))) RunArgs* LateArgs;
+__device__ __forceinline__ LateArgs late_args() {
+    LateArgs p = (LateArgs)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return p;
+}
 
 // One workgroup per sample, 2^log_t threads (at least one wavefront; lanes
 // past 2^n hold zeros and mix with nothing). Every table the steps read is in
@@ -289,6 +322,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
                                                const uint32_t* __restrict__ words_g) {
     using T2 = typename Cx<Real>::T;
     constexpr int R = 1 << LOG_R;
+    constexpr bool NORMS = sizeof(Real) == 4;
     extern __shared__ __align__(16) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, nt = blockDim.x, NW = nt >> 6;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -296,15 +330,18 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     const int64_t b = blockIdx.x;
     const int n = a.n, log_t = a.log_t, dim = 1 << n;
     T2* mat = (T2*)(smem + a.lds.mat);                   // [n_mat]
+    // prefix runs (positions' matrices at the head of the table): the factors of
+    // bit 0 and 1 of position p at fac[FS p], fac[FS p + 1]
+    double2* fac = (double2*)mat;
+    constexpr int FS = (int)(4 * sizeof(T2) / sizeof(double2));
     double2* cs = (double2*)(smem + a.lds.cs);           // [n_cs]
+    double* scale = (double*)(smem + a.lds.scale);       // [n_mats] (fp32): see deviation()
     uint8_t* kinds = smem + a.lds.kind;                  // [n_members]
     uint32_t* words = (uint32_t*)(smem + a.lds.words);   // [n_words]
-    double* red = (double*)(smem + a.lds.red);           // [n + 1][NW]
     Real* go = (Real*)(smem + a.lds.go);                 // [n] upstream gradient by position
     Real* sums = (Real*)(smem + a.lds.sum);              // [n_grads][NW][3]
-    double* gs = (double*)(smem + a.lds.gs);             // [n_slots]
     const bool active = sid < (1 << log_t);
-    auto last_qubit = [&](int p) { return (int)((a.last_qubit >> (4 * p)) & 15u); };
+    auto qubit_at = [&](uint64_t qubits, int p) { return (int)((qubits >> (4 * p)) & 15u); };
 
     // ---- the sample's matrices: angles first, one member per thread, then
     // one run per thread
@@ -312,7 +349,9 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     DevRunEntry my{};                                      // this thread's first run
     if (tid < a.n_entries) my = entries[tid];
     for (int i = tid; i < a.n_words; i += nt) words[i] = words_g[i];
-    if (a.bwd && tid < n) go[tid] = ((const Real*)a.grad_out)[b * n + last_qubit(tid)];
+    if constexpr (NORMS)
+        for (int i = tid; i < a.n_mats; i += nt) scale[i] = 0.0;
+    if (a.bwd && tid < n) go[tid] = ((const Real*)a.grad_out)[b * n + qubit_at(a.last_qubit, tid)];
     const int64_t bs = a.vper > 0 ? (a.v0 + b) / a.vper : b;
     for (int i = tid; i < a.n_members; i += nt) {
         const DevRunMember m = members[i];
@@ -339,17 +378,40 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     for (int i = tid; i < a.n_entries; i += nt) {
         const DevRunEntry e = i == tid ? my : entries[i];
         for (int v = 0; v < 1 + e.controlled; ++v) {
-            Z2 m = zident();
-            for (int k = 0; k < e.count; ++k)
-                m = left_mul(kinds[e.first + k], cs[e.cs + (k << e.controlled) + v], m);
+            // the first column (a, c); the determinant is -1 after an odd
+            // number of H and Paulis, so the second is (-det c*, det a*)
+            double2 a1 = make_double2(1.0, 0.0), c1 = make_double2(0.0, 0.0);
+            bool odd = false;
+            for (int k = 0; k < e.count; ++k) {
+                const int kind = kinds[e.first + k];
+                const double2 t = cs[e.cs + (k << e.controlled) + v], u = a1, w = c1;
+                left_row(kind, t, u, w, a1, c1);
+                odd ^= kind == K_H || (kind == K_PAULI && t.x != 0.0);
+            }
+            if (e.mat < 4 * (uint32_t)min(n, LOG_R + 6)) {  // a prefix run: its first column, in fp64
+                fac[FS * (e.mat >> 2)] = a1;
+                fac[FS * (e.mat >> 2) + 1] = c1;
+                continue;
+            }
             T2* o = mat + e.mat + 4 * v;
-            o[0] = to_real<T2, Real>(m.a);
-            o[1] = to_real<T2, Real>(m.b);
-            o[2] = to_real<T2, Real>(m.d);
-            o[3] = to_real<T2, Real>(m.c);
+            o[0] = to_real<T2, Real>(a1);
+            o[1] = to_real<T2, Real>(odd ? make_double2(c1.x, -c1.y) : make_double2(-c1.x, c1.y));
+            o[2] = to_real<T2, Real>(odd ? make_double2(-a1.x, a1.y) : make_double2(a1.x, -a1.y));
+            o[3] = to_real<T2, Real>(c1);
+            if constexpr (NORMS)
+                if (!e.controlled) scale[e.mat >> 2] = deviation(o[0], o[3]);
         }
     }
     __syncthreads();
+    if (NORMS && a.bwd && wave == 0) {  // the sums over the matrices up to each (read after the next barrier)
+        double before = 0.0;
+        for (int i0 = 0; i0 < a.n_mats; i0 += 64) {
+            const int i = i0 + lane;
+            const double t = before + lane_scan(i < a.n_mats ? scale[i] : 0.0);
+            if (i < a.n_mats) scale[i] = t;
+            before = lane_value(t, 63);
+        }
+    }
 
     // ---- initial state. Amplitude index of (thread, register i): bits of the
     // storage index moved to their qubits.
@@ -360,15 +422,36 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         return j;
     };
     T2 ps[R], lm[R];
+    // the product of the prefix runs' first columns (bits past n are 0 in
+    // every active thread); the thread's factor in fp64
+    auto product_state = [&](T2* dst, uint32_t prefix) {
+        auto factor = [&](int p, int bit) {
+            const double2 f = fac[FS * p + bit];
+            return (prefix >> p) & 1u ? f : make_double2(bit ? 0.0 : 1.0, 0.0);
+        };
+        auto two = [&](int l) { return cxmul(factor(LOG_R + l, (sid >> l) & 1), factor(LOG_R + l + 1, (sid >> (l + 1)) & 1)); };
+        double2 c = cxmul(cxmul(two(0), two(2)), two(4));
+        if (!active || wave > 0) c = make_double2(0.0, 0.0);  // (no prefix run on a wavefront bit)
+        dst[0] = to_real<T2, Real>(c);
+#pragma unroll
+        for (int m = 0; m < LOG_R; ++m) {
+            const T2 f0 = to_real<T2, Real>(factor(m, 0)), f1 = to_real<T2, Real>(factor(m, 1));
+#pragma unroll
+            for (int i = 0; i < (1 << m); ++i) {
+                dst[i | 1 << m] = cxmul(dst[i], f1);
+                dst[i] = cxmul(dst[i], f0);
+            }
+        }
+    };
     const Real* x = a.embed ? (const Real*)a.inputs + bs * a.F + a.first : nullptr;
     double norm = 0.0;
     if (a.embed == E_AMPLITUDE) {
-        double acc = 0.0;
+        double *red0 = (double*)(smem + a.lds.red), acc = 0.0;
         for (int j = tid; j < dim; j += nt) acc = fma((double)x[j], (double)x[j], acc);
         acc = wave_total(acc);
-        if (lane == 0) red[wave] = acc;
+        if (lane == 0) red0[wave] = acc;
         __syncthreads();
-        for (int w = 0; w < NW; ++w) norm += red[w];
+        for (int w = 0; w < NW; ++w) norm += red0[w];
         norm = sqrt(norm);
         __syncthreads();
 #pragma unroll
@@ -384,25 +467,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         for (int i = 0; i < R; ++i)
             ps[i] = mk<T2>((Real)(active && amp_index(a.first_qubit, i) == idx), (Real)0);
     } else {
-        // the product of the prefix runs' first columns (bits past n are 0 in every active thread)
-        auto factor = [&](int p, int bit) {
-            const T2 f = mat[4 * p + 3 * bit];
-            return (a.prefix >> p) & 1u ? f : mk<T2>((Real)(bit ? 0 : 1), (Real)0);
-        };
-        T2 c = mk<T2>((Real)(active ? 1 : 0), (Real)0);
-#pragma unroll
-        for (int p = LOG_R; p < LOG_R + 6; ++p) c = cxmul(c, factor(p, (sid >> (p - LOG_R)) & 1));
-        if (wave > 0) c = mk<T2>((Real)0, (Real)0);  // no prefix run on a wavefront bit
-        ps[0] = c;
-#pragma unroll
-        for (int m = 0; m < LOG_R; ++m) {
-            const T2 f0 = factor(m, 0), f1 = factor(m, 1);
-#pragma unroll
-            for (int i = 0; i < (1 << m); ++i) {
-                ps[i | 1 << m] = cxmul(ps[i], f1);
-                ps[i] = cxmul(ps[i], f0);
-            }
-        }
+        product_state(ps, a.prefix);
     }
 
     // ---- steps
@@ -495,11 +560,14 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     }
 
     // ---- <Z> and the final state, in the last layout
-    if (a.psi_out && active) {
+    const LateArgs f = late_args();
+    const uint64_t last = f->last_qubit;
+    double *red = (double*)(smem + f->lds.red), *norms = (double*)(smem + f->lds.scale);
+    if (f->psi_out && active) {
 #pragma unroll
-        for (int i = 0; i < R; ++i) ((T2*)a.psi_out)[b * dim + amp_index(a.last_qubit, i)] = ps[i];
+        for (int i = 0; i < R; ++i) ((T2*)f->psi_out)[b * dim + amp_index(last, i)] = ps[i];
     }
-    if (a.expz) {
+    if (f->expz) {
         Real pt = 0, dm[LOG_R + 1];
 #pragma unroll
         for (int m = 0; m < LOG_R; ++m) dm[m] = 0;
@@ -512,29 +580,38 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         }
 #pragma unroll
         for (int m = 0; m < LOG_R; ++m) {
-            const Real t = wave_to_last(dm[m]);
-            if (lane == 63) red[m * NW + wave] = (double)t;
+            const double t = wave_total(dm[m]);
+            if (lane == 0) red[m * NW + wave] = t;
         }
 #pragma unroll
         for (int l = 0; l < 6; ++l)
             if (LOG_R + l < n) {
-                const Real t = wave_to_last((sid >> l & 1) ? -pt : pt);
-                if (lane == 63) red[(LOG_R + l) * NW + wave] = (double)t;
+                const double t = wave_total((sid >> l & 1) ? -pt : pt);
+                if (lane == 0) red[(LOG_R + l) * NW + wave] = t;
             }
         if (NW > 1) {
-            const Real t = wave_to_last(pt);
-            if (lane == 63)
-                for (int p = LOG_R + 6; p < n; ++p)
-                    red[p * NW + wave] = (wave >> (p - LOG_R - 6) & 1) ? -(double)t : (double)t;
+            const double t = wave_total(pt);
+            if (lane == 0)
+                for (int p = LOG_R + 6; p < n; ++p) red[p * NW + wave] = (wave >> (p - LOG_R - 6) & 1) ? -t : t;
+        }
+        if (NORMS && !f->bwd) {
+            double t = 0.0;
+            for (int i = tid; i < f->n_mats; i += nt) t += norms[i];
+            t = wave_total(t);
+            if (lane == 0) red[n * NW + wave] = t;
         }
         __syncthreads();
         if (tid < n) {
-            double t = 0.0;
-            for (int w = 0; w < NW; ++w) t += red[tid * NW + w];
-            ((Real*)a.expz)[b * n + last_qubit(tid)] = (Real)t;
+            double t = 0.0, u = 1.0;
+            for (int w = 0; w < NW; ++w) {
+                t += red[tid * NW + w];
+                if (NORMS && !f->bwd) u += red[n * NW + w];
+            }
+            if (NORMS && f->bwd) u += norms[f->n_mats - 1];
+            ((Real*)f->expz)[b * n + qubit_at(last, tid)] = (Real)(NORMS ? t / u : t);
         }
     }
-    if (!a.bwd) return;
+    if (!f->bwd) return;
 
     // ---- lambda = (sum_q g_q Z_q) psi
     {
@@ -610,34 +687,50 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         }
         c1 = c0;
     }
-    layer<LOG_R, RUN_SUMS, 0, false, T2, Real>(ps, lm, mat, a.prefix, Rows<T2>{}, my_sums, sum_stride, sid, lane);
+    const LateArgs t = late_args();
+    if (t->prefix) product_state(ps, t->prefix);  // exact, not un-computed
+    layer<LOG_R, RUN_SUMS, 0, false, T2, Real>(ps, lm, mat, t->prefix, Rows<T2>{}, my_sums, sum_stride, sid, lane);
 #undef QL_CRUN_CASE
 #undef QL_CRUN_CASES
     __syncthreads();
 
     // ---- the gradient of every rotation, one run per thread
-    for (int i = tid; i < a.n_entries; i += nt) {
+    const uint8_t* kinds_t = smem + t->lds.kind;
+    const double2* cs_t = (const double2*)(smem + t->lds.cs);
+    double* gs = (double*)(smem + t->lds.gs);
+    double* red_t = (double*)(smem + t->lds.red);
+    const double* scale_t = (const double*)(smem + t->lds.scale);
+    const double all = NORMS ? scale_t[t->n_mats - 1] : 0.0;
+    for (int i = tid; i < t->n_entries; i += nt) {
         const DevRunEntry e = i == tid ? my : entries[i];
         if (e.grad == RUNS_NONE) continue;
         double S[3] = {0.0, 0.0, 0.0};
         for (int w = 0; w < NW; ++w)
             for (int c = 0; c < 3; ++c) S[c] += (double)sums[((size_t)e.grad * NW + w) * 3 + c];
+        // psi and lambda have the scale of every run, and of those undone before these sums once more
+        if constexpr (NORMS) {
+            const int at = (int)(e.mat >> 2);
+            double off = all;
+            if (at >= min(n, LOG_R + 6)) off += (all - scale_t[e.layer_end - 1]) + (scale_t[at - 1] - scale_t[e.layer_first - 1]);
+            const double f = 1.0 / (1.0 + off);
+            for (int c = 0; c < 3; ++c) S[c] *= f;
+        }
         // the sums seen before each gate: g^dagger P g mixes them like a rotation of the three axes
         for (int k = e.count - 1; k >= 0; --k) {
-            const int kind = kinds[e.first + k];
-            const double2 t = cs[e.cs + (k << e.controlled) + e.controlled];
+            const int kind = kinds_t[e.first + k];
+            const double2 h = cs_t[e.cs + (k << e.controlled) + e.controlled];
             if (kind == K_H) {
                 const double u = S[0];
                 S[0] = S[2];
                 S[1] = -S[1];
                 S[2] = u;
             } else if (kind == K_PAULI) {
-                const int w = (int)t.x;
+                const int w = (int)h.x;
                 if (w == 2 || w == 3) S[0] = -S[0];
                 if (w == 1 || w == 3) S[1] = -S[1];
                 if (w == 1 || w == 2) S[2] = -S[2];
             } else {
-                const double c = t.x * t.x - t.y * t.y, sn = 2.0 * t.x * t.y;
+                const double c = h.x * h.x - h.y * h.y, sn = 2.0 * h.x * h.y;
                 const double own = kind == K_RX ? S[0] : kind == K_RY ? S[1] : S[2];
                 const int2 sl = *(const int2*)&members[e.first + k].slot;
                 gs[sl.x] = own;
@@ -647,45 +740,45 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         }
     }
     __syncthreads();
-    for (int s = tid; s < a.n_slots; s += nt)
-        if (a.gpart && slots[s].src == S_WEIGHT) a.gpart[(size_t)s * a.B + b] = gs[s];
-    if (a.grad_weights)
-        for (int p = tid; p < a.P; p += nt) {
+    for (int s = tid; s < t->n_slots; s += nt)
+        if (t->gpart && slots[s].src == S_WEIGHT) t->gpart[(size_t)s * t->B + b] = gs[s];
+    if (t->grad_weights)
+        for (int p = tid; p < t->P; p += nt) {
             double acc = 0.0;
-            for (int i = a.w_ptr[p]; i < a.w_ptr[p + 1]; ++i) acc += slots[a.w_slot[i]].scale * gs[a.w_slot[i]];
-            ((Real*)a.grad_weights)[p] = (Real)acc;
+            for (int i = t->w_ptr[p]; i < t->w_ptr[p + 1]; ++i) acc += slots[t->w_slot[i]].scale * gs[t->w_slot[i]];
+            ((Real*)t->grad_weights)[p] = (Real)acc;
         }
-    if (!a.grad_inputs) return;
+    if (!t->grad_inputs) return;
 
     // ---- input gradients: the rotations bound to each feature, and the
     // amplitude embedding's (2 / |x|) (Re lambda_0 - psi_0 L), L = sum psi_0 Re lambda_0
     Real* lx = (Real*)smem;  // Re lambda_0 by amplitude index
     double L = 0.0;
-    if (a.embed == E_AMPLITUDE) {
+    if (t->embed == E_AMPLITUDE) {
         // (the last exchange's reads are over: two barriers since)
         if (active) {
 #pragma unroll
-            for (int i = 0; i < R; ++i) lx[amp_index(a.first_qubit, i)] = lm[i].x;
+            for (int i = 0; i < R; ++i) lx[amp_index(t->first_qubit, i)] = lm[i].x;
         }
         __syncthreads();
         double acc = 0.0;
         for (int j = tid; j < dim; j += nt) acc = fma((double)x[j], (double)lx[j], acc);
         acc = wave_total(acc);
-        if (lane == 0) red[wave] = acc;
+        if (lane == 0) red_t[wave] = acc;
         __syncthreads();
-        for (int w = 0; w < NW; ++w) L += red[w];
+        for (int w = 0; w < NW; ++w) L += red_t[w];
         L = norm > 0 ? L / norm : 0.0;
     }
-    for (int f = tid; f < a.F; f += nt) {
+    for (int f = tid; f < t->F; f += nt) {
         double acc = 0.0;
-        for (int i = a.x_ptr[f]; i < a.x_ptr[f + 1]; ++i) {
-            const int s = a.x_slot[i];
+        for (int i = t->x_ptr[f]; i < t->x_ptr[f + 1]; ++i) {
+            const int s = t->x_slot[i];
             acc += slots[s].scale * gs[s];
         }
-        const int j = f - a.first;
-        if (a.embed == E_AMPLITUDE && j >= 0 && j < dim && norm > 0)
-            acc += 2.0 / norm * ((double)lx[j] - (double)x[j] / norm * L);
-        ((Real*)a.grad_inputs)[b * a.F + f] = (Real)acc;
+        const int j = f - t->first;
+        if (t->embed == E_AMPLITUDE && j >= 0 && j < dim && norm > 0)
+            acc += 2.0 / norm * ((double)lx[j] - (double)x[j] / norm * L) / (1.0 + all);
+        ((Real*)t->grad_inputs)[b * t->F + f] = (Real)acc;
     }
 }
 
@@ -709,6 +802,7 @@ RunLds runs_lds(int dtype, const RunPlan& p, int n_slots, bool bwd) {
     l.mat = put((size_t)(p.n_mat + 4 * 9) * amp);  // a layer fetches the rows of all 9 positions
     l.cs = put((size_t)p.n_cs * 16);
     l.kind = put(p.members.size());
+    l.scale = put(dtype == 0 ? (size_t)(p.n_mat / 4) * 8 : 0);
     l.words = put(p.words.size() * 4);
     l.red = put((size_t)(p.n + 1) * p.n_waves * 8);
     l.go = put(bwd ? (size_t)p.n * real : 0);

@@ -61,7 +61,7 @@ struct DevRunEntry {
     int32_t controlled;
     uint32_t mat, grad;
     int32_t cs;
-    int32_t pad[2];
+    int32_t layer_first, layer_end;  // matrices (of 4 elements) of its step
 };
 
 // One gate of a run, in circuit order. kind K_H, K_RX, K_RY, K_RZ or K_PAULI;

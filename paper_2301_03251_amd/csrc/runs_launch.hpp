@@ -10,7 +10,7 @@ namespace qlayer {
 struct RunLds {
     uint32_t alt;    // bytes from one exchange buffer to the next (0: only one, used with two barriers)
     uint32_t lam;    // bytes from psi's part of an exchange buffer to lambda's
-    uint32_t mat, cs, kind, words, red, go, sum, gs;
+    uint32_t mat, cs, kind, scale, words, red, go, sum, gs;
     uint32_t total;
 };
 
@@ -36,7 +36,7 @@ struct RunArgs {
     int64_t B, v0;
     int32_t vper, bwd;
     int32_t n, log_t, F, P, n_slots;
-    int32_t n_steps, n_entries, n_members, n_words;
+    int32_t n_steps, n_entries, n_members, n_words, n_mats;
     int32_t embed, first;          // initial state (E_*) and its first feature
     uint64_t first_qubit, last_qubit;  // qubit of every position, four bits each: first and last layout
     uint32_t prefix;                   // positions with a prefix run (matrices and sums of layer 0)

@@ -191,3 +191,28 @@ def test_captured_calls():
             for a, b in zip(outs, want):
                 assert torch.equal(a, b)
             r.forward_backward(x, w, g)
+
+
+@pytest.mark.parametrize("n", [10, 12])
+def test_rounding(n):
+    """Relative errors of complex64 in the 2-norm, over six sets of weights of
+    eight layers of RY. An amplitude takes two roundings per run, 2^-24 / sqrt(6)
+    of it in the root mean square, so <Z> is off by sqrt(2 N) of that after N
+    independent ones, and the gradients, whose psi and lambda also come back, by
+    sqrt(3) more. Errors common to all amplitudes (matrices that are not quite
+    rotations) add up past it."""
+    B, layers = 8, 8
+    gates = W.layered_circuit(n, "ry", layers, (W.RY,), W.CZ, "ring")
+    P = layers * n
+    r = Q.Runner(Q.Circuit(n, gates, n, P), "c64")
+    err = {"expz": [], "grad_inputs": [], "grad_weights": []}
+    for seed in range(6):
+        x, w, g = W.random_inputs(B, n, P, n, seed=seed, dtype="c64")
+        want = oracle.run(n, gates, x, w, grad_out=g)
+        got = _fb(r, "c64", x, w, g)
+        for k in err:
+            err[k].append(np.linalg.norm(got[k] - want[k]) / np.linalg.norm(want[k]))
+    once = 2.0 ** -24 / np.sqrt(6.0) * np.sqrt(2 * len(gates[gates[:, 0] == W.RY]))
+    for k, bound in (("expz", once), ("grad_inputs", np.sqrt(3) * once), ("grad_weights", np.sqrt(3) * once)):
+        rms = float(np.sqrt(np.mean(np.square(err[k]))))
+        assert rms <= bound, f"{k}: {rms:.2e} > {bound:.2e}"
