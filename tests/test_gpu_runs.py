@@ -216,3 +216,17 @@ def test_rounding(n):
     for k, bound in (("expz", once), ("grad_inputs", np.sqrt(3) * once), ("grad_weights", np.sqrt(3) * once)):
         rms = float(np.sqrt(np.mean(np.square(err[k]))))
         assert rms <= bound, f"{k}: {rms:.2e} > {bound:.2e}"
+
+
+def test_tile_coefficients_complex128():
+    """A tile rotation's coefficients are within a unit in the last place: an RY
+    on |0> by shears leaves sin(theta / 2), as bound, on |1>."""
+    n, B = 8, 4096
+    r = Q.Runner(Q.Circuit(n, np.array([[W.RY, 0, -1, W.SRC_INPUT, 0]], np.int32), 1, 0, force_tiled=1,
+                           product_prefix=-1), "c128")
+    x = np.random.default_rng(3).uniform(-np.pi, np.pi, (B, 1))
+    psi = r.state(_dev(x, "c128"), None)
+    torch.cuda.synchronize()
+    want = np.sin(x[:, 0].astype(np.longdouble) / 2)
+    ulps = np.abs(psi.real[:, 1].cpu().numpy().astype(np.longdouble) - want) / np.spacing(np.abs(want).astype(np.float64))
+    assert float(ulps.max()) <= 1.0
