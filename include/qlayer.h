@@ -338,7 +338,9 @@ const char* ql_last_error(void);
 /* ---- introspection (host only, no GPU needed) ---------------------------- */
 
 typedef struct {
-    int32_t kernel;        /* 0 = whole state in LDS (one workgroup per sample), 1 = tile passes */
+    int32_t kernel;        /* plan of the handle: 0 = whole state on chip (one workgroup per sample), 1 =
+                              tile passes. Calls of small circuits may take the run kernel
+                              instead: ql_call_kernel tells */
     int32_t n_passes;      /* forward tile passes (1 for the whole-state kernel) */
     int32_t tile_qubits;   /* qubits per tile (log2 amplitudes per workgroup tile) */
     int32_t log_regs;      /* amplitudes per thread = 2^log_regs */
@@ -358,6 +360,19 @@ typedef struct {
 
 int ql_plan_info_get(const ql_circuit* c, ql_dtype dtype, ql_plan_info* out);
 
+/* Which kernel the state of a call runs in: QL_KERNEL_RUNS is the run kernel
+ * (n <= 12: one workgroup per sample, the whole call in one launch, runs of
+ * one-qubit gates as one matrix), the others the handle's plan
+ * (ql_plan_info.kernel). mode: QL_MODE_*, or QL_CALL_STATE for ql_state;
+ * ql_param_shift runs its chunks as QL_MODE_FWD of that many samples. The run
+ * kernel takes circuits below 8 qubits, and of 8 to 12
+ * qubits when every planning option is at its default (the options describe
+ * tile plans), where its tables fit and the batch is not too large for it;
+ * complex64 final states never. */
+enum { QL_KERNEL_WHOLE = 0, QL_KERNEL_TILE = 1, QL_KERNEL_RUNS = 2 };
+enum { QL_CALL_STATE = 3 };
+int ql_call_kernel(const ql_circuit* c, ql_dtype dtype, int64_t batch, int mode, int32_t* out);
+
 /* Forward schedule: pass_of_gate[n_gates] receives the pass that applies each
  * gate, order[n_gates] the gate indices in execution order (pass by pass).
  * Gates of the product-state prefix belong to pass 0 and come first, in gate
@@ -367,15 +382,15 @@ int ql_plan_info_get(const ql_circuit* c, ql_dtype dtype, ql_plan_info* out);
 int ql_plan_schedule(const ql_circuit* c, ql_dtype dtype, int32_t* pass_of_gate,
                      int32_t* order);
 
-/* Algorithmic HBM bytes of the state passes of one call in a mode (QL_MODE_*:
- * reads + writes of psi and lambda by the tile kernel; 0 for the whole-state
- * kernel). */
+/* Algorithmic HBM bytes of the handle's plan in a mode (QL_MODE_*: reads +
+ * writes of psi and lambda by the tile passes; 0 for a whole-state plan; a call
+ * that the run kernel takes moves none). */
 int ql_plan_state_bytes(const ql_circuit* c, ql_dtype dtype, int64_t batch, int mode,
                         double* out);
 
 /* ---- timing (for benchmarks) --------------------------------------------- */
 
-/* Kernel classes: 0 tile passes, 1 whole-state kernel, 2 angle binding and
+/* Kernel classes: 0 tile passes, 1 whole-state and run kernels, 2 angle binding and
  * embedding, 3 reductions. enable = 0 turns timing off; otherwise bit c of
  * enable selects class c (15: all). Every launch of a selected class is then
  * bracketed by HIP events on the call's stream (each pair costs host time,

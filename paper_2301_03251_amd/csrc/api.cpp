@@ -1346,6 +1346,17 @@ int ql_plan_info_get(const ql_circuit* h, ql_dtype dtype, ql_plan_info* out) {
     return QL_OK;
 }
 
+int ql_call_kernel(const ql_circuit* h, ql_dtype dtype, int64_t batch, int mode, int32_t* out) {
+    if (!h || !out) return fail(QL_EINVAL, "NULL argument");
+    if (dtype != QL_C64 && dtype != QL_C128) return fail(QL_EINVAL, "unknown dtype");
+    if (mode < QL_MODE_FWD || mode > QL_CALL_STATE) return fail(QL_EINVAL, "unknown mode");
+    Layout L;
+    int rc = compute_layout(h, (int)dtype, batch, mode == QL_CALL_STATE ? (int)QL_MODE_FWD : mode, L, mode != QL_CALL_STATE);
+    if (rc) return rc;
+    *out = L.route == RUNS ? QL_KERNEL_RUNS : plan_of(h, (int)dtype, L.route).whole_state ? QL_KERNEL_WHOLE : QL_KERNEL_TILE;
+    return QL_OK;
+}
+
 int ql_plan_schedule(const ql_circuit* h, ql_dtype dtype, int32_t* pass_of_gate, int32_t* order) {
     if (!h || !pass_of_gate || !order) return fail(QL_EINVAL, "NULL argument");
     if (dtype != QL_C64 && dtype != QL_C128) return fail(QL_EINVAL, "unknown dtype");

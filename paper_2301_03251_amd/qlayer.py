@@ -18,6 +18,8 @@ LIB_PATH = os.path.join(_HERE, "libqlayer.so")
 
 C64, C128 = 0, 1
 MODE_FWD, MODE_FWD_BWD, MODE_FWD_BWD_KEEP = 0, 1, 2
+CALL_STATE = 3  # QL_CALL_STATE of qlayer.h
+KERNELS = ("whole", "tile", "runs")  # QL_KERNEL_*
 STATIC_SCRATCH_BYTES = 64 << 20  # QL_STATIC_SCRATCH_BYTES of qlayer.h
 H, RX, RY, RZ, CNOT, CZ, CRX, CRY, CRZ, PAULI = range(10)
 SRC_NONE, SRC_INPUT, SRC_WEIGHT = 0, 1, 2
@@ -56,7 +58,7 @@ EXPORTS = ("ql_circuit_create", "ql_circuit_create_ex", "ql_circuit_create_desc"
            "ql_workspace_bytes", "ql_forward", "ql_forward_backward", "ql_last_error",
            "ql_param_shift_workspace_bytes", "ql_param_shift", "ql_state_workspace_bytes",
            "ql_state", "ql_sample_workspace_bytes", "ql_sample",
-           "ql_plan_info_get", "ql_plan_schedule", "ql_plan_state_bytes",
+           "ql_plan_info_get", "ql_call_kernel", "ql_plan_schedule", "ql_plan_state_bytes",
            "ql_timing_enable", "ql_timing_read")
 
 
@@ -90,6 +92,7 @@ def load():
     lib.ql_last_error.argtypes = []
     lib.ql_last_error.restype = ctypes.c_char_p
     lib.ql_plan_info_get.argtypes = [P, ctypes.c_int, ctypes.POINTER(_PlanInfo)]
+    lib.ql_call_kernel.argtypes = [P, ctypes.c_int, I64, ctypes.c_int, ctypes.POINTER(I32)]
     lib.ql_plan_schedule.argtypes = [P, ctypes.c_int, P, P]
     lib.ql_plan_state_bytes.argtypes = [P, ctypes.c_int, I64, ctypes.c_int,
                                         ctypes.POINTER(ctypes.c_double)]
@@ -99,7 +102,7 @@ def load():
                  "ql_workspace_bytes", "ql_forward",
                  "ql_forward_backward", "ql_param_shift_workspace_bytes", "ql_param_shift",
                  "ql_state_workspace_bytes", "ql_state", "ql_sample_workspace_bytes", "ql_sample",
-                 "ql_plan_info_get", "ql_plan_schedule",
+                 "ql_plan_info_get", "ql_call_kernel", "ql_plan_schedule",
                  "ql_plan_state_bytes", "ql_timing_enable", "ql_timing_read"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib
@@ -168,6 +171,12 @@ class Circuit:
         _check(load().ql_plan_info_get(self._h, _dt(dtype), ctypes.byref(info)))
         return {f: getattr(info, f) for f, _ in _PlanInfo._fields_}
 
+    def call_kernel(self, dtype, batch, mode=MODE_FWD_BWD) -> str:
+        """The kernel a call's state runs in (mode: MODE_* or CALL_STATE)."""
+        out = ctypes.c_int32()
+        _check(load().ql_call_kernel(self._h, _dt(dtype), int(batch), int(mode), ctypes.byref(out)))
+        return KERNELS[out.value]
+
     def schedule(self, dtype):
         G = self.gates.shape[0]
         pog = np.zeros(max(G, 1), dtype=np.int32)
@@ -183,7 +192,7 @@ class Circuit:
 
     def timing(self, enable: bool, classes: int = 0xF):
         """Bracket the launches of the kernel classes in the mask `classes`
-        (bit 0 tile passes, 1 whole-state kernel, 2 binding, 3 reductions)."""
+        (bit 0 tile passes, 1 whole-state and run kernels, 2 binding, 3 reductions)."""
         _check(load().ql_timing_enable(self._h, int(classes) & 0xF if enable else 0))
 
     def timing_read(self):

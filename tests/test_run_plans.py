@@ -56,3 +56,19 @@ def test_run_plans_on_the_host(tmp_path):
     r = subprocess.run([exe, path, "v"], capture_output=True, text=True, timeout=600)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     assert "cases 123 " in r.stdout
+
+
+@pytest.mark.parametrize("n,options,dtype,mode,want", [
+    (4, {}, "c64", 1, "runs"), (7, {"force_tiled": 1}, "c128", 0, "runs"), (10, {}, "c64", 2, "runs"),
+    (12, {}, "c128", 0, "runs"), (10, {"rz_groups": -1}, "c64", 1, "tile"), (9, {"force_tiled": 1}, "c64", 0, "tile"),
+    (11, {"force_tiled": -1}, "c128", 1, "whole"), (13, {}, "c64", 1, "tile"),
+    (5, {}, "c64", 3, "whole"), (9, {}, "c64", 3, "tile"), (9, {}, "c128", 3, "runs")])
+def test_call_kernel(n, options, dtype, mode, want):
+    """Which kernel takes a call, and the errors of asking."""
+    Q = pytest.importorskip("paper_2301_03251_amd")
+    c = Q.Circuit(n, W.random_circuit(n, 30, 3, 4, seed=n), 3, 4, **options)
+    assert c.call_kernel(dtype, 8, mode) == want
+    for batch, bad in ((0, mode), (8, 4), (8, -1)):
+        with pytest.raises(Q.QLError) as e:
+            c.call_kernel(dtype, batch, bad)
+        assert e.value.code == -1
