@@ -154,9 +154,11 @@ typedef struct {
     int32_t log_threads;        /* threads per workgroup = 2^log_threads (6..9) */
     int32_t low_qubits;         /* qubits 0..low_qubits-1 are in every tile (1..8) */
     int32_t max_gates_per_pass; /* cap on gates per tile pass (>= 1) */
-    int32_t force_tiled;        /* kernel choice: 0 library default (register tiles for
-                                   n >= 8, a whole-state kernel below), 1 register
-                                   tiles, -1 a whole-state kernel whenever it fits
+    int32_t force_tiled;        /* kernel choice: 0 library default (the run kernel for
+                                   n <= 12 where it fits and pays, see
+                                   ql_call_kernel; else register tiles for n >= 8, a
+                                   whole-state kernel below), 1 register tiles for
+                                   n >= 8, -1 a whole-state kernel whenever it fits
                                    (n <= 12 for QL_C64, n <= 11 for QL_C128). The
                                    whole-state kernels hold a sample in one
                                    wavefront's registers for n <= 8 (in LDS for
@@ -365,7 +367,7 @@ int ql_plan_info_get(const ql_circuit* c, ql_dtype dtype, ql_plan_info* out);
  * one-qubit gates as one matrix), the others the handle's plan
  * (ql_plan_info.kernel). mode: QL_MODE_*, or QL_CALL_STATE for ql_state;
  * ql_param_shift runs its chunks as QL_MODE_FWD of that many samples. The run
- * kernel takes circuits below 8 qubits, and of 8 to 12
+ * kernel takes circuits below 8 qubits unless force_tiled is -1, and of 8 to 12
  * qubits when every planning option is at its default (the options describe
  * tile plans), where its tables fit and the batch is not too large for it;
  * complex64 final states never. */

@@ -1101,14 +1101,15 @@ Options to_options(const ql_options* o) {
 }
 
 // Whether the run kernel takes a circuit's calls: small states planned with
-// the default options (the options describe tile plans), whose matrices and
-// sums fit in LDS beside the state.
+// the default options (the options describe tile plans; force_tiled = -1 asks
+// for a whole-state kernel), whose matrices and sums fit in LDS beside the
+// state.
 void choose_runs(ql_circuit* h) {
     const Circuit& c = h->c;
     const Options& o = c.opts;
     const bool plain = !o.log_regs && !o.log_threads && !o.low_qubits && !o.max_gates_per_pass && !o.force_tiled &&
                        !o.wg_per_sample && !o.rz_groups && !o.pass_search && !o.product_prefix && !o.cz_groups;
-    if (c.n > RUNS_MAX_QUBITS || (c.n >= 8 && !plain)) return;
+    if (c.n > RUNS_MAX_QUBITS || (c.n >= 8 && !plain) || o.force_tiled < 0) return;
     for (int dt = 0; dt < 2; dt++) {
         if (dt == 1 && runs_log_regs(c.n, 0) == runs_log_regs(c.n, 1)) h->rp[1] = h->rp[0];
         else build_run_plan(c, runs_log_regs(c.n, dt), h->rp[dt]);

@@ -230,3 +230,30 @@ def test_tile_coefficients_complex128():
     want = np.sin(x[:, 0].astype(np.longdouble) / 2)
     ulps = np.abs(psi.real[:, 1].cpu().numpy().astype(np.longdouble) - want) / np.spacing(np.abs(want).astype(np.float64))
     assert float(ulps.max()) <= 1.0
+
+
+# complex64, 2000 gates: an amplitude takes up to 4000 roundings of 2^-24 / sqrt(6)
+# in the root mean square, 1.5e-6 of it together, psi and lambda each; ten times
+# both at one value. complex128 keeps its bound.
+LONG = {"c64": 3e-5, "c128": 1e-12}
+
+
+@pytest.mark.parametrize("n,G,B,dtype,kernels", [
+    (7, 2000, 3, "c128", ("whole", "whole")), (6, 1500, 3, "c64", ("whole", "whole")),
+    (7, 1200, 2, "c64", ("runs", "whole")), (4, 1000, 2, "c128", ("runs", "whole")),
+    (6, 400, 2100, "c64", ("whole", "whole"))])
+def test_long_small_circuits(n, G, B, dtype, kernels):
+    """Below 8 qubits: circuits too long for the run kernel's tables, some only
+    with a backward (the one-wavefront kernel takes the rest), and many forward
+    circuits on request (the LDS kernel)."""
+    F, P = 100, 400
+    gates = W.random_circuit(n, G, F, P, seed=G + n, kinds=ALL)
+    circ = Q.Circuit(n, gates, F, P, **({"force_tiled": -1} if B > 2000 else {}))
+    assert tuple(circ.call_kernel(dtype, B, m) for m in (Q.MODE_FWD, Q.MODE_FWD_BWD)) == kernels
+    x, w, g = W.random_inputs(B, F, P, n, seed=G, dtype=dtype)
+    r = Q.Runner(circ, dtype)
+    want = oracle.run(n, gates, x, w, grad_out=g)
+    check(_fb(r, dtype, x, w, g), want, LONG[dtype], f"n={n} {dtype} G={G}")
+    e = r.forward(_dev(x, dtype), _dev(w, dtype))
+    torch.cuda.synchronize()
+    close(e.cpu().double().numpy(), want["expz"], LONG[dtype], f"n={n} {dtype} G={G}", "forward")

@@ -61,7 +61,8 @@ def test_run_plans_on_the_host(tmp_path):
 @pytest.mark.parametrize("n,options,dtype,mode,want", [
     (4, {}, "c64", 1, "runs"), (7, {"force_tiled": 1}, "c128", 0, "runs"), (10, {}, "c64", 2, "runs"),
     (12, {}, "c128", 0, "runs"), (10, {"rz_groups": -1}, "c64", 1, "tile"), (9, {"force_tiled": 1}, "c64", 0, "tile"),
-    (11, {"force_tiled": -1}, "c128", 1, "whole"), (13, {}, "c64", 1, "tile"),
+    (11, {"force_tiled": -1}, "c128", 1, "whole"), (5, {"force_tiled": -1}, "c64", 1, "whole"),
+    (8, {"force_tiled": -1}, "c128", 0, "whole"), (13, {}, "c64", 1, "tile"),
     (5, {}, "c64", 3, "whole"), (9, {}, "c64", 3, "tile"), (9, {}, "c128", 3, "runs")])
 def test_call_kernel(n, options, dtype, mode, want):
     """Which kernel takes a call, and the errors of asking."""
