@@ -206,7 +206,7 @@ bool mul_ok(size_t a, size_t b, size_t& out) {
 struct ql_circuit {
     Circuit c;
     RunPlan rp[2];         // per dtype
-    bool runs[2][2] = {};  // [dtype][with a backward]: the run kernel can take the call
+    int runs[2][2] = {};   // [dtype][with a backward]: the run kernel's workgroups per CU (0: it cannot take the call)
     Tables t[2][3];        // [dtype][Route]
     // device copies of the tables (device, memory), see place_tables
     std::mutex res_mu;
@@ -223,29 +223,50 @@ struct ql_circuit {
 
 namespace {
 
-// Whether the run kernel takes a call. Below 32 KiB of state per sample (n <=
-// 10, and 11 in complex64) it is faster at every batch (1.0 to 3.4 times the
-// tile kernel; circuits of 4 layers, batches of 256 to 30000). Larger states
-// fill the chip with fewer samples, and from there on the tile kernel's 3 FMAs
-// per RY cost less than a matrix's 8. Tile / run kernel, us, for the circuits
-// of layers that the run kernel gains least on: complex64, 12 qubits, forward
-// of 2000 samples 141 (noise) / 144, of 1000 95 / 58, step of 512 193 / 154, of 700
-// (noise) 181 / 216; complex128, 11 qubits, forward of 512 samples 101 / 88,
-// of 2000 145 / 170, step of 512 181 / 132, of 700 (noise) 167 / 179; 12
-// qubits, forward of 768 samples (noise) 102 / 99, of 2000 247 / 262. Runs
-// under controls take a step each, a layer's runs share one, so circuits with
-// such runs turn earlier (400 random gates): complex64, forward of 512 samples
-// 239 / 239, of 768 297 / 353, step of 256 459 / 453, of 700 (150 gates) 343 /
-// 447; complex128, 11 qubits, forward of 512 250 / 218, of 768 276 / 318, step
-// of 256 511 / 485, of 700 (150 gates) 299 / 413; 12 qubits, forward of 512
-// 295 / 333, step of 256 622 / 613.
+// Whether the run kernel takes a call: two rules, on the state's size and on the
+// LDS of a workgroup.
+//
+// States of 32 KiB and more per sample fill the chip with fewer samples, and
+// from there on the tile kernel's 3 FMAs per RY cost less than a matrix's 8.
+// Tile / run kernel, us, for the circuits of layers that the run kernel gains
+// least on: complex64, 12 qubits, forward of 2000 samples 141 (noise) / 144, of
+// 1000 95 / 58, step of 512 193 / 154, of 700 (noise) 181 / 216; complex128, 11
+// qubits, forward of 512 samples 101 / 88, of 2000 145 / 170, step of 512 181 /
+// 132, of 700 (noise) 167 / 179; 12 qubits, forward of 768 samples (noise) 102
+// / 99, of 2000 247 / 262. Runs under controls take a step each, a layer's runs
+// share one, so circuits with such runs turn earlier (400 random gates):
+// complex64, forward of 512 samples 239 / 239, of 768 297 / 353, step of 256
+// 459 / 453, of 700 (150 gates) 343 / 447; complex128, 11 qubits, forward of
+// 512 250 / 218, of 768 276 / 318, step of 256 511 / 485, of 700 (150 gates)
+// 299 / 413; 12 qubits, forward of 512 295 / 333, step of 256 622 / 613.
+//
+// A workgroup's LDS holds the matrices, tables and sums of its circuit too, so
+// long circuits leave few wavefronts on a CU, each waiting on its own steps.
+// While the batch is on the chip in two rounds the run kernel is faster all the
+// same; above that with enough wavefronts, or with layers of many gates per
+// step. Other / run kernel, us, random gates with controlled rotations unless
+// said: complex64, 9 qubits, 400 gates, 1 workgroup of 2 wavefronts per CU:
+// step of 512 400 / 420, of 1024 481 / 835, of 2000 665 / 1655; 10 qubits, 400
+// gates, 4 wavefronts: step of 512 437 / 399, of 1024 556 / 790; 8 wavefronts:
+// forward of 2000 366 / 296; 100 gates, 12 wavefronts: step of 2000 275 / 274;
+// 40 layers of RX RY RZ, 4 wavefronts: step of 2000 1996 / 1731; 11 qubits, 200
+// gates without controls, 16 wavefronts: step of 2000 520 / 440; complex128, 9
+// qubits, 12 layers of RY, 6 wavefronts: step of 2000 321 / 269; 200 gates, 6
+// wavefronts: forward of 2000 142 / 154, 2 wavefronts: step of 1024 334 / 509.
+// Below 8 qubits the whole-state kernels hold no tables: 6 qubits, complex64,
+// 800 gates, 1 wavefront: forward of 1024 198 / 466; 400 gates, 3 wavefronts:
+// forward of 1024 102 / 124, step of 1024 403 / 384, of 4000 813 / 1495; 4
+// wavefronts (4 qubits): forward of 4000 301 / 271.
 bool runs_take(const ql_circuit* h, int dt, int64_t B, int mode) {
-    const bool bwd = mode != QL_MODE_FWD;
-    if (!h->runs[dt][bwd]) return false;
+    const bool bwd = mode != QL_MODE_FWD, small = h->c.n < 8;
+    const int64_t per_cu = h->runs[dt][bwd];
+    if (!per_cu) return false;
+    const RunPlan& p = h->rp[dt];
     const int64_t bytes = (int64_t)(dt == 0 ? 8 : 16) << h->c.n;
-    if (bytes < 32768) return true;
-    if (h->rp[dt].controlled) return B <= (bwd || bytes > 32768 ? 256 : 512);
-    return B <= (bwd ? 512 : dt == 1 ? 768 : 1536);
+    if (bytes >= 32768 && p.controlled && B > (bwd || bytes > 32768 ? 256 : 512)) return false;
+    if (bytes >= 32768 && B > (bwd ? 512 : dt == 1 ? 768 : 1536)) return false;
+    if (B <= (small && !bwd ? 256 : 512) * per_cu || p.members.size() >= 8 * p.steps.size()) return true;
+    return per_cu * p.n_waves >= (bwd ? (p.controlled ? 12 : 6) : small ? 4 : 6);
 }
 
 // The kernels of a call. Final states (psi_out) of complex64 take those that
@@ -1115,7 +1136,7 @@ void choose_runs(ql_circuit* h) {
         else build_run_plan(c, runs_log_regs(c.n, dt), h->rp[dt]);
         if (!h->rp[dt].ok) continue;
         for (int bwd = 0; bwd < 2; bwd++)
-            h->runs[dt][bwd] = runs_lds(dt, h->rp[dt], (int)c.slots.size(), bwd != 0).total <= RUNS_LDS_MAX;
+            h->runs[dt][bwd] = (int)(RUNS_LDS_MAX / runs_lds(dt, h->rp[dt], (int)c.slots.size(), bwd != 0).total);
     }
 }
 

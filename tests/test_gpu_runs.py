@@ -257,3 +257,23 @@ def test_long_small_circuits(n, G, B, dtype, kernels):
     e = r.forward(_dev(x, dtype), _dev(w, dtype))
     torch.cuda.synchronize()
     close(e.cpu().double().numpy(), want["expz"], LONG[dtype], f"n={n} {dtype} G={G}", "forward")
+
+
+@pytest.mark.parametrize("n,dtype,limit", [(9, "c64", 512), (9, "c128", 512), (6, "c64", 1024)])
+def test_lds_rule(n, dtype, limit):
+    """On both sides of the batch up to which a long circuit keeps the run
+    kernel: rows agree, and the weight gradients of the larger batch are those of
+    the smaller plus the last row's (from the oracle)."""
+    F, P = 100, 300
+    gates = W.random_circuit(n, 400, F, P, seed=n, kinds=ALL)
+    circ = Q.Circuit(n, gates, F, P)
+    other = "tile" if n >= 8 else "whole"
+    assert (circ.call_kernel(dtype, limit), circ.call_kernel(dtype, limit + 1)) == ("runs", other)
+    x, w, g = W.random_inputs(limit + 1, F, P, n, seed=n, dtype=dtype)
+    r = Q.Runner(circ, dtype)
+    big, small = _fb(r, dtype, x, w, g), _fb(r, dtype, x[:limit], w, g[:limit])
+    last = oracle.run(n, gates, x[-1:], w, grad_out=g[-1:])
+    for k in ("expz", "grad_inputs"):
+        close(big[k][:limit], small[k], 2 * TOL[dtype], f"n={n} {dtype}", k)
+        close(big[k][-1:], last[k], TOL[dtype], f"n={n} {dtype}", k)
+    close(big["grad_weights"], small["grad_weights"] + last["grad_weights"], 2 * TOL[dtype], f"n={n} {dtype}", "grad_weights")

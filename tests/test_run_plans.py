@@ -73,3 +73,22 @@ def test_call_kernel(n, options, dtype, mode, want):
         with pytest.raises(Q.QLError) as e:
             c.call_kernel(dtype, batch, bad)
         assert e.value.code == -1
+
+
+@pytest.mark.parametrize("n,circuit,dtype,mode,runs,other", [
+    (9, "random 400", "c64", 1, 512, 513), (10, "random 400", "c64", 1, 512, 1024), (9, "random 400", "c128", 1, 512, 513),
+    (10, "random 400", "c64", 0, 3000, None), (6, "random 700", "c64", 0, 256, 4000), (6, "random 300", "c64", 1, 1024, 4000),
+    (10, "layers 20", "c64", 1, 3000, None), (4, "layers 2", "c128", 1, 20000, None), (7, "layers 4", "c64", 0, 40000, None)])
+def test_long_circuits_turn_earlier(n, circuit, dtype, mode, runs, other):
+    """The LDS of long irregular circuits limits the batch that the run kernel
+    takes; layered ones keep it at every batch below 32 KiB of state."""
+    Q = pytest.importorskip("paper_2301_03251_amd")
+    kind, size = circuit.split()
+    if kind == "random":
+        gates, F, P = W.random_circuit(n, int(size), 5, 9, seed=n, kinds=ALL), 5, 9
+    else:
+        gates, F, P = W.layered_circuit(n, "ry", int(size), (W.RX, W.RY, W.RZ), W.CNOT, "linear"), n, 3 * n * int(size)
+    c = Q.Circuit(n, gates, F, P)
+    assert c.call_kernel(dtype, runs, mode) == "runs"
+    if other:
+        assert c.call_kernel(dtype, other, mode) == ("tile" if n >= 8 else "whole")
