@@ -253,8 +253,9 @@ int ql_forward_backward(const ql_circuit* c, ql_dtype dtype, int64_t batch,
  * workspace: the call runs in a static device buffer of
  * QL_STATIC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends, and returns QL_ENOMEM (before launching anything)
- * when the circuit, dtype and batch need more than that
- * (ql_workspace_bytes(..., QL_MODE_FWD_BWD) tells). It calls no device or
+ * when the circuit, dtype and batch need more than that (they never do when
+ * ql_workspace_bytes(..., QL_MODE_FWD_BWD) is no more; a tile plan may fit with
+ * somewhat more, in a layout of less workspace). It calls no device or
  * host allocator: the plan tables are copied from the handle's own host copy.
  * The caller still provides inputs and outputs. All calls on one GPU share
  * that GPU's buffer: calls that overlap in time on one GPU (other streams,

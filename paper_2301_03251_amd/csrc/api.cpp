@@ -282,10 +282,13 @@ const Plan& plan_of(const ql_circuit* h, int dt, int route) {
 }
 
 // own_psi = false: the caller's state buffer holds psi (ql_state), so the
-// workspace has none.
-int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, bool own_psi = true) {
+// workspace has none. lean: the tile layout of least workspace (no rotation
+// runs, whose angles and axes are per sample, and no extra workgroups).
+int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, bool own_psi = true,
+                   bool lean = false) {
     const Circuit& c = h->c;
-    const int route = route_of(h, dt, B, mode, !own_psi);
+    int route = route_of(h, dt, B, mode, !own_psi);
+    if (lean && route == TILE && !h->c.plain[dt].passes.empty()) route = PLAIN;
     const Plan& pl = plan_of(h, dt, route);
     const size_t amp = dt == 0 ? 8 : 16;
     if (B < 1) return fail(QL_EINVAL, "batch must be >= 1");
@@ -316,9 +319,9 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
         // -> 384; 64 samples of 8 tiles: 434 -> 405; with 1024 tiles it would
         // cost 5 to 12 %). Forward passes (else two tiles per iteration): up to
         // one workgroup per CU.
-        if (!c.opts.wg_per_sample && tiles <= 256 / B) nwg = tiles;
+        if (!lean && !c.opts.wg_per_sample && tiles <= 256 / B) nwg = tiles;
         L.n_wg_fwd = (int)nwg;
-        if (mode != QL_MODE_FWD && !c.opts.wg_per_sample && tiles <= 512 / B) nwg = tiles;
+        if (!lean && mode != QL_MODE_FWD && !c.opts.wg_per_sample && tiles <= 512 / B) nwg = tiles;
         if (nwg * B > (int64_t)INT32_MAX) return fail(QL_ENOMEM, "grid too large");
         L.n_wg = (int)nwg;
     }
@@ -328,7 +331,7 @@ int compute_layout(const ql_circuit* h, int dt, int64_t B, int mode, Layout& L, 
     off = align256(off + T.blob.size());
     L.coef = off;
     if (!mul_ok((size_t)B * (size_t)std::max(1, (int)c.slots.size()), amp, sz)) return fail(QL_ENOMEM, "size overflow");
-    if (!runs) off = align256(off + sz);
+    if (pl.whole_state && !runs) off = align256(off + sz);
     if (!one) {
         // per-sample op records (16 bytes fp32 / 32 bytes fp64) plus an end record
         L.opc = off;
@@ -902,6 +905,7 @@ int run(const ql_circuit* hc, ql_dtype dtype, int64_t B, int mode, const void* i
     Layout L;
     int rc = compute_layout(h, dt, B, mode, L);
     if (rc) return rc;
+    if (no_alloc && ws_bytes < L.total && (rc = compute_layout(h, dt, B, mode, L, true, true))) return rc;
     if (bwd) {  // keep the forward states when the workspace holds them
         Layout K;
         if (compute_layout(h, dt, B, QL_MODE_FWD_BWD_KEEP, K) == QL_OK && K.n_keep > 0 && ws_bytes >= K.total)
@@ -1245,6 +1249,8 @@ int ql_forward_backward_static(const ql_circuit* h, ql_dtype dtype, int64_t batc
     Layout L;
     int rc = compute_layout(h, (int)dtype, batch, QL_MODE_FWD_BWD, L);
     if (rc) return rc;
+    if (L.total > QL_STATIC_SCRATCH_BYTES && (rc = compute_layout(h, (int)dtype, batch, QL_MODE_FWD_BWD, L, true, true)))
+        return rc;
     if (L.total > QL_STATIC_SCRATCH_BYTES)
         return fail(QL_ENOMEM, "ql_forward_backward_static needs " + std::to_string(L.total) +
                                    " bytes of scratch, above its static maximum of " +

@@ -100,3 +100,23 @@ def test_static_refuses_beyond_its_maximum():
     with pytest.raises(Q.QLError) as e:
         Q.Runner(circ, "c64").forward_backward_static(_dev(x, "c64"), _dev(w, "c64"), _dev(g, "c64"))
     assert e.value.code == -2
+
+
+@pytest.mark.parametrize("n,B,dtype", [(12, 4500, "c64"), (13, 224, "c128")])
+def test_static_near_its_maximum(n, B, dtype):
+    """Batches whose workspace is past the static maximum with the angles and
+    axes of rotation runs, and within it without (6 and 8 layers of three
+    rotations): the first and last rows against a call of their own."""
+    layers = 6 if n == 12 else 8
+    gates = W.layered_circuit(n, "h_rz", layers, (W.RX, W.RY, W.RZ), W.CNOT, "brick")
+    P = 3 * layers * n
+    circ = Q.Circuit(n, gates, n, P)
+    assert circ.workspace_bytes(dtype, B, Q.MODE_FWD_BWD) > Q.STATIC_SCRATCH_BYTES
+    x, w, g = W.random_inputs(B, n, P, n, seed=n, dtype=dtype)
+    got = _static(circ, dtype, x, w, g)
+    for rows in (slice(0, 2), slice(B - 2, B)):
+        want = _workspace(circ, dtype, x[rows], w, g[rows])
+        for k in ("expz", "grad_inputs"):
+            check({k: got[k][rows]}, want, 2 * TOL[dtype], f"static n={n} {dtype} B={B}", keys=(k,))
+    whole = _workspace(circ, dtype, x, w, g)
+    check(got, whole, 2 * TOL[dtype], f"static n={n} {dtype} B={B}")
