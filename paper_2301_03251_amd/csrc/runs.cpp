@@ -19,7 +19,7 @@ std::vector<Item> items_of(const Circuit& c) {
     auto member = [&](const Gate& g, int slot2) {
         const double scale = g.slot >= 0 ? c.slots[g.slot].scale : 1.0;
         const int src = g.slot >= 0 ? c.slots[g.slot].src : (int)S_NONE;
-        return DevRunMember{g.kind, g.slot, slot2, 0, src, g.index, scale};
+        return DevRunMember{g.slot, slot2, g.kind, 0, src, g.index, scale};
     };
     for (size_t i = 0; i < c.gates.size(); i++) {
         const Gate& g = c.gates[i];

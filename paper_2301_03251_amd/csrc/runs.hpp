@@ -21,6 +21,7 @@
 // state that the kernel writes directly ("prefix" runs).
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 #include <vector>
 
@@ -71,10 +72,15 @@ struct DevRunEntry {
 // + slot2 for control bit 0 and slot - slot2 for control bit 1. `cs` is the
 // index of its (cos, sin) pairs.
 struct DevRunMember {
-    int32_t kind, slot, slot2, cs;
+    int32_t slot, slot2;  // read as a pair
+    int32_t kind, cs;
     int32_t src, index;
     double scale;
 };
+
+static_assert(offsetof(DevRunMember, slot) % 8 == 0 && offsetof(DevRunMember, slot2) == offsetof(DevRunMember, slot) + 4 &&
+                  sizeof(DevRunMember) % 8 == 0,
+              "a member's slots are read as one aligned pair");
 
 // A step as the kernel reads it: op | mat << 8, and for a run or layer ctl |
 // grad << 9, for an exchange its sign table + 1 (0: no signs).
