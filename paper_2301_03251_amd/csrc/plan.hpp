@@ -91,8 +91,8 @@ struct DevFuse {
     int32_t slot;
     uint32_t gslot;
 };
-// A rotation run: RUN_MIN_COST or more of consecutive rotations of one qubit
-// on a register bit become RZ(alpha) RY(beta) RZ(gamma), angles from
+// A rotation run: consecutive rotations of one qubit on a register bit that cost
+// more than RZ RY RZ become RZ(alpha) RY(beta) RZ(gamma), angles from
 // k_bind_runs per sample. Their "slots" are RUN_SLOT + 4 * run + (0 alpha, 1
 // beta, 2 gamma). The gradient of every rotation of the run is the scalar
 // product of the run's three sums with an axis (k_bind_runs).

@@ -825,9 +825,12 @@ static hipError_t launch_runs_t(int log_r, const RunArgs& a, int threads, hipStr
         QL_LR(3, 512);
     } else if (log_r == 2 && threads <= 256) {
         QL_LR(2, 256);
-    } else if (log_r == 2 && threads <= 512) {
-        QL_LR(2, 512);
     } else {
+        if constexpr (sizeof(Real) == 4)
+            if (log_r == 2 && threads <= 512) {  // 11 qubits
+                QL_LR(2, 512);
+                return hipGetLastError();
+            }
         return hipErrorInvalidValue;
     }
 #undef QL_LR
@@ -844,8 +847,8 @@ hipError_t configure_runs_kernels(size_t max_lds) {
     if (e == hipSuccess)                                                                                 \
         e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_runs<REAL, LR, MT>),                     \
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_lds);
-#define QL_ATS(REAL) QL_AT(REAL, 0, 64) QL_AT(REAL, 1, 64) QL_AT(REAL, 2, 64) QL_AT(REAL, 2, 256) QL_AT(REAL, 2, 512) QL_AT(REAL, 3, 512)
-    QL_ATS(float)
+#define QL_ATS(REAL) QL_AT(REAL, 0, 64) QL_AT(REAL, 1, 64) QL_AT(REAL, 2, 64) QL_AT(REAL, 2, 256) QL_AT(REAL, 3, 512)
+    QL_ATS(float) QL_AT(float, 2, 512)
     QL_ATS(double)
 #undef QL_ATS
 #undef QL_AT
