@@ -36,13 +36,14 @@
  * caller. The caller also provides the device workspace (size from
  * ql_workspace_bytes). The library writes only the workspace and the outputs.
  * It allocates device memory in one place: the first call of a dtype on a
- * handle and device makes a device copy of the handle's plan tables (some KiB),
- * which later calls read and ql_circuit_destroy frees. Where nothing may be
- * allocated (a stream in capture, ql_forward_backward_static), where that
- * allocation fails, or where the stream belongs to another device than the
- * current one, the call copies the tables to the workspace instead. A graph
- * captured from calls on a handle reads the handle's tables when it is
- * replayed: keep the handle until the last replay has ended. Outputs are
+ * handle and device queues a device copy of the handle's plan tables (some KiB),
+ * which later calls read and ql_circuit_destroy frees.
+ * Until that copy has arrived, and where no device memory may be
+ * allocated (a stream in capture, ql_forward_backward_static), an allocation
+ * fails, or the stream belongs to another device than the current one, the call
+ * copies the tables to the workspace instead. A graph captured from calls on a
+ * handle reads the handle's tables when it is replayed: keep the handle until
+ * the last replay has ended. Outputs are
  * overwritten (not accumulated). Buffers must not alias each other or the
  * workspace.
  *

@@ -3,8 +3,9 @@
 // One call = angle binding, then either one whole-state launch (small n) or
 // the forward tile passes, a fused pass (last forward pass + <Z> partials +
 // lambda seed + first backward pass), the remaining backward passes in reverse
-// order, and the final reductions -- all on the caller's stream, no host
-// synchronisation, no device allocation.
+// order, and the final reductions; or one launch of the run kernel (small
+// states). All on the caller's stream without host synchronisation; the only
+// allocations are the plan tables' (see place_tables).
 #include "qlayer.h"
 
 #include <hip/hip_runtime.h>
@@ -35,8 +36,7 @@ int fail(int code, const std::string& msg) {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Device tables of one dtype's plan, packed into one blob that each call
-// copies into the head of the workspace.
+// Device tables of one dtype's plan, packed into one blob (see place_tables).
 struct Tables {
     std::vector<uint8_t> blob;
     size_t off_pass = 0, off_phase = 0, off_ops = 0, off_gslot = 0, off_slots = 0;
@@ -208,9 +208,15 @@ struct ql_circuit {
     RunPlan rp[2];         // per dtype
     int runs[2][2] = {};   // [dtype][with a backward]: the run kernel's workgroups per CU (0: it cannot take the call)
     Tables t[2][3];        // [dtype][Route]
-    // device copies of the tables (device, memory), see place_tables
+    // copies of the tables on the devices (see place_tables)
+    struct Resident {
+        int dev = 0;
+        void* p = nullptr;
+        hipEvent_t ready = nullptr;  // after the copy
+        bool arrived = false;        // `ready` was seen completed
+    };
     std::mutex res_mu;
-    std::vector<std::pair<int, void*>> resident[2][3];
+    std::vector<Resident> resident[2][3];
     // timing
     int timing = 0;
     struct Ev {
@@ -519,37 +525,59 @@ Ctx context(ql_circuit* h, int dt, const Layout& L, void* ws, hipStream_t stream
             L.route == RUNS};
 }
 
-// The call's plan tables on the device (x.tab): the handle's own copy, made on
-// the first call on each device and kept until the handle is destroyed; in the
-// workspace, copied on the call's stream, where nothing may be allocated (the
-// allocation-free entry point, a stream being captured), the stream belongs to
-// another device than the current one or the allocation fails. (A copy and an
-// event on every call cost 10 us of the smallest calls.)
+// Allocations beside a stream in capture, of this or another thread.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// The call's plan tables on the device (x.tab): the handle's own copy, queued
+// by the first call on each device and kept until the handle is destroyed. The
+// call that queues it reads it in stream order, others once it has arrived.
+// Until then, and where nothing may be allocated (the allocation-free entry
+// point), the stream is in capture before the copy has arrived or belongs to
+// another device than the current one, or an allocation fails, the call copies
+// the tables to its workspace. No call waits on the host. (A copy and an event
+// on every call cost 10 us of the smallest calls.)
 int place_tables(Ctx& x, int dev) {
     const Tables& T = x.T;
-    auto& copies = x.h->resident[x.dt][x.L.route];
-    hipDevice_t at = dev;  // a null stream is the current device's
-    if (x.stream && hipStreamGetDevice(x.stream, &at) != hipSuccess) {
-        (void)hipGetLastError();
-        at = -1;
-    }
-    if (!x.no_alloc && at == dev) {
+    if (!x.no_alloc) {
+        auto& copies = x.h->resident[x.dt][x.L.route];
+        hipDevice_t at = dev;  // a null stream is the current device's
+        if (x.stream && hipStreamGetDevice(x.stream, &at) != hipSuccess) {
+            (void)hipGetLastError();
+            at = -1;
+        }
         std::lock_guard<std::mutex> lk(x.h->res_mu);
-        for (const auto& r : copies)
-            if (r.first == dev) {
-                x.tab = (const uint8_t*)r.second;
-                return QL_OK;
-            }
+        ql_circuit::Resident* mine = nullptr;
+        for (auto& r : copies)
+            if (r.dev == dev) mine = &r;
+        if (at == dev && mine && mine->arrived) {
+            x.tab = (const uint8_t*)mine->p;
+            return QL_OK;
+        }
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        void* p = nullptr;
-        if (hipStreamIsCapturing(x.stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone &&
-            hipMalloc(&p, T.blob.size()) == hipSuccess) {
-            if (hipMemcpy(p, T.blob.data(), T.blob.size(), hipMemcpyHostToDevice) == hipSuccess) {
-                copies.push_back({dev, p});
-                x.tab = (const uint8_t*)p;
+        const bool eager = hipStreamIsCapturing(x.stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+        if (at == dev && eager && mine && hipEventQuery(mine->ready) == hipSuccess) {
+            mine->arrived = true;
+            x.tab = (const uint8_t*)mine->p;
+            return QL_OK;
+        }
+        if (at == dev && eager && !mine) {
+            ql_circuit::Resident r;
+            r.dev = dev;
+            RelaxedCapture rc;
+            if (hipMalloc(&r.p, T.blob.size()) == hipSuccess &&
+                hipEventCreateWithFlags(&r.ready, hipEventDisableTiming) == hipSuccess &&
+                hipMemcpyAsync(r.p, T.blob.data(), T.blob.size(), hipMemcpyHostToDevice, x.stream) == hipSuccess &&
+                hipEventRecord(r.ready, x.stream) == hipSuccess) {
+                copies.push_back(r);
+                x.tab = (const uint8_t*)r.p;
                 return QL_OK;
             }
-            (void)hipFree(p);
+            if (r.ready) (void)hipEventDestroy(r.ready);
+            if (r.p) (void)hipFree(r.p);  // (waits for a copy that was queued)
         }
         (void)hipGetLastError();
     }
@@ -1204,7 +1232,10 @@ void ql_circuit_destroy(ql_circuit* h) {
     // (freeing waits for the device, so for every queued call that reads the tables)
     for (auto& d : h->resident)
         for (auto& v : d)
-            for (auto& r : v) (void)hipFree(r.second);
+            for (auto& r : v) {
+                (void)hipFree(r.p);
+                (void)hipEventDestroy(r.ready);
+            }
     for (auto& e : h->ev) {
         (void)hipEventDestroy(e.a);
         (void)hipEventDestroy(e.b);

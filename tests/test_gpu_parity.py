@@ -325,8 +325,8 @@ def test_forward_only_and_null_grads():
 
 def test_destroy_right_after_a_call():
     """A handle destroyed while its call may still be queued: the outputs are
-    still right (the table upload reads the handle's pinned copy, and
-    destruction waits for the device first)."""
+    still right (calls read the handle's tables, and destruction waits for the
+    device first)."""
     import gc
     n, F, P, B = 14, 3, 5, 2
     gates = W.random_circuit(n, 120, F, P, seed=33)

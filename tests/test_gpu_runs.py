@@ -277,3 +277,59 @@ def test_lds_rule(n, dtype, limit):
         close(big[k][:limit], small[k], 2 * TOL[dtype], f"n={n} {dtype}", k)
         close(big[k][-1:], last[k], TOL[dtype], f"n={n} {dtype}", k)
     close(big["grad_weights"], small["grad_weights"] + last["grad_weights"], 2 * TOL[dtype], f"n={n} {dtype}", "grad_weights")
+
+
+@pytest.mark.parametrize("n", [9, 13])
+def test_first_call_does_not_wait(n):
+    """The first call of a handle returns while the stream is busy, calls on
+    other streams do not wait for its tables, and all results agree with those
+    of later calls."""
+    gates = W.random_circuit(n, 60, 3, 4, seed=n)
+    x, w, g = (_dev(a, "c64") for a in W.random_inputs(4, 3, 4, n, seed=n, dtype="c64"))
+    r, other = (Q.Runner(Q.Circuit(n, gates, 3, 4), "c64") for _ in range(2))
+    want = [t.clone() for t in other.forward_backward(x, w, g)]
+    side_r = Q.Runner(r.c, "c64")  # the same handle, a workspace of its own
+    for q in (r, side_r):
+        q.workspace(4, Q.MODE_FWD_BWD)
+    side, busy, done = torch.cuda.Stream(), torch.cuda.Event(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(1 << 28)  # about 0.1 s
+    busy.record()
+    got = r.forward_backward(x, w, g)
+    assert not busy.query()
+    with torch.cuda.stream(side):
+        got_side = side_r.forward_backward(x, w, g)
+        done.record()
+    done.synchronize()
+    assert not busy.query()
+    torch.cuda.synchronize()
+    again = r.forward_backward(x, w, g)
+    torch.cuda.synchronize()
+    for a, b, c, d in zip(want, got, got_side, again):
+        assert torch.equal(a, b) and torch.equal(a, c) and torch.equal(a, d)
+
+
+@pytest.mark.parametrize("n,dtype", [(6, "c64"), (9, "c128"), (13, "c64")])
+def test_first_call_captured(n, dtype):
+    """A handle whose first call is captured (its tables go to the workspace in
+    the graph): every replay gives the eager results, with eager calls between."""
+    gates = W.random_circuit(n, 60, 3, 4, seed=n)
+    x, w, g = (_dev(a, dtype) for a in W.random_inputs(4, 3, 4, n, seed=n, dtype=dtype))
+    eager = Q.Runner(Q.Circuit(n, gates, 3, 4), dtype)
+    want = [t.clone() for t in eager.forward_backward(x, w, g)]
+    r = Q.Runner(Q.Circuit(n, gates, 3, 4), dtype)
+    r.workspace(4, Q.MODE_FWD_BWD_KEEP)
+    outs = tuple(torch.empty_like(t) for t in want)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        r.forward_backward(x, w, g, outs=outs)
+    for _ in range(4):
+        for t in outs:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(outs, want))
+        mine = Q.Runner(r.c, dtype).forward_backward(x, w, g)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(mine, want))
