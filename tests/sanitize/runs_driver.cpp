@@ -167,6 +167,19 @@ int check(int n_case, const Circuit& c, const RunPlan& p, long& exchanges, long&
     };
     if (p.steps.empty() || p.steps.back().op != RS_END) return fail(n_case, "no end");
     const int S = (int)p.steps.size() - 1;
+    // matrices are numbered in the order of the steps, and a run knows its step's
+    int next = p.n_pos;
+    for (int i = 0; i < S; i++) {
+        const DevRunStep& s = p.steps[i];
+        if (s.op >= RS_EXCHANGE) continue;
+        const int first = (int)s.mat / 4, end = first + (s.op < RS_LAYER_REAL ? 2 : p.n_pos);
+        if (first != next) return fail(n_case, "order of the matrices");
+        next = end;
+        for (const DevRunEntry& e : p.entries)
+            if ((int)e.mat / 4 >= first && (int)e.mat / 4 < end && (e.layer_first != first || e.layer_end != end))
+                return fail(n_case, "matrices of a run's step");
+    }
+    if (4 * next != p.n_mat) return fail(n_case, "number of matrices");
     for (int i = 0; i < S; i++) {
         const DevRunStep& s = p.steps[i];
         if (s.op < RS_LAYER_REAL && ((int)s.op >= p.n_pos || (int)s.ctl >= p.log_t)) return fail(n_case, "controlled run's positions");

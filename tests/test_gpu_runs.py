@@ -43,13 +43,15 @@ def _fb(runner, dtype, x, w, g):
 
 
 def _all_paths(n, gates, F, P, B, dtype, seed, embed=None, pauli_p=None, amplitude=False):
-    """Forward + adjoint, forward alone and final states, each against the oracle."""
+    """Forward + adjoint and forward alone, in the run kernel, and final states,
+    each against the oracle."""
     x, w, g = W.random_inputs(B, F, P, n, seed=seed, dtype=dtype)
     if pauli_p is not None:
         x[:, F - len(pauli_p):] = np.random.default_rng(seed).random((B, len(pauli_p))).astype(x.dtype)
     x[0, 0] = 9.0  # well outside [-pi, pi]
     r = Q.Runner(Q.Circuit(n, gates, F, P, embed=embed, pauli_p=pauli_p), dtype)
     what = f"n={n} {dtype} B={B} G={len(gates)}"
+    assert [r.c.call_kernel(dtype, B, m) for m in (Q.MODE_FWD, Q.MODE_FWD_BWD)] == ["runs", "runs"], what
     want = oracle.run(n, gates, x, w, grad_out=g, embed=embed, pauli_p=pauli_p, want_state=True)
     check(_fb(r, dtype, x, w, g), want, TOL[dtype], what)
     e = r.forward(_dev(x, dtype), _dev(w, dtype))
@@ -65,18 +67,22 @@ def test_every_gate_kind(n, dtype):
     """Every size of the kernel's layouts (registers, lanes, wavefronts): runs,
     controlled runs, exchanges, signs and Pauli channels."""
     F, P = 4, 6
-    gates = W.random_circuit(n, 30 + 8 * n, F, P, seed=900 + n, kinds=ALL)
+    # 4096 complex128 amplitudes of psi and lambda leave LDS for a short circuit only
+    G = 30 if (n, dtype) == (12, "c128") else 30 + 8 * n
+    gates = W.random_circuit(n, G, F, P, seed=900 + n, kinds=ALL)
     channels = np.array([[W.PAULI, q % n, -1, W.SRC_INPUT, F + q] for q in range(3)], np.int32)
     half = len(gates) // 2
     gates = np.concatenate([gates[:half], channels, gates[half:]])
     _all_paths(n, gates, F + 3, P, 3, dtype, seed=n, pauli_p=[[0.3, 0.3, 0.3], [0.2, 0.5, 0.1], [0.1, 0.1, 0.6]])
 
 
-@pytest.mark.parametrize("n,G,B", [(5, 700, 2), (10, 500, 1), (3, 0, 2), (9, 0, 1)])
-def test_long_and_empty(n, G, B):
+@pytest.mark.parametrize("n,G,B,dtype", [(5, 700, 2, "c128"), (10, 500, 1, "c64"), (3, 0, 2, "c128"), (9, 0, 1, "c128"),
+                                         (6, 80, 1, "c128"), (7, 60, 1, "c64"), (11, 50, 1, "c128")])
+def test_long_and_empty(n, G, B, dtype):
     """More steps than one chunk of 64 records, no gates at all, and a single
-    sample (whose weight gradients the kernel writes itself)."""
-    _all_paths(n, W.random_circuit(n, G, 3, 4, seed=G + n, kinds=ALL), 3, 4, B, "c128", seed=n)
+    sample of one or several wavefronts (whose weight gradients the kernel
+    writes itself)."""
+    _all_paths(n, W.random_circuit(n, G, 3, 4, seed=G + n, kinds=ALL), 3, 4, B, dtype, seed=n)
 
 
 @pytest.mark.parametrize("n,dtype", [(2, "c64"), (6, "c128"), (9, "c64"), (12, "c128")])
@@ -114,16 +120,36 @@ def test_param_shift(n, dtype):
 @pytest.mark.parametrize("n,dtype,limit,circuit", [(11, "c128", 256, "random"), (12, "c64", 256, "random"),
                                                    (11, "c128", 512, "layers"), (12, "c64", 512, "layers")])
 def test_batch_rule(n, dtype, limit, circuit):
-    """On both sides of the batch from which the tile kernel takes the step:
-    the rows of the smaller batch agree, and the last row with the oracle."""
+    """On both sides of the batch from which the tile kernel takes the step: the
+    rows of the smaller batch agree, the last row with the oracle, and the weight
+    gradients of the larger batch are those of the smaller plus the last row's."""
     F, P = 3, 4
-    gates = W.random_circuit(n, 40, F, P, seed=n) if circuit == "random" else run_layers(n, 2, F, P, seed=n)
+    gates = W.random_circuit(n, 40, F, P, seed=n, kinds=ALL) if circuit == "random" else run_layers(n, 2, F, P, seed=n)
     x, w, g = W.random_inputs(limit + 1, F, P, n, seed=n, dtype=dtype)
     r = Q.Runner(Q.Circuit(n, gates, F, P), dtype)
+    assert (r.c.call_kernel(dtype, limit), r.c.call_kernel(dtype, limit + 1)) == ("runs", "tile")
     big, small = _fb(r, dtype, x, w, g), _fb(r, dtype, x[:limit], w, g[:limit])
+    last = oracle.run(n, gates, x[-1:], w, grad_out=g[-1:])
     for k in ("expz", "grad_inputs"):
         close(big[k][:limit], small[k], 2 * TOL[dtype], f"n={n} {dtype}", k)  # each within TOL of the truth
-        close(big[k][-1:], oracle.run(n, gates, x[-1:], w, grad_out=g[-1:])[k], TOL[dtype], f"n={n} {dtype}", k)
+        close(big[k][-1:], last[k], TOL[dtype], f"n={n} {dtype}", k)
+    close(big["grad_weights"], small["grad_weights"] + last["grad_weights"], 2 * TOL[dtype], f"n={n} {dtype}", "grad_weights")
+
+
+@pytest.mark.parametrize("n,dtype,limit,circuit", [(12, "c64", 512, "random"), (11, "c128", 512, "random"), (12, "c64", 1536, "layers"),
+                                                   (11, "c128", 768, "layers"), (12, "c128", 256, "random"),
+                                                   (12, "c128", 768, "layers")])
+def test_batch_rule_forward(n, dtype, limit, circuit):
+    """The same of the forward: <Z> of both kernels agrees, and the last rows
+    with the oracle."""
+    F, P = 3, 4
+    gates = W.random_circuit(n, 40, F, P, seed=n, kinds=ALL) if circuit == "random" else run_layers(n, 2, F, P, seed=n)
+    x, w, _ = W.random_inputs(limit + 1, F, P, n, seed=n, dtype=dtype)
+    r = Q.Runner(Q.Circuit(n, gates, F, P), dtype)
+    assert [r.c.call_kernel(dtype, limit + i, Q.MODE_FWD) for i in (0, 1)] == ["runs", "tile"]
+    big, small = (r.forward(_dev(x[:rows], dtype), _dev(w, dtype)).cpu().double().numpy() for rows in (limit + 1, limit))
+    close(big[:limit], small, 2 * TOL[dtype], f"n={n} {dtype}", "expz")
+    close(big[-2:], oracle.run(n, gates, x[-2:], w)["expz"], TOL[dtype], f"n={n} {dtype}", "expz")
 
 
 def run_layers(n, layers, F, P, seed):

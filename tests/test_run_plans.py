@@ -40,7 +40,7 @@ def test_run_plans_on_the_host(tmp_path):
                 kinds = [ALL, (W.RX, W.RY, W.RZ, W.CNOT), (W.H, W.RZ, W.CZ, W.RY), (W.CRX, W.CRY, W.CRZ, W.RZ, W.RX),
                          (W.CNOT, W.CZ, W.RZ, W.RX), (W.CNOT, W.CRY, W.H, W.RY)][seed]
                 _record(f, n, W.random_circuit(n, 12 * n + 10, 4, 6, seed=100 * n + seed, kinds=kinds), 4, 6,
-                        embed=(W.EMBED_AMPLITUDE, 0) if seed == 9 else (0, 0))
+                        embed=(0, 0))
             layered = W.layered_circuit(n, "h_rz" if n % 2 else "ry", 3, (W.RY, W.RZ), W.CZ if n % 2 else W.CNOT,
                                         ("ring", "linear", "brick")[n % 3])
             noisy, pp, k = W.with_depolarizing(layered, n, n, 0.3, every=max(len(layered) // 4, 1))
