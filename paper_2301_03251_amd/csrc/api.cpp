@@ -564,7 +564,13 @@ int place_tables(Ctx& x, int dev) {
             x.tab = (const uint8_t*)mine->p;
             return QL_OK;
         }
-        if (at == dev && eager && !mine) {
+        bool room = at == dev && eager && !mine;
+        try {
+            if (room) copies.reserve(copies.size() + 1);
+        } catch (const std::bad_alloc&) {
+            room = false;
+        }
+        if (room) {
             ql_circuit::Resident r;
             r.dev = dev;
             RelaxedCapture rc;

@@ -1383,7 +1383,7 @@ __device__ __forceinline__ void chunk_of(int bb, int lane, int64_t& lo, int64_t&
 // block total into bsum. The block is read in coalesced rows of 64
 // amplitudes. A full block (4096 amplitudes) has 64 rows of one chunk each:
 // the 64 row sums come from one reduction of 64 values per lane (bound by the
-// reads: 128 MiB of states 53 -> 35 us against a butterfly per row). Smaller
+// reads: 128 MiB of states 53 -> 21 us against a butterfly per row). Smaller
 // states: a row holds 64 / csz whole chunks, summed by a butterfly over each
 // group of csz lanes, and lane c keeps chunk c's sum. Fixed orders.
 template <typename T2>
