@@ -525,7 +525,8 @@ Ctx context(ql_circuit* h, int dt, const Layout& L, void* ws, hipStream_t stream
             L.route == RUNS};
 }
 
-// Allocations beside a stream in capture, of this or another thread.
+// Allocations and event queries beside a stream in capture, of this or another
+// thread.
 struct RelaxedCapture {
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
@@ -557,6 +558,7 @@ int place_tables(Ctx& x, int dev) {
             x.tab = (const uint8_t*)mine->p;
             return QL_OK;
         }
+        RelaxedCapture relaxed;
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         const bool eager = hipStreamIsCapturing(x.stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
         if (at == dev && eager && mine && hipEventQuery(mine->ready) == hipSuccess) {
@@ -573,7 +575,6 @@ int place_tables(Ctx& x, int dev) {
         if (room) {
             ql_circuit::Resident r;
             r.dev = dev;
-            RelaxedCapture rc;
             if (hipMalloc(&r.p, T.blob.size()) == hipSuccess &&
                 hipEventCreateWithFlags(&r.ready, hipEventDisableTiming) == hipSuccess &&
                 hipMemcpyAsync(r.p, T.blob.data(), T.blob.size(), hipMemcpyHostToDevice, x.stream) == hipSuccess &&
