@@ -349,7 +349,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     DevRunEntry my{};                                      // this thread's first run
     if (tid < a.n_entries) my = entries[tid];
     for (int i = tid; i < a.n_words; i += nt) words[i] = words_g[i];
-    if constexpr (NORMS)
+    if (NORMS && a.bwd)
         for (int i = tid; i < a.n_mats; i += nt) scale[i] = 0.0;
     if (a.bwd && tid < n) go[tid] = ((const Real*)a.grad_out)[b * n + qubit_at(a.last_qubit, tid)];
     const int64_t bs = a.vper > 0 ? (a.v0 + b) / a.vper : b;
@@ -375,6 +375,7 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
         cs[m.cs] = make_double2(c, sn);
     }
     __syncthreads();
+    double norms = 0.0;  // deviations of this thread's runs
     for (int i = tid; i < a.n_entries; i += nt) {
         const DevRunEntry e = i == tid ? my : entries[i];
         for (int v = 0; v < 1 + e.controlled; ++v) {
@@ -399,8 +400,16 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
             o[2] = to_real<T2, Real>(odd ? make_double2(-a1.x, a1.y) : make_double2(a1.x, -a1.y));
             o[3] = to_real<T2, Real>(c1);
             if constexpr (NORMS)
-                if (!e.controlled) scale[e.mat >> 2] = deviation(o[0], o[3]);
+                if (!e.controlled) {
+                    const double d = deviation(o[0], o[3]);
+                    norms += d;
+                    if (a.bwd) scale[e.mat >> 2] = d;
+                }
         }
+    }
+    if constexpr (NORMS) {
+        norms = wave_total(norms);
+        if (lane == 0) ((double*)(smem + a.lds.norm))[wave] = norms;
     }
     __syncthreads();
     if (NORMS && a.bwd && wave == 0) {  // the sums over the matrices up to each (read after the next barrier)
@@ -562,7 +571,18 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
     // ---- <Z> and the final state, in the last layout
     const LateArgs f = late_args();
     const uint64_t last = f->last_qubit;
-    double *red = (double*)(smem + f->lds.red), *norms = (double*)(smem + f->lds.scale);
+    // sums of a wavefront: four of 16 lanes each in fp32, added in fp64 below
+    constexpr int ROWS = sizeof(Real) == 4 ? 4 : 1;
+    Real* red = (Real*)(smem + f->lds.red);  // [n][NW][ROWS]
+    auto put_sum = [&](int p, Real v) {
+        if constexpr (ROWS == 4) {
+            v = row_sum(v);
+            if ((lane & 15) == 0) red[(p * NW + wave) * 4 + (lane >> 4)] = v;
+        } else {
+            const double t = wave_total(v);
+            if (lane == 0) red[p * NW + wave] = t;
+        }
+    };
     if (f->psi_out && active) {
 #pragma unroll
         for (int i = 0; i < R; ++i) ((T2*)f->psi_out)[b * dim + amp_index(last, i)] = ps[i];
@@ -579,35 +599,17 @@ __global__ void __launch_bounds__(MAXT) k_runs(const RunArgs a, const uint2* __r
             for (int m = 0; m < LOG_R; ++m) dm[m] += (i >> m & 1) ? -p : p;
         }
 #pragma unroll
-        for (int m = 0; m < LOG_R; ++m) {
-            const double t = wave_total(dm[m]);
-            if (lane == 0) red[m * NW + wave] = t;
-        }
+        for (int m = 0; m < LOG_R; ++m) put_sum(m, dm[m]);
 #pragma unroll
         for (int l = 0; l < 6; ++l)
-            if (LOG_R + l < n) {
-                const double t = wave_total((sid >> l & 1) ? -pt : pt);
-                if (lane == 0) red[(LOG_R + l) * NW + wave] = t;
-            }
-        if (NW > 1) {
-            const double t = wave_total(pt);
-            if (lane == 0)
-                for (int p = LOG_R + 6; p < n; ++p) red[p * NW + wave] = (wave >> (p - LOG_R - 6) & 1) ? -t : t;
-        }
-        if (NORMS && !f->bwd) {
-            double t = 0.0;
-            for (int i = tid; i < f->n_mats; i += nt) t += norms[i];
-            t = wave_total(t);
-            if (lane == 0) red[n * NW + wave] = t;
-        }
+            if (LOG_R + l < n) put_sum(LOG_R + l, (sid >> l & 1) ? -pt : pt);
+        for (int p = LOG_R + 6; p < n; ++p) put_sum(p, (wave >> (p - LOG_R - 6) & 1) ? -pt : pt);
         __syncthreads();
         if (tid < n) {
             double t = 0.0, u = 1.0;
-            for (int w = 0; w < NW; ++w) {
-                t += red[tid * NW + w];
-                if (NORMS && !f->bwd) u += red[n * NW + w];
-            }
-            if (NORMS && f->bwd) u += norms[f->n_mats - 1];
+            for (int w = 0; w < NW * ROWS; ++w) t += (double)red[tid * NW * ROWS + w];
+            if constexpr (NORMS)
+                for (int w = 0; w < NW; ++w) u += ((const double*)(smem + f->lds.norm))[w];
             ((Real*)f->expz)[b * n + qubit_at(last, tid)] = (Real)(NORMS ? t / u : t);
         }
     }
@@ -802,9 +804,10 @@ RunLds runs_lds(int dtype, const RunPlan& p, int n_slots, bool bwd) {
     l.mat = put((size_t)(p.n_mat + 4 * 9) * amp);  // a layer fetches the rows of all 9 positions
     l.cs = put((size_t)p.n_cs * 16);
     l.kind = put(p.members.size());
-    l.scale = put(dtype == 0 ? (size_t)(p.n_mat / 4) * 8 : 0);
+    l.scale = put(dtype == 0 && bwd ? (size_t)(p.n_mat / 4) * 8 : 0);
     l.words = put(p.words.size() * 4);
-    l.red = put((size_t)(p.n + 1) * p.n_waves * 8);
+    l.norm = put(dtype == 0 ? (size_t)p.n_waves * 8 : 0);
+    l.red = put((size_t)p.n * p.n_waves * (dtype == 0 ? 16 : 8));
     l.go = put(bwd ? (size_t)p.n * real : 0);
     l.sum = put(bwd ? (size_t)p.n_grads * p.n_waves * 3 * real : 0);
     l.gs = put(bwd ? (size_t)n_slots * 8 : 0);

@@ -10,7 +10,7 @@ namespace qlayer {
 struct RunLds {
     uint32_t alt;    // bytes from one exchange buffer to the next (0: only one, used with two barriers)
     uint32_t lam;    // bytes from psi's part of an exchange buffer to lambda's
-    uint32_t mat, cs, kind, scale, words, red, go, sum, gs;
+    uint32_t mat, cs, kind, scale, words, norm, red, go, sum, gs;
     uint32_t total;
 };
 

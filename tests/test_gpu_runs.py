@@ -265,7 +265,7 @@ LONG = {"c64": 3e-5, "c128": 1e-12}
 
 
 @pytest.mark.parametrize("n,G,B,dtype,kernels", [
-    (7, 2000, 3, "c128", ("whole", "whole")), (6, 1500, 3, "c64", ("whole", "whole")),
+    (7, 2000, 3, "c128", ("whole", "whole")), (6, 2000, 3, "c64", ("whole", "whole")),
     (7, 1200, 2, "c64", ("runs", "whole")), (4, 1000, 2, "c128", ("runs", "whole")),
     (6, 400, 2100, "c64", ("whole", "whole"))])
 def test_long_small_circuits(n, G, B, dtype, kernels):
